@@ -3241,14 +3241,36 @@ __device__ void conclude_block(PassState* __restrict__ st, const double* __restr
   __shared__ double wJ[4], wS[4], wN[4];
   __shared__ long long wU[4], wE[4], wP[4];
   __shared__ int wM[4];
+  __shared__ long long wA[2];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   double J = 0.0, sh = 0.0, nm = 0.0;
   long long U = 0, E = 0, Pc = 0;
   int jm = INT_MAX;  // lowest empty cluster
-  for (int64_t b = tid; b < nb; b += 256) {
-    if (!jslots) J += ld_agent(&Jpart[b]);
-    U += ld_agent(&upart[2 * b]);
-    Pc += ld_agent(&upart[2 * b + 1]);
+  // the sorted update's J: exact integer limbs of 2^-FJ and 2^(40-FJ), one slot
+  // per lane of the last wave
+  long long a0 = 0, a1 = 0;
+  if (jslots && wv == 3 && lane < kSlots) {
+    a0 = ld_agent(&jslots[2 * lane]);
+    a1 = ld_agent(&jslots[2 * lane + 1]);
+  }
+  // partials of four blocks in flight per thread, added in block order
+  for (int64_t b0 = tid; b0 < nb; b0 += 1024) {
+    double jv[4];
+    long long uv[4], pv[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int64_t b = b0 + 256 * u;
+      const bool in = b < nb;
+      jv[u] = in && !jslots ? ld_agent(&Jpart[b]) : 0.0;
+      uv[u] = in ? ld_agent(&upart[2 * b]) : 0;
+      pv[u] = in ? ld_agent(&upart[2 * b + 1]) : 0;
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      J += jv[u];
+      U += uv[u];
+      Pc += pv[u];
+    }
   }
   if (update)
     for (int j = tid; j < k; j += 256) {
@@ -3262,6 +3284,15 @@ __device__ void conclude_block(PassState* __restrict__ st, const double* __restr
   // fixed-order reductions: lanes of a wave, then the four waves
   J = wave_sum(J); U = wave_sum(U); Pc = wave_sum(Pc); E = wave_sum(E);
   sh = wave_max(sh); nm = wave_max(nm);
+  if (jslots && wv == 3) {
+    if (lane < kSlots) jslots[2 * lane] = jslots[2 * lane + 1] = 0;
+    a0 = wave_sum(a0);
+    a1 = wave_sum(a1);
+    if (lane == 0) {
+      wA[0] = a0;
+      wA[1] = a1;
+    }
+  }
   if (lane == 0) {
     wJ[wv] = J; wU[wv] = U; wP[wv] = Pc; wE[wv] = E; wS[wv] = sh; wN[wv] = nm; wM[wv] = jm;
   }
@@ -3274,14 +3305,8 @@ __device__ void conclude_block(PassState* __restrict__ st, const double* __restr
     const double St = fmax(fmax(wS[0], wS[1]), fmax(wS[2], wS[3]));
     const double Nt = fmax(fmax(wN[0], wN[1]), fmax(wN[2], wN[3]));
     if (jslots) {
-      // the sorted update's J: exact integer limbs of 2^-FJ and 2^(40-FJ)
-      long long a0 = 0, a1 = 0;
-      for (int q = 0; q < kSlots; ++q) {
-        a0 += ld_agent(&jslots[2 * q]);
-        a1 += ld_agent(&jslots[2 * q + 1]);
-        jslots[2 * q] = 0;
-        jslots[2 * q + 1] = 0;
-      }
+      a0 = wA[0];
+      a1 = wA[1];
       a1 += a0 >> 40;
       a0 &= (1ll << 40) - 1;
       Jt = ldexp((double)a1, 40 - st->FJ) + ldexp((double)a0, -st->FJ);
@@ -3314,6 +3339,15 @@ __device__ void conclude_block(PassState* __restrict__ st, const double* __restr
 // keeps its center -- its movement and norm, and the BF16 copy of the screen.
 // With jslots, J is that of the sorted update.  The last block concludes the
 // pass.
+// A chain of dependent memory accesses bounds it (a few hundred kilobytes, but
+// each step waits about a microsecond for the last), so everything a center
+// needs is requested at once: a thread owns dim t0 + tid % DT and every
+// (256 / DT)-th slot row of it (DT the power of two that covers d, at most
+// 256), eight rows in flight; the slot groups are then added by shuffles and
+// through LDS.  (With eight dims a round, each waiting for the last, it took
+// 23.3 us at 64 dims and k = 256 against 15.4 us now, and the batched form 75
+// against 40 us for the 30 problems of 32 and 128 dims it was measured on; a
+// pass of a few dims stays at 7.7 us, the latency of the chain that is left.)
 __device__ void finalize_center(
     int j, long long* __restrict__ slots, long long* __restrict__ jslots, int k, int d,
     PassState* __restrict__ st, int update, double* __restrict__ c64, float* __restrict__ cw,
@@ -3330,45 +3364,59 @@ __device__ void finalize_center(
   // this pass's index in the stage (the last block of the pass advances it
   // only after every block has read it)
   const int64_t it = st->iter;
+  const int F = st->F;
+  const float B = st->B;
   if (!update) trace_c = nullptr, trace_n = nullptr;
   double* tc = trace_c ? trace_c + (it * k + j) * d : nullptr;
   long long* col = slots + (int64_t)j * (d + 1);
-  __shared__ long long scnt[kSlots];  // points per slot row (biased sums)
+  __shared__ long long part[256];
   __shared__ long long sN;
   __shared__ double wred[3][4];
   __shared__ int last;
-  if (wv == 0) {
-    long long v = 0;
-    if (lane < kSlots) scnt[lane] = 0;
-    if (lane < nslots) {
-      v = col[(int64_t)lane * C + d];
-      col[(int64_t)lane * C + d] = 0;
-      scnt[lane] = v;
-    }
-    v = wave_sum(v);
-    if (lane == 0) sN = v;
-  }
-  __syncthreads();
-  const long long Nj = sN;
-  const int F = st->F;
+  int dl = 3;  // at least 8 dims a round: at most 32 slot groups
+  while ((1 << dl) < d && dl < 8) ++dl;
+  const int DT = 1 << dl, SG = 256 >> dl, c = tid & (DT - 1), sg = tid >> dl;
+  const int GW = max(DT, 64);  // stride of the slot groups' partial sums in LDS
+  // the points of the cluster (counts of the slot rows)
+  long long cv = 0;
+  if (tid < nslots) cv = col[(int64_t)tid * C + d];
   double sh = 0.0, nn = 0.0, ee = 0.0;
-  const int r = tid & 31, c = tid >> 5;  // 32 slots x 8 dims per round
-  for (int t0 = 0; t0 < d; t0 += 8) {
+  for (int t0 = 0; t0 < d; t0 += DT) {
     const int t = t0 + c;
+    const bool in = t < d;
+    double cold = 0.0;
+    if (update && sg == 0 && in) cold = c64[(int64_t)j * d + t];
     long long sv = 0;
-    if (t < d && r < nslots) {
-      sv = col[(int64_t)r * C + t];
-      col[(int64_t)r * C + t] = 0;
+    if (in)
+      for (int r0 = sg; r0 < nslots; r0 += 8 * SG) {
+        long long v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+          v[u] = r0 + u * SG < nslots ? col[(int64_t)(r0 + u * SG) * C + t] : 0;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          sv += v[u];
+          if (r0 + u * SG < nslots) col[(int64_t)(r0 + u * SG) * C + t] = 0;
+        }
+      }
+    for (int o = DT; o < 64; o <<= 1) sv += __shfl_xor(sv, o);
+    if (t0 > 0) __syncthreads();  // part of the previous round was read
+    part[tid] = sv;
+    if (t0 == 0 && wv == 0) {
+      if (tid < nslots) col[(int64_t)tid * C + d] = 0;
+      cv = wave_sum(cv);
+      if (lane == 0) sN = cv;
+    }
+    __syncthreads();
+    if (tid < DT && in) {
+      const long long Nj = sN;
+      sv = part[c];
+      for (int g = GW; g < 256; g += GW) sv += part[g + c];
       // biased sums: every point added kSumBias + q (mod 2^64)
       if (biased)
-        sv = (long long)((unsigned long long)sv - (unsigned long long)scnt[r] * kSumBias);
-    }
-    // the 32 slot rows of dim t are the lanes of one half wave
-    for (int o = 16; o > 0; o >>= 1) sv += __shfl_xor(sv, o);
-    if (r == 0 && t < d) {
+        sv = (long long)((unsigned long long)sv - (unsigned long long)Nj * kSumBias);
       const double sum = ldexp((double)sv, -F);
       if (update) {
-        const double cold = c64[(int64_t)j * d + t];
         if (tc) tc[t] = cold;
         const double cnew = Nj > 0 ? sum / (double)Nj : cold;
         const double diff = cnew - cold;
@@ -3392,28 +3440,38 @@ __device__ void finalize_center(
       if (S_out) S_out[(int64_t)j * d + t] = sum;
     }
   }
-  sh = wave_sum(sh);
-  nn = wave_sum(nn);
-  ee = wave_sum(ee);
-  if (lane == 0) {
-    wred[0][wv] = sh;
-    wred[1][wv] = nn;
-    wred[2][wv] = ee;
+  const long long Nj = sN;
+  if (update) {
+    // lanes past DT hold zeros: the butterfly covers the lanes of the dims
+    for (int o = min(DT, 64) >> 1; o > 0; o >>= 1) {
+      sh += __shfl_xor(sh, o);
+      nn += __shfl_xor(nn, o);
+      ee += __shfl_xor(ee, o);
+    }
+    if (DT > 64) {
+      if (lane == 0) {
+        wred[0][wv] = sh;
+        wred[1][wv] = nn;
+        wred[2][wv] = ee;
+      }
+      __syncthreads();
+      if (tid == 0) {
+        sh = (wred[0][0] + wred[0][1]) + (wred[0][2] + wred[0][3]);
+        nn = (wred[1][0] + wred[1][1]) + (wred[1][2] + wred[1][3]);
+        ee = (wred[2][0] + wred[2][1]) + (wred[2][2] + wred[2][3]);
+      }
+    }
   }
-  __syncthreads();
   const bool new_copy = update && cb16;  // the BF16 copy of this center was rewritten
   if (tid == 0) {
-    const double rd0 = (wred[0][0] + wred[0][1]) + (wred[0][2] + wred[0][3]);
-    const double rn0 = (wred[1][0] + wred[1][1]) + (wred[1][2] + wred[1][3]);
-    const double re0 = (wred[2][0] + wred[2][1]) + (wred[2][2] + wred[2][3]);
     if (update) {
-      shiftj[j] = sqrt(rd0);
-      cn[j] = (float)rn0;
-      cnorm[j] = sqrt(rn0);
+      shiftj[j] = sqrt(sh);
+      cn[j] = (float)nn;
+      cnorm[j] = sqrt(nn);
       emptyj[j] = Nj == 0 ? 1 : 0;
-      if (cnB) cnB[j] = (float)(rn0 + (double)st->B);
+      if (cnB) cnB[j] = (float)(nn + (double)B);
     }
-    if (new_copy) dcn_max(st, re0);
+    if (new_copy) dcn_max(st, ee);
     if (N_out) N_out[j] = (int64_t)Nj;
     if (trace_n) trace_n[it * k + j] = Nj;
     __threadfence();
