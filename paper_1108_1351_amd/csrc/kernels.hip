@@ -4150,42 +4150,53 @@ __global__ __launch_bounds__(256, 3) void k_batch_screen(const BatchHead* __rest
 
 // Exact cluster sums of the listed instances whose sums do not fit in LDS,
 // from the labels the assignment launch wrote.  A work unit is a range of
-// kBatchSumPts points and a range of skc centers: the block adds the rows of
-// the points labelled inside its center range into an LDS table skc x (d+1)
-// (64-bit integer atomics), then adds the table's non-zero entries into the
-// instance's slot row.  Each point is read once, by the unit of its center
-// range; integer sums do not depend on the order.  A wave takes 64 labels at a
-// time and moves the selected points four at once (16 lanes a point, 8 dims a
-// lane), four such groups in flight.  Persistent: blocks loop over the units.
-__global__ __launch_bounds__(256) void k_batch_sums(const BatchHead* __restrict__ hd,
-                                                    const BatchInst* __restrict__ bi) {
+// b.spts points and a range of skc centers: the block adds the rows of the
+// points labelled inside its center range into an LDS table (64-bit integer
+// atomics), then adds the table's non-zero entries into the instance's slot
+// row.  Integer sums do not depend on the order.  A wave takes 64 labels at a
+// time and moves the selected points in groups of GL lanes a point (8 dims a
+// lane, GL the power of two that covers d), four groups in flight.
+// A unit is a chain of dependent steps (labels, rows, LDS atomics, the flush),
+// so what bounds the kernel is how many units and waves run beside each other:
+// 16 waves a block, two blocks a CU, and units of as few as 1024 points (one
+// label group per wave) when the problems are small.  (Four waves a block and
+// 8192 points a unit took 331 us per pass on 30 problems of 1e3 to 1e5 points
+// in 32 and 128 dims, 47 % of a 43.9 ms batch; the batch takes 23.5 ms now.)  The table keeps dim
+// 8 s + e of a lane's piece s at column e * pieces + s, so the lanes of a point
+// add to consecutive words.
+__global__ __launch_bounds__(1024, 8) void k_batch_sums(const BatchHead* __restrict__ hd,
+                                                     const BatchInst* __restrict__ bi) {
   extern __shared__ __align__(16) unsigned char smem[];
   unsigned long long* S = reinterpret_cast<unsigned long long*>(smem);
-  __shared__ int order[4][64];
+  __shared__ uint8_t order[16][64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int grp = lane >> 4, sub = lane & 15;
   const int ninst = hd->ninst;
   const int64_t units = hd->units;
   for (int64_t u = blockIdx.x; u < units; u += gridDim.x) {
     const BatchInst& b = bi[batch_find(bi, ninst, u, 2)];
     PassState* st = b.st;
     if (b.mode != 1 || ld_agent(&st->done)) continue;
-    const int d = b.d, k = b.k, kc = b.skc;
+    const int d = b.d, k = b.k, kc = b.skc, spts = b.spts;
     const int nkr = (k + kc - 1) / kc;
     const int64_t local = u - b.sunit0;
     const int64_t pb = local / nkr;
     const int c0 = (int)(local - pb * nkr) * kc;
     const int cn = min(kc, k - c0);
-    const int w = d + 1;
-    for (int e = threadIdx.x; e < cn * w; e += 256) S[e] = 0ull;
+    const int np = (d + 7) >> 3;          // 8-dim pieces of a row (d <= 128: at most 16)
+    const int w = 8 * np + 1, ws = d + 1;  // widths of a table row and of a slot row
+    int gl = 0;
+    while ((1 << gl) < np) ++gl;
+    const int sub = lane & ((1 << gl) - 1), grp = lane >> gl, ppi = 64 >> gl;
+    for (int e = threadIdx.x; e < cn * w; e += 1024) S[e] = 0ull;
     __syncthreads();
-    const int64_t i0 = pb * kBatchSumPts, i1 = min(b.n, i0 + kBatchSumPts);
+    const int64_t i0 = pb * spts, i1 = min(b.n, i0 + spts);
     const float sc = st->scale;
     const bool bf = b.dtype == 1;
     // whole 16-byte pieces of every row (8 BF16 or 2 x 4 FP32 dims)
     const bool vec = (d & 7) == 0 && (reinterpret_cast<uintptr_t>(b.X) & 15) == 0;
     const int32_t* lab = b.labels;
-    for (int64_t g = i0 + (int64_t)wave * 64; g < i1; g += 256) {
+    const int t0 = 8 * sub;
+    for (int64_t g = i0 + (int64_t)wave * 64; g < i1; g += 1024) {
       const int64_t i = g + lane;
       const int l = i < i1 ? lab[i] : -1;
       const bool sel = l >= c0 && l < c0 + cn;
@@ -4195,65 +4206,61 @@ __global__ __launch_bounds__(256) void k_batch_sums(const BatchHead* __restrict_
       // the selected lanes in order: order[r] = lane of the r-th selected
       const int rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
                                                  __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
-      if (sel) order[wave][rank] = lane;
+      if (sel) order[wave][rank] = (uint8_t)lane;
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
       __builtin_amdgcn_wave_barrier();
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-      for (int q0 = 0; q0 < cnt; q0 += 16) {
-        constexpr int R = 4;
-        long long qv[R][8];
+      constexpr int R = 4;
+      for (int q0 = 0; q0 < cnt; q0 += R * ppi) {
+        uint4 w0[R], w1[R];  // a lane's 8 dims: BF16 in w0, FP32 in w0 and w1
         int lp[R];
-        bool ok[R];
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-          const int qi = q0 + 4 * r + grp;
-          ok[r] = qi < cnt;
-          const int src = ok[r] ? order[wave][qi] : 0;
+          const int qi = q0 + ppi * r + grp;
+          const bool in = qi < cnt;
+          const int src = in ? order[wave][qi] : 0;
           lp[r] = __shfl(l, src);
-          const int64_t row = (g + src) * d;
-          const int t0 = 8 * sub;
-#pragma unroll
-          for (int e = 0; e < 8; ++e) qv[r][e] = 0;
-          if (ok[r] && t0 < d) {
-            float xv[8];
+          if (!in || t0 >= d) lp[r] = -1;
+          const int64_t row = (g + src) * d + t0;
+          w0[r] = w1[r] = make_uint4(0u, 0u, 0u, 0u);
+          if (lp[r] >= 0) {
             if (vec && bf) {
-              const uint4 v = *reinterpret_cast<const uint4*>(
-                  static_cast<const uint16_t*>(b.X) + row + t0);
-              const uint32_t w4[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-              for (int e = 0; e < 4; ++e) {
-                xv[2 * e] = bf16_lo(w4[e]);
-                xv[2 * e + 1] = bf16_hi(w4[e]);
-              }
+              w0[r] = *reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(b.X) + row);
             } else if (vec) {
-              const float4 v0 = *reinterpret_cast<const float4*>(
-                  static_cast<const float*>(b.X) + row + t0);
-              const float4 v1 = *reinterpret_cast<const float4*>(
-                  static_cast<const float*>(b.X) + row + t0 + 4);
-              xv[0] = v0.x; xv[1] = v0.y; xv[2] = v0.z; xv[3] = v0.w;
-              xv[4] = v1.x; xv[5] = v1.y; xv[6] = v1.z; xv[7] = v1.w;
+              w0[r] = *reinterpret_cast<const uint4*>(static_cast<const float*>(b.X) + row);
+              w1[r] = *reinterpret_cast<const uint4*>(static_cast<const float*>(b.X) + row + 4);
             } else {
+              uint32_t e8[8];
 #pragma unroll
-              for (int e = 0; e < 8; ++e) {
-                const int t = t0 + e;
-                xv[e] = t >= d ? 0.f
-                        : bf ? __uint_as_float((uint32_t)static_cast<const uint16_t*>(b.X)[row + t]
-                                               << 16)
-                             : static_cast<const float*>(b.X)[row + t];
+              for (int e = 0; e < 8; ++e)
+                e8[e] = t0 + e >= d ? 0u
+                        : bf ? (uint32_t)static_cast<const uint16_t*>(b.X)[row + e]
+                             : __float_as_uint(static_cast<const float*>(b.X)[row + e]);
+              if (bf) {
+                w0[r] = make_uint4(e8[0] | e8[1] << 16, e8[2] | e8[3] << 16, e8[4] | e8[5] << 16,
+                                   e8[6] | e8[7] << 16);
+              } else {
+                w0[r] = make_uint4(e8[0], e8[1], e8[2], e8[3]);
+                w1[r] = make_uint4(e8[4], e8[5], e8[6], e8[7]);
               }
             }
-#pragma unroll
-            for (int e = 0; e < 8; ++e) qv[r][e] = (long long)__float2int_rn(xv[e] * sc);
           }
         }
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-          if (!ok[r]) continue;
+          if (lp[r] < 0) continue;
           unsigned long long* Sr = S + (int64_t)(lp[r] - c0) * w;
+          const uint32_t a4[4] = {w0[r].x, w0[r].y, w0[r].z, w0[r].w};
+          const uint32_t b4[4] = {w1[r].x, w1[r].y, w1[r].z, w1[r].w};
 #pragma unroll
-          for (int e = 0; e < 8; ++e)
-            if (8 * sub + e < d) atomicAdd(&Sr[8 * sub + e], (unsigned long long)qv[r][e]);
-          if (sub == 0) atomicAdd(&Sr[d], 1ull);
+          for (int e = 0; e < 8; ++e) {
+            const float xv = bf ? ((e & 1) ? bf16_hi(a4[e >> 1]) : bf16_lo(a4[e >> 1]))
+                                : __uint_as_float(e < 4 ? a4[e & 3] : b4[e & 3]);
+            if (t0 + e < d)
+              atomicAdd(&Sr[e * np + sub],
+                        (unsigned long long)(long long)__float2int_rn(xv * sc));
+          }
+          if (sub == 0) atomicAdd(&Sr[8 * np], 1ull);
         }
       }
       // order[] is rewritten by the next group of labels
@@ -4261,10 +4268,13 @@ __global__ __launch_bounds__(256) void k_batch_sums(const BatchHead* __restrict_
     }
     __syncthreads();
     unsigned long long* row = reinterpret_cast<unsigned long long*>(
-        b.slots + (int64_t)(pb & (b.nslots - 1)) * k * w + (int64_t)c0 * w);
-    for (int e = threadIdx.x; e < cn * w; e += 256) {
+        b.slots + (int64_t)(pb & (b.nslots - 1)) * k * ws + (int64_t)c0 * ws);
+    for (int e = threadIdx.x; e < cn * w; e += 1024) {
       const unsigned long long v = S[e];
-      if (v) atomicAdd(&row[e], v);
+      if (!v) continue;
+      const int c = e / w, q = e - c * w;
+      const int p = q / np, t = q == 8 * np ? d : 8 * (q - p * np) + p;
+      atomicAdd(&row[(int64_t)c * ws + t], v);
     }
     __syncthreads();
   }
@@ -4923,7 +4933,7 @@ hipError_t batch_assign(const BatchHead* hd, const BatchInst* bi, const BatchSha
 }
 
 hipError_t batch_sums(const BatchHead* hd, const BatchInst* bi, int blocks, hipStream_t s) {
-  hipLaunchKernelGGL(k_batch_sums, dim3((unsigned)std::max(1, blocks)), dim3(256),
+  hipLaunchKernelGGL(k_batch_sums, dim3((unsigned)std::max(1, blocks)), dim3(1024),
                      kBatchSumLds, s, hd, bi);
   return hipGetLastError();
 }

@@ -102,8 +102,8 @@ struct BatchInst {
   uint16_t* cb16; float* cnB; int32_t kd16;
   uint16_t* cb16lo;
   // Lloyd passes whose sums do not fit in LDS: units of k_batch_sums (ranges of
-  // kBatchSumPts points x skc centers), 0 when the assignment adds the sums
-  int32_t skc;
+  // spts points x skc centers), 0 when the assignment adds the sums
+  int32_t skc, spts;
   int64_t sunit0, sunits;
   // slot rows the pass adds into (a power of two <= kSlots; the finalize reads
   // only these)
@@ -217,8 +217,10 @@ int64_t batch_resident_blocks(int dtype, int dmax, int ppt, size_t lds, int cus,
 hipError_t batch_assign(const BatchHead* hd, const BatchInst* bi, const BatchShape& sh,
                         hipStream_t s);
 // Cluster sums of the instances with sum units (after the assignment launches).
-constexpr int64_t kBatchSumPts = 8192;
+constexpr int64_t kBatchSumMin = 1024, kBatchSumMax = 8192;  // points of a unit
 constexpr size_t kBatchSumLds = 65536;
+// 64-bit words of a center's row in the LDS table: whole 8-dim pieces, the count
+inline int64_t batch_sum_width(int32_t d) { return (d + 7) / 8 * 8 + 1; }
 hipError_t batch_sums(const BatchHead* hd, const BatchInst* bi, int blocks, hipStream_t s);
 hipError_t batch_finalize(const BatchHead* hd, const BatchInst* bi, int blocks, hipStream_t s);
 hipError_t batch_status(const BatchHead* hd, const BatchInst* bi, BatchStatus* out,

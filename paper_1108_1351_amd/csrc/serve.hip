@@ -233,6 +233,17 @@ bool valid_request(const km_request& r, bool serving) {
   return true;
 }
 
+// Whether the assignment kernel keeps the problem's cluster sums in LDS (the
+// BF16 screen keeps its LDS for the center tiles: its sums always go through
+// k_batch_sums), and the centers of a k_batch_sums unit otherwise.
+bool sums_in_lds(const Job& j) {
+  return !j.screen && (size_t)j.rq.k * (j.rq.d + 1) * 8 <= kSumsLds;
+}
+int32_t sum_centers(const Job& j) {
+  return (int32_t)std::min<int64_t>(j.rq.k,
+                                    (int64_t)kBatchSumLds / (batch_sum_width(j.rq.d) * 8));
+}
+
 // Device bytes of a problem: sampling, subset copy, centers, sums, labels,
 // partials, and (serving) its copy of X.
 size_t job_layout(Job& j, void* base) {
@@ -385,6 +396,19 @@ class Engine {
     std::vector<int64_t> units(ns, 0);
     int64_t centers = 0, sunits = 0;
     unsigned mask = 0;
+    // points of a cluster-sum unit: about four units per CU (two blocks of 16
+    // waves are resident on each), as long as that leaves 1024 points a unit;
+    // more points a unit mean fewer flushes of the LDS table
+    int64_t spts = kBatchSumMin;
+    {
+      int64_t work = 0;
+      for (const Job* j : act)
+        if (j->phase != 3 && !sums_in_lds(*j)) {
+          const int64_t kc = sum_centers(*j);
+          work += (j->phase == 1 ? j->m : j->rq.n) * ((j->rq.k + kc - 1) / kc);
+        }
+      while (spts < kBatchSumMax && work / spts > 4 * device_cus()) spts <<= 1;
+    }
     for (int a = 0; a < na; ++a) {
       Job& j = *act[a];
       const int g = j.shape;
@@ -395,9 +419,7 @@ class Engine {
       b.k = j.rq.k;
       b.dtype = j.rq.dtype == KM_F32 ? 0 : 1;
       b.mode = j.phase == 3 ? 2 : 1;
-      // the BF16 screen keeps its LDS for the center tiles: its sums always
-      // go through k_batch_sums
-      b.lds_sums = !j.screen && (size_t)j.rq.k * (j.rq.d + 1) * 8 <= kSumsLds ? 1 : 0;
+      b.lds_sums = sums_in_lds(j) ? 1 : 0;
       b.cb16 = j.cb16;
       b.cb16lo = j.cb16lo;
       b.cnB = j.cnB;
@@ -419,15 +441,16 @@ class Engine {
       b.Jpart = j.jpart;
       b.upart = j.upart;
       // sums too large for the assignment's LDS: ranges of points x centers
-      b.skc = (int32_t)std::min<int64_t>(b.k, kBatchSumLds / ((size_t)(b.d + 1) * 8));
+      b.skc = sum_centers(j);
+      b.spts = (int32_t)spts;
       b.sunit0 = sunits;
       b.sunits = b.mode == 1 && !b.lds_sums
-                     ? (b.n + kBatchSumPts - 1) / kBatchSumPts * ((b.k + b.skc - 1) / b.skc)
+                     ? (b.n + spts - 1) / spts * ((b.k + b.skc - 1) / b.skc)
                      : 0;
       sunits += b.sunits;
       {
         // one slot row per writer (tile flushes or point ranges), at most kSlots
-        const int64_t writers = b.sunits ? (b.n + kBatchSumPts - 1) / kBatchSumPts : b.units;
+        const int64_t writers = b.sunits ? (b.n + spts - 1) / spts : b.units;
         int ns = 1;
         while (ns < kSlots && ns < writers) ns <<= 1;
         b.nslots = ns;

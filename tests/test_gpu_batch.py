@@ -281,3 +281,19 @@ def test_fit_batch_bf16_screen_shapes(d, k):
     out = km.kmeans_fit_batch([(to_device(Xh), k, 0.2, 3, (8, 8), (1e-5, 1e-5))])
     C, L, info = out[0]
     _check_against_oracle(Xh, C, L, info, k, 0.2, 3, (8, 8), (1e-5, 1e-5), f"d={d} k={k}")
+
+
+@pytest.mark.parametrize("d,dtype,ks", [(128, "bf16", (1, 63, 64, 127)), (100, "bf16", (78, 79)),
+                                        (17, "bf16", (40, 255)), (33, "bf16", (12,)),
+                                        (64, "f32", (112, 113)), (127, "f32", (33,))])
+def test_batch_sums_unit_edges(d, dtype, ks):
+    """Cluster sums of the batched pass at the edges of its work units: one point
+    less and more than a unit's 1024, the last unit ragged, as many centers as
+    one LDS table holds and one more, rows of whole 8-dim pieces and others."""
+    specs = [(n, k) for k in ks for n in (1023, 1024, 1025, 2051) if k <= n]
+    data = [_problem(n, d, k, 40 + n + k, dtype) for n, k in specs]
+    out = km.kmeans_fit_batch([(to_device(Xh), k, 0.5, 3, (3, 4), (0.0, 0.0))
+                               for Xh, (n, k) in zip(data, specs)])
+    for Xh, (C, L, info), (n, k) in zip(data, out, specs):
+        _check_against_oracle(Xh, C, L, info, k, 0.5, 3, (3, 4), (0.0, 0.0),
+                              f"n={n} d={d} k={k} {dtype}")
