@@ -52,7 +52,9 @@ int64_t blocks_max(const Sizes& z) {
 }
 
 bool any_bf16(const Sizes& z) { return (z.stage1 && z.p1.bf16) || z.p2.bf16; }
-bool any_copy16(const Sizes& z) { return (z.stage1 && copy16(z.p1)) || copy16(z.p2); }
+// (the split screen keeps its copy beside the sums, in the slot rows)
+bool own_copy16(const PassPlan& p) { return copy16(p) && !p.split; }
+bool any_copy16(const Sizes& z) { return (z.stage1 && own_copy16(z.p1)) || own_copy16(z.p2); }
 int ks_max(const Sizes& z) { return std::max(z.stage1 ? z.p1.ks : 0, z.p2.ks); }
 
 // Buffers of the sorted update (split paths), sized for the larger stage.
@@ -211,8 +213,8 @@ km_status run_stage(PassBufs b, const PassPlan& plan, int32_t max_iter, double t
   HIP_TRY(row_stats(b.X, b.dtype, rows, b.d, wants_norms(plan), b.st, s));
   HIP_TRY(stage_begin(b.st, max_iter, tol, rows, b.cnorm, b.k, b.d, plan.fused ? 0 : plan.pg, s,
                       reseed));
-  if (copy16(plan)) HIP_TRY(prep_bf16(b.c64, b.k, b.d, plan.ks * 16, b.st, b.cb16, b.cnB, s));
-  HIP_TRY(zero_i64(b.slots, (int64_t)kSlots * b.k * (b.d + 1), s));
+  HIP_TRY(prep_copy(b, plan, s));
+  HIP_TRY(zero_sums(b, plan, s));
   HIP_TRY(zero_i64(b.jslots, (int64_t)kSlots * 2, s));
   // Passes go out in chunks (2, 4, 8, then 16), each followed by a copy of the
   // pass state.  One more chunk is queued before the host waits for a chunk's
@@ -674,7 +676,7 @@ static km_status one_pass(const void* X, km_dtype dtype, int64_t n, int32_t d, c
                o_sh = c.take<double>(k), o_em = c.take<int32_t>(k),
                o_st = c.take<PassState>(1), o_slots = c.take<long long>((size_t)kSlots * C_),
                o_qs = c.take<long long>((size_t)kSlots * 2),
-               o_cb = c.take<uint16_t>(copy16(p) ? (size_t)bf16_rows(k) * 16 * p.ks : 0),
+               o_cb = c.take<uint16_t>(own_copy16(p) ? (size_t)bf16_rows(k) * 16 * p.ks : 0),
                o_cnb = c.take<float>((size_t)bf16_rows(k)), o_q = c.take<uint32_t>(p.bf16 ? (size_t)n : 0),
                o_qt = c.take<float>(p.bf16 ? (size_t)n : 0),
                o_rqc = c.take<int4>(p.bf16 ? (size_t)n : 0),
@@ -723,8 +725,8 @@ static km_status one_pass(const void* X, km_dtype dtype, int64_t n, int32_t d, c
   HIP_TRY(stage_reset(b.st, s));
   HIP_TRY(row_stats(X, b.dtype, n, d, wants_norms(p), b.st, s));
   HIP_TRY(stage_begin(b.st, 1, 0.0, n, b.cnorm, k, d, p.fused ? 0 : p.pg, s));
-  if (copy16(p)) HIP_TRY(prep_bf16(b.c64, k, d, p.ks * 16, b.st, b.cb16, b.cnB, s));
-  HIP_TRY(zero_i64(b.slots, (int64_t)kSlots * k * (d + 1), s));
+  HIP_TRY(prep_copy(b, p, s));
+  HIP_TRY(zero_sums(b, p, s));
   HIP_TRY(zero_i64(b.jslots, (int64_t)kSlots * 2, s));
   HIP_TRY(hipMemcpyAsync(&hs, b.st, sizeof hs, hipMemcpyDeviceToHost, s));
   HIP_TRY(hipStreamSynchronize(s));

@@ -563,9 +563,11 @@ __global__ __launch_bounds__(256) void k_stage_begin(PassState* __restrict__ st,
     // below 2^80 units and all rows' parts below 2^96.
     int FJ = 0;
     if (pg > 0 && !st->nonfinite) {
-      const float r = 2.0f * fmaxf(sqrtf(xm), cm) * (1.0f + 0x1p-20f);
-      const float bound = fmaxf(r * r, 0x1p-100f);
-      FJ = min(80, 96 - ceil_log2(rows)) - ilogbf(bound) - 1;
+      // (rows whose FP32 sum of squares overflows: d max|x|^2 bounds it)
+      const double xa = (double)__uint_as_float(bits);
+      const double rx = isinf(xm) ? sqrt((double)d_) * xa : sqrt((double)xm);
+      const double r = 2.0 * fmax(rx, red[0]) * (1.0 + 0x1p-19);
+      FJ = min(80, 96 - ceil_log2(rows)) - ilogb(fmax(r * r, 0x1p-500)) - 1;
       FJ = min(600, max(-600, FJ));
     }
     st->FJ = FJ;
@@ -1216,7 +1218,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k
     const uint32_t* __restrict__ perm, const long long* __restrict__ start,
     const double* __restrict__ c64, const PassState* __restrict__ st,
     const int32_t* __restrict__ gate, long long* __restrict__ slots,
-    long long* __restrict__ jslots) {
+    long long* __restrict__ jslots, int nslots) {
   if (gated(gate)) return;
   const int G = 1 << glog;
   const int lane = threadIdx.x & 63, gi = lane >> glog, gl = lane & (G - 1);
@@ -1242,7 +1244,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k
   for (int e = 0; e < E; ++e) acc[e] = 0.0;
   double j0 = 0.0, j1 = 0.0;  // J limbs: units of 2^-FJ and of 2^(40-FJ)
   long long cnt = 0;
-  const int slot = (int)(group & (kSlots - 1));
+  const int slot = (int)(group & (nslots - 1));
   long long* srow = slots + (int64_t)slot * k * (d + 1);
   auto flush = [&]() {
     if (cnt == 0) return;
@@ -3210,6 +3212,541 @@ __global__ __launch_bounds__(512) void k_rescreen_bf16(
 }
 
 // ============================================================================
+// Split BF16 screen for rows of any dims: FP32 rows with d > 16, and BF16 rows
+// that the BF16 screen does not take
+// ============================================================================
+// FP32 value as the sum of three BF16 values (exact: 24 bits in three pieces of 8).
+__device__ __forceinline__ void bf16_parts(float v, uint16_t& a, uint16_t& b, uint16_t& c) {
+  a = f32_to_bf16(v);
+  const float r = v - __uint_as_float((uint32_t)a << 16);
+  b = f32_to_bf16(r);
+  c = f32_to_bf16(r - __uint_as_float((uint32_t)b << 16));
+}
+
+// Labels of points a screen leaves open are negative: all ones when any center
+// may be the nearest, otherwise the sign bit and up to four candidate centers
+// of bg bits each (the first one repeated in the fields that are not used).
+__device__ __forceinline__ int open_fields(int bg) { return min(4, 31 / bg); }
+
+// Dims [t0, t0 + 8) of a row, zero from d on.  whole: all eight lie below d
+// (wave-uniform).  FP32 rows load as dwords; BF16 rows as 16-byte pieces when
+// vec says they are aligned.
+constexpr int kSplitTiles = 2;   // 32-center tiles of a center group
+constexpr int kSplitSteps = 4;   // 16-dim steps of a chunk, at most
+typedef float f32x4a4 __attribute__((ext_vector_type(4), aligned(4)));
+template <typename T>
+__device__ __forceinline__ void load8_split(const T* __restrict__ row, int t0, int d, bool whole,
+                                            bool vec, float (&v)[8]) {
+  if constexpr (sizeof(T) == 4) {
+    if (whole) {
+      const f32x4a4 a = *reinterpret_cast<const f32x4a4*>(row + t0);
+      const f32x4a4 b = *reinterpret_cast<const f32x4a4*>(row + t0 + 4);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        v[e] = a[e];
+        v[4 + e] = b[e];
+      }
+      return;
+    }
+  } else if (whole && vec) {
+    const uint4 w = *reinterpret_cast<const uint4*>(row + t0);
+    const uint32_t w4[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      v[2 * u] = bf16_lo(w4[u]);
+      v[2 * u + 1] = bf16_hi(w4[u]);
+    }
+    return;
+  }
+#pragma unroll
+  for (int e = 0; e < 8; ++e) v[e] = t0 + e < d ? widen<T>(row[t0 + e]) : 0.f;
+}
+
+// The split screen of all points: scores from 32x32x16 BF16 MFMAs over three
+// products per dim, c'lo x^ + c'hi xlo + c'hi x^ (c' = -2c = c'hi + c'lo + e,
+// x = x^ + xlo + r, BF16 parts; BF16 rows: x^ = x, two products), as in the
+// fused pass of small d, for any d and k.  A block of four waves takes 256
+// points, two 32-point tiles a wave.  Centers pass through LDS in groups of 32 CT
+// and chunks of 16 KC dims (both parts), double-buffered by LDS-direct loads, one
+// barrier a chunk; two chunks in all, or one, stay in LDS for the block's life.  A
+// wave's rows of a chunk are loaded straight into operand layout and split in
+// registers (kept over the groups when d <= 64).
+// One more MFMA per tile adds ||c||^2 and an offset of the point, ||x||^2 and a
+// margin, as three BF16 parts each against ones: a score is then
+// ||x - c||^2 + margin >= 0, so the index bits of a key cost little, and the
+// large terms join after the products (inside a chunk the small products come
+// first), which keeps the rounding of the FP32 accumulation, the band's largest
+// term, near that of a plain FP32 sum.
+// Each lane ranks its 16 CT scores a group as in the fused pass (best three
+// keys of its half of the centers); a point then knows its best three of both
+// halves.  Certain: the second best is out of the band of the best.  Otherwise,
+// with both halves' thirds out of the band, the (up to four) keys inside it are
+// the candidates; else any center may be.  The label then says so
+// (open_fields), and k_resolve decides.
+// Why 256 points x 32 CT centers: 2 x CT accumulator tiles per wave reuse every
+// center operand for two point tiles, and two such blocks fit a CU (64 KB of
+// LDS, 256 VGPRs a wave), one wave's key updates beside another's MFMAs.
+template <typename T, int KC>
+__global__ __launch_bounds__(256, 2) void k_screen_split(
+    const T* __restrict__ X, int64_t n, int d, int k, int nq, int bg,
+    const uint16_t* __restrict__ cb16, const uint16_t* __restrict__ cb16lo,
+    const float* __restrict__ cnB, const PassState* __restrict__ st,
+    const int32_t* __restrict__ gate, int32_t* __restrict__ labels, double* __restrict__ Jpart,
+    long long* __restrict__ upart) {
+  if (gated(gate)) return;
+  constexpr int CT = kSplitTiles;
+  constexpr int PB = KC * 512;               // elements of one part of a tile's chunk
+  // two buffers as separate objects, each read by its own code path, so that
+  // reads of one do not wait for the LDS-direct loads into the other
+  __shared__ __align__(16) uint16_t buf0[2 * CT * PB], buf1[2 * CT * PB];
+  const int lane = threadIdx.x & 63, h = lane >> 5, pc = lane & 31;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int ng = (k + 32 * CT - 1) / (32 * CT), ns = ng * nq, ksl = nq * KC;
+  const int GM = (1 << bg) - 1;
+  const int keep = opaque_vgpr(~GM);
+  const bool vec = (d & 7) == 0 && (reinterpret_cast<uintptr_t>(X) & 15u) == 0;
+  const float delta = (float)(1 << bg) * 0x1p-23f * 1.01f;
+  // additions at the magnitude of the products: those of the c'hi x^ products,
+  // of the small products of every chunk but the first, and the small ones of
+  // the first chunk among themselves (at 2^-6 of it, counted as a sixteenth)
+  const float nadd = (float)(16 * ksl + 32 * (ksl - KC) + ksl + 8);
+  // chunk q of group g into a buffer: a wave copies the parts (tile, hi / lo)
+  // wave, wave + 4, ..., each 1 KB per 16-dim step and contiguous
+  auto issue = [&](int g, int q, uint16_t* buf) {
+    static_assert(2 * CT == 4, "one part per wave");
+    const uint16_t* src = (wave & 1 ? cb16lo : cb16) +
+                          ((int64_t)(g * CT + (wave >> 1)) * ksl + KC * q) * 512 + lane * 8;
+#pragma unroll
+    for (int s = 0; s < KC; ++s)
+      __builtin_amdgcn_global_load_lds(static_cast<const void*>(src + s * 512),
+                                       static_cast<void*>(buf + wave * PB + s * 512), 16, 0, 0);
+  };
+  int64_t nfull = 0, ncand = 0;
+  int par = 0;         // buffer of the next chunk
+  int loaded = 1;      // chunks issued so far, when all of them stay in LDS
+  const bool fixed = ns <= 2;
+  const int64_t first = (int64_t)blockIdx.x * 256;
+  if (first < n) issue(0, 0, buf0);
+  for (int64_t base = first; base < n; base += (int64_t)gridDim.x * 256) {
+    const bool last_base = base + (int64_t)gridDim.x * 256 >= n;
+    v8bf xh[2][KC], xl[2][KC];
+    float s2[2] = {0.f, 0.f}, r2[2] = {0.f, 0.f};
+    v8bf xa[2];          // the point's offset as the B operand of the last MFMA
+    float E2v[2];
+    int m1[2], m2[2], m3[2];
+#pragma unroll
+    for (int p = 0; p < 2; ++p) m1[p] = m2[p] = m3[p] = INT_MAX;
+    v16f acc[2][CT];
+    // rows of chunk q, split; the norms on the way in the first group
+    auto load_chunk = [&](int q, bool norms) {
+#pragma unroll
+      for (int s = 0; s < KC; ++s) {
+        // two steps' loads in flight (more would not leave the accumulators
+        // their registers)
+        if (s % 2 == 0) __builtin_amdgcn_sched_barrier(0);
+        const int t0 = 16 * (KC * q + s) + 8 * h;
+        const bool whole = 16 * (KC * q + s) + 16 <= d;
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+          const T* row = X + min(base + wave * 64 + p * 32 + pc, n - 1) * d;
+          float v[8];
+          load8_split<T>(row, t0, d, whole, vec, v);
+          typedef float f32x2 __attribute__((ext_vector_type(2)));
+          typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+          uint32_t hw[4], lw[4];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            const f32x2 pr = {v[2 * u], v[2 * u + 1]};
+            hw[u] = __builtin_bit_cast(uint32_t, __builtin_convertvector(pr, bf16x2));
+            if constexpr (sizeof(T) == 4) {
+              const f32x2 rr = {v[2 * u] - bf16_lo(hw[u]), v[2 * u + 1] - bf16_hi(hw[u])};
+              lw[u] = __builtin_bit_cast(uint32_t, __builtin_convertvector(rr, bf16x2));
+              if (norms) {
+                r2[p] = __builtin_fmaf(rr.x, rr.x, r2[p]);
+                r2[p] = __builtin_fmaf(rr.y, rr.y, r2[p]);
+              }
+            }
+            if (norms) {
+              s2[p] = __builtin_fmaf(v[2 * u], v[2 * u], s2[p]);
+              s2[p] = __builtin_fmaf(v[2 * u + 1], v[2 * u + 1], s2[p]);
+            }
+          }
+          xh[p][s] = __builtin_bit_cast(v8bf, hw);
+          if constexpr (sizeof(T) == 4) xl[p][s] = __builtin_bit_cast(v8bf, lw);
+        }
+      }
+    };
+    // The point's offset and band once its norms are known.  Two scores differ
+    // from their exact values by at most E2 = 2 e1 together: the dropped part
+    // x^.e + xlo.(c' - c'hi) + r.c' (||e|| <= dcn, ||c' - c'hi|| <= 2^-8 ||c||,
+    // ||r|| <= 2^-9 ||x - x^|| and ||xlo|| <= (1 + 2^-8) ||x - x^||), the
+    // rounding of the FP32 sums (any rounding of every addition: nadd at the
+    // products' magnitude, 16 with the norms joining, the last MFMA), and that
+    // of ||c||^2 from cnB = ||c||^2 + B.  An error of the offset is common to
+    // all scores of the point.
+    auto point_norms = [&]() {
+      const float B = st->B, cmax = st->cmax, dcn = st->dcn * 1.01f;
+#pragma unroll
+      for (int p = 0; p < 2; ++p) {
+        const float xn2 = sum_halves(s2[p], h);
+        const float xn = __builtin_amdgcn_sqrtf(xn2) * 1.01f;
+        const float xr =
+            sizeof(T) == 4 ? __builtin_amdgcn_sqrtf(sum_halves(r2[p], h)) * 1.01f : 0.f;
+        const float xc = xn * cmax, nn = 1.1f * (cmax * cmax + xn2);
+        const float e1 = 0x1.03p-23f * (nadd * 2.05f * xc + 18.f * (nn + 2.05f * xc)) +
+                         xn * dcn + 2.1f * 0x1p-8f * xr * cmax +
+                         3.f * 0x1p-23f * (B + cmax * cmax) + 1e-30f;
+        const float off = xn2 + 1.02f * e1 + (float)(16 * ksl + 16) * 0x1.03p-23f * xn2;
+        E2v[p] = 2.01f * e1;
+        uint16_t a, b, c;
+        bf16_parts(off, a, b, c);
+        u16x8 v = {0, 0, 0, 0, 0, 0, 0, 0};
+        if (h) v = (u16x8){0x3f80, 0x3f80, 0x3f80, a, b, c, 0, 0};
+        xa[p] = __builtin_bit_cast(v8bf, v);
+      }
+    };
+    auto products = [&](const uint16_t* buf) {
+      auto op = [&](int t, int part, int s) -> v8bf {
+        return *reinterpret_cast<const v8bf*>(
+            &buf[(2 * t + part) * PB + ((2 * s + h) * 32 + pc) * 8]);
+      };
+#pragma unroll
+      for (int s = 0; s < KC; ++s) {
+#pragma unroll
+        for (int t = 0; t < CT; ++t) {
+          const v8bf lo = op(t, 1, s);
+#pragma unroll
+          for (int p = 0; p < 2; ++p)
+            acc[p][t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lo, xh[p][s], acc[p][t], 0, 0, 0);
+        }
+        if constexpr (sizeof(T) == 4) {
+#pragma unroll
+          for (int t = 0; t < CT; ++t) {
+            const v8bf hi = op(t, 0, s);
+#pragma unroll
+            for (int p = 0; p < 2; ++p)
+              acc[p][t] =
+                  __builtin_amdgcn_mfma_f32_32x32x16_bf16(hi, xl[p][s], acc[p][t], 0, 0, 0);
+          }
+        }
+      }
+#pragma unroll
+      for (int s = 0; s < KC; ++s)
+#pragma unroll
+        for (int t = 0; t < CT; ++t) {
+          const v8bf hi = op(t, 0, s);
+#pragma unroll
+          for (int p = 0; p < 2; ++p)
+            acc[p][t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(hi, xh[p][s], acc[p][t], 0, 0, 0);
+        }
+    };
+    if (fixed) par = 0;  // chunk 0 is in buf0, chunk 1 in buf1
+    for (int g = 0; g < ng; ++g) {
+      float cb[CT];
+#pragma unroll
+      for (int t = 0; t < CT; ++t) cb[t] = cnB[(g * CT + t) * 32 + pc];
+#pragma unroll
+      for (int p = 0; p < 2; ++p)
+#pragma unroll
+        for (int t = 0; t < CT; ++t)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) acc[p][t][r] = 0.f;
+      for (int q = 0; q < nq; ++q) {
+        if (nq > 1 || g == 0) load_chunk(q, g == 0);
+        // the chunk's centers are in LDS after the barrier, which also frees
+        // the other buffer for the next chunk
+        if (!fixed || base == first) {
+          __builtin_amdgcn_s_waitcnt(0);
+          __syncthreads();
+        }
+        const bool wrap = q == nq - 1, end = wrap && g == ng - 1;
+        if (fixed ? loaded < ns : !(end && last_base)) {
+          issue(end ? 0 : g + (wrap ? 1 : 0), wrap ? 0 : q + 1, par ? buf0 : buf1);
+          ++loaded;
+        }
+        if (par) products(buf1);
+        else products(buf0);
+        par ^= 1;
+      }
+      if (g == 0) point_norms();
+      // the norms' MFMA, then the keys of the group's scores
+      {
+        const float B = st->B;
+#pragma unroll
+        for (int t = 0; t < CT; ++t) {
+          uint16_t a, b, c;
+          bf16_parts(fminf(cb[t] - B, 1e30f), a, b, c);  // padding rows: 1e30
+          u16x8 v = {0, 0, 0, 0, 0, 0, 0, 0};
+          if (h) v = (u16x8){a, b, c, 0x3f80, 0x3f80, 0x3f80, 0, 0};
+          const v8bf ca = __builtin_bit_cast(v8bf, v);
+#pragma unroll
+          for (int p = 0; p < 2; ++p)
+            acc[p][t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ca, xa[p], acc[p][t], 0, 0, 0);
+        }
+      }
+#pragma unroll
+      for (int t = 0; t < CT; ++t)
+#pragma unroll
+        for (int p = 0; p < 2; ++p)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            // the lane half's 4h joins after the last group
+            const int j = (g * CT + t) * 32 + 8 * (r >> 2) + (r & 3);
+            const int kv = (__float_as_int(acc[p][t][r]) & keep) | j;
+            m3[p] = med3_i32(m2[p], kv, m3[p]);
+            m2[p] = med3_i32(m1[p], kv, m2[p]);
+            m1[p] = min(m1[p], kv);
+          }
+    }
+    // lane l takes point l of the wave's 64: both halves' keys and its own band
+    int a[3], b[3];
+    {
+      const int k4 = h << 2;
+      const auto w1 = __builtin_amdgcn_permlane32_swap(m1[0] | k4, m1[1] | k4, false, false);
+      const auto w2 = __builtin_amdgcn_permlane32_swap(m2[0] | k4, m2[1] | k4, false, false);
+      const auto w3 = __builtin_amdgcn_permlane32_swap(m3[0] | k4, m3[1] | k4, false, false);
+      a[0] = (int)w1[0]; a[1] = (int)w2[0]; a[2] = (int)w3[0];
+      b[0] = (int)w1[1]; b[1] = (int)w2[1]; b[2] = (int)w3[1];
+    }
+    const float E2 = h ? E2v[1] : E2v[0];
+    const int64_t i = base + wave * 64 + lane;
+    const bool valid = i < n;
+    auto val = [&](int key) { return __int_as_float(key & ~GM); };
+    const int best = min(a[0], b[0]);
+    const float v1 = val(best);
+    auto apart = [&](int key) {
+      const float v = val(key);
+      return (v - v1) > E2 + delta * (fabsf(v) + fabsf(v1));
+    };
+    const int bj = best & GM;
+    const int second = min(max(a[0], b[0]), min(a[1], b[1]));
+    const bool certain = bj < k && (k == 1 || apart(second));
+    int label = bj;
+    if (!certain) {
+      label = -1;
+      const bool closed = bj < k && apart(a[2]) && apart(b[2]);
+      const int nf = open_fields(bg);
+      int code = 0, nc = 0;
+      const int c4[4] = {a[0], a[1], b[0], b[1]};
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int j = c4[u] & GM;
+        if (!apart(c4[u]) && j < k) {
+          if (nc < nf) code |= j << (bg * nc);
+          ++nc;
+        }
+      }
+      for (int u = nc; u < nf; ++u) code |= (code & GM) << (bg * u);
+      if (closed && nc >= 1 && nc <= nf) label = (int)(0x80000000u | (uint32_t)code);
+      if (label == -1) nfull += valid ? 1 : 0;
+      else ncand += valid ? 1 : 0;
+    }
+    if (valid) labels[i] = label;
+  }
+  // block_sum_J takes counts that are uniform over a wave
+  block_sum_J(0.0, wave_sum_i64(nfull), wave_sum_i64(ncand), Jpart, upart);
+}
+
+// Decides the points that k_screen_split left open: the nearest of a point's
+// candidates (or of all centers), lowest index among equal distances, by the
+// direct form: FP32 first, with its error bound, FP64 when the best two are
+// closer than that.  A block takes ranges of rb points and lists the open ones
+// in LDS; groups of 16 lanes take one point each, four center rows in flight.  A
+// point without candidates is worked on by all 16 groups of the block, each
+// over its share of the centers (one group alone walks k / 4 dependent loads:
+// 2,400 such points of 1e6 x 64, k = 256 took 0.7 ms).
+template <typename T>
+__global__ __launch_bounds__(256) void k_resolve(
+    const T* __restrict__ X, int64_t n, int d, int k, int bg, int rb,
+    const float* __restrict__ cw, const double* __restrict__ c64,
+    const PassState* __restrict__ st, const int32_t* __restrict__ gate,
+    int32_t* __restrict__ labels) {
+  if (gated(gate)) return;
+  __shared__ uint16_t list[4096];  // points with candidates from the front, others from the back
+  __shared__ int cnt, fcnt;
+  __shared__ float gbest[16], gsec[16];
+  __shared__ double gD[16];
+  __shared__ int gj[16];
+  const int li = threadIdx.x & 15, grp = threadIdx.x >> 4;
+  const bool vec = (d & 7) == 0 && (reinterpret_cast<uintptr_t>(X) & 15u) == 0;
+  const bool cvec = (d & 3) == 0;
+  const int GM = (1 << bg) - 1, nf = open_fields(bg);
+  // FP32 direct form over a lane's 8 ceil(d / 128) terms and four pairwise adds,
+  // plus 2 sqrt(D) ||c - cw|| for the rounded center
+  const float u32 = 0x1p-24f * 1.01f, cmax = st->cmax;
+  const float rel = (float)(8 * ((d + 127) / 128) + 6) * u32;
+  auto err = [&](float D) { return rel * D + 2.f * sqrtf(D) * u32 * cmax + 1e-30f; };
+  auto close = [&](float b, float s) { return !((s - b) > err(b) + err(s)); };
+  // FP32 distances of four centers (those not negative), summed over the group,
+  // into the running best two
+  auto rank4 = [&](const T* xr, const int (&cj)[4], float& best, float& sec, int& bj) {
+    float part[4] = {0.f, 0.f, 0.f, 0.f};
+    for (int t0 = 8 * li; t0 < d; t0 += 128) {
+      const bool in8 = t0 + 8 <= d;
+      float xv[8];
+      load8_split<T>(xr, t0, d, in8, vec, xv);
+      float cv[4][8];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const float* cr = cw + (int64_t)(cj[u] >= 0 ? cj[u] : 0) * d + t0;
+        if (cvec && in8) {
+          const float4 a = *reinterpret_cast<const float4*>(cr);
+          const float4 b = *reinterpret_cast<const float4*>(cr + 4);
+          cv[u][0] = a.x; cv[u][1] = a.y; cv[u][2] = a.z; cv[u][3] = a.w;
+          cv[u][4] = b.x; cv[u][5] = b.y; cv[u][6] = b.z; cv[u][7] = b.w;
+        } else {
+#pragma unroll
+          for (int e = 0; e < 8; ++e) cv[u][e] = t0 + e < d ? cr[e] : 0.f;
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const float diff = xv[e] - cv[u][e];
+          part[u] = __builtin_fmaf(diff, diff, part[u]);
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      float v = part[u];
+      v += __shfl_xor(v, 8);
+      v += __shfl_xor(v, 4);
+      v += __shfl_xor(v, 2);
+      v += __shfl_xor(v, 1);
+      const int j = cj[u];
+      if (j < 0 || j == bj) continue;
+      if (v < best || (v == best && j < bj)) {
+        sec = best;
+        best = v;
+        bj = j;
+      } else if (v < sec) {
+        sec = v;
+      }
+    }
+  };
+  // FP64 distance of center j, summed over the group, into the running best
+  auto rank64 = [&](const T* xr, int j, double& bD, int& b64) {
+    double p = 0.0;
+    for (int t0 = 8 * li; t0 < d; t0 += 128) {
+      float xv[8];
+      load8_split<T>(xr, t0, d, t0 + 8 <= d, vec, xv);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const double cv = c64[(int64_t)j * d + (t0 + e < d ? t0 + e : 0)];
+        const double diff = t0 + e < d ? (double)xv[e] - cv : 0.0;
+        p = __builtin_fma(diff, diff, p);
+      }
+    }
+    p += __shfl_xor(p, 8);
+    p += __shfl_xor(p, 4);
+    p += __shfl_xor(p, 2);
+    p += __shfl_xor(p, 1);
+    if (p < bD || (p == bD && j < b64)) {
+      bD = p;
+      b64 = j;
+    }
+  };
+  for (int64_t r0 = (int64_t)blockIdx.x * rb; r0 < n; r0 += (int64_t)gridDim.x * rb) {
+    if (threadIdx.x == 0) cnt = fcnt = 0;
+    __syncthreads();
+    const int rn = (int)min<int64_t>(rb, n - r0);
+#pragma unroll 1
+    for (int u0 = 0; u0 < rn; u0 += 1024) {
+      int lv[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int o = u0 + u * 256 + (int)threadIdx.x;
+        lv[u] = o < rn ? labels[r0 + o] : 0;
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const uint16_t o = (uint16_t)(u0 + u * 256 + threadIdx.x);
+        if (lv[u] == -1) list[4095 - atomicAdd(&fcnt, 1)] = o;
+        else if (lv[u] < 0) list[atomicAdd(&cnt, 1)] = o;
+      }
+    }
+    __syncthreads();
+    const int m = cnt, mf = fcnt;
+    for (int q = grp; q < m; q += 16) {
+      const int64_t pt = r0 + list[q];
+      const int code = labels[pt];
+      const T* xr = X + pt * d;
+      int cj[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int j = u < nf ? (code >> (bg * u)) & GM : -1;
+        cj[u] = j < k ? j : -1;
+      }
+      float best = INFINITY, sec = INFINITY;
+      int bj = INT_MAX;
+      rank4(xr, cj, best, sec, bj);
+      if (close(best, sec)) {
+        double bD = INFINITY;
+        bj = INT_MAX;
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          if (cj[u] >= 0 && cj[u] != bj) rank64(xr, cj[u], bD, bj);
+      }
+      if (li == 0) labels[pt] = bj < k ? bj : 0;
+    }
+    for (int q = 0; q < mf; ++q) {
+      const int64_t pt = r0 + list[4095 - q];
+      const T* xr = X + pt * d;
+      float best = INFINITY, sec = INFINITY;
+      int bj = INT_MAX;
+      for (int u0 = 4 * grp; u0 < k; u0 += 64) {
+        int cj[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) cj[u] = u0 + u < k ? u0 + u : -1;
+        rank4(xr, cj, best, sec, bj);
+      }
+      if (li == 0) {
+        gbest[grp] = best;
+        gsec[grp] = sec;
+        gj[grp] = bj;
+      }
+      __syncthreads();
+      best = sec = INFINITY;
+      bj = INT_MAX;
+#pragma unroll
+      for (int g = 0; g < 16; ++g) {
+        const float v = gbest[g];
+        if (v < best || (v == best && gj[g] < bj)) {
+          sec = fminf(best, gsec[g]);
+          best = v;
+          bj = gj[g];
+        } else {
+          sec = fminf(sec, v);
+        }
+      }
+      if (bj == INT_MAX || close(best, sec)) {  // the same in every thread
+        double bD = INFINITY;
+        int b64 = INT_MAX;
+        for (int u = grp; u < k; u += 16) rank64(xr, u, bD, b64);
+        __syncthreads();
+        if (li == 0) {
+          gD[grp] = bD;
+          gj[grp] = b64;
+        }
+        __syncthreads();
+        bD = INFINITY;
+        bj = INT_MAX;
+#pragma unroll
+        for (int g = 0; g < 16; ++g)
+          if (gD[g] < bD || (gD[g] == bD && gj[g] < bj)) {
+            bD = gD[g];
+            bj = gj[g];
+          }
+      }
+      if (threadIdx.x == 0) labels[pt] = bj < k ? bj : 0;
+      __syncthreads();  // the groups' results are read before the next point's
+    }
+    __syncthreads();  // the lists are rebuilt for the next range
+  }
+}
+
+// ============================================================================
 // New centers from the slot sums, stage bookkeeping
 // ============================================================================
 // Fixed-order sums of J (the assignment blocks' partials, or the sorted
@@ -3499,11 +4036,12 @@ __global__ __launch_bounds__(256) void k_finalize(
     uint16_t* __restrict__ cb16, float* __restrict__ cnB, int kd16,
     const double* __restrict__ Jpart, const long long* __restrict__ upart, int64_t nb,
     double* __restrict__ J_hist, double* __restrict__ shift_hist, int biased,
-    double* __restrict__ trace_c, long long* __restrict__ trace_n) {
+    double* __restrict__ trace_c, long long* __restrict__ trace_n,
+    uint16_t* __restrict__ cb16lo, int nslots) {
   if (gated(gate)) return;
   finalize_center(blockIdx.x, slots, jslots, k, d, st, update, c64, cw, cn, cnorm, shiftj, emptyj,
                   S_out, N_out, cb16, cnB, kd16, Jpart, upart, nb, J_hist, shift_hist, false,
-                  biased != 0, trace_c, trace_n);
+                  biased != 0, trace_c, trace_n, cb16lo, nslots);
 }
 
 // ----------------------------------------------------------------------------
@@ -3581,6 +4119,7 @@ __global__ __launch_bounds__(256) void k_reseed(const T* __restrict__ X, int d, 
                                                 float* __restrict__ cn,
                                                 double* __restrict__ cnorm,
                                                 uint16_t* __restrict__ cb16,
+                                                uint16_t* __restrict__ cb16lo,
                                                 float* __restrict__ cnB, int kd16,
                                                 PassState* __restrict__ st,
                                                 const double* __restrict__ fpart,
@@ -3630,7 +4169,13 @@ __global__ __launch_bounds__(256) void k_reseed(const T* __restrict__ X, int d, 
     nn += x * x;
     c64[(int64_t)j * d + t] = x;
     cw[(int64_t)j * d + t] = (float)x;
-    if (cb16) {
+    if (cb16lo) {
+      uint16_t hi, lo;
+      const double e = bf16_split(x, hi, lo);
+      cb16[cb16_at(j, t, kd16)] = hi;
+      cb16lo[cb16_at(j, t, kd16)] = lo;
+      ee += e * e;
+    } else if (cb16) {
       const uint16_t b = f32_to_bf16((float)(-2.0 * x));
       cb16[cb16_at(j, t, kd16)] = b;
       const double e = bf16_err(b, x);
@@ -4376,8 +4921,8 @@ __global__ __launch_bounds__(64) void k_prep_bf16(const double* __restrict__ c64
 }
 
 hipError_t prep_bf16(const double* c64, int32_t k, int32_t d, int kd16, PassState* st,
-                     uint16_t* cb16, float* cnB, hipStream_t s, uint16_t* cb16lo) {
-  hipLaunchKernelGGL(k_prep_bf16, dim3((unsigned)bf16_rows(k)), dim3(64), 0, s, c64, k, d, kd16,
+                     uint16_t* cb16, float* cnB, hipStream_t s, uint16_t* cb16lo, int64_t rows) {
+  hipLaunchKernelGGL(k_prep_bf16, dim3((unsigned)(rows ? rows : bf16_rows(k))), dim3(64), 0, s, c64, k, d, kd16,
                      st, cb16, cnB, cb16lo);
   return hipGetLastError();
 }
@@ -4541,11 +5086,46 @@ static void visit_rescreen(int ks, F&& f) {
   }
 }
 
+// Split screen for a plan's 16-dim steps per chunk (p.kd; p.nt chunks, p.ks steps
+// in all).
+template <typename T, typename F>
+static void visit_split(int kc, F&& f) {
+  switch (kc) {
+    case 1: f(k_screen_split<T, 1>); break;
+    case 2: f(k_screen_split<T, 2>); break;
+    case 3: f(k_screen_split<T, 3>); break;
+    default: f(k_screen_split<T, 4>); break;
+  }
+}
+// Rows of its center copy (whole groups) and the index bits of its keys.
+static int64_t split_rows(int32_t k) {
+  return ((int64_t)k + 32 * kSplitTiles - 1) / (32 * kSplitTiles) * (32 * kSplitTiles);
+}
+static int split_bits(int32_t k) {
+  int bg = 6;
+  while ((1 << bg) < split_rows(k)) ++bg;
+  return bg;
+}
+// The split screen needs no memory of its own: its plan adds the cluster sums
+// into half of the slot rows and keeps the center copy's two parts in the rest.
+static int plan_slots(const PassPlan& p) { return p.split ? kSlots / 2 : kSlots; }
+static uint16_t* copy_hi(const PassBufs& b, const PassPlan& p) {
+  if (p.split) return reinterpret_cast<uint16_t*>(b.slots + (int64_t)kSlots / 2 * b.k * (b.d + 1));
+  return copy16(p) ? b.cb16 : nullptr;
+}
+static uint16_t* copy_lo(const PassBufs& b, const PassPlan& p) {
+  return p.split ? copy_hi(b, p) + split_rows(b.k) * p.ks * 16 : nullptr;
+}
+static bool split_copy_fits(int32_t k, int32_t d, int ks) {
+  return split_rows(k) * ks * 16 * 4 <= (int64_t)kSlots / 2 * k * (d + 1) * 8;
+}
+
 template <typename T>
 static int64_t plan_blocks(const PassPlan& p, int cus) {
   int64_t r = 0;
   auto f = [&](auto kern) { r = resident_blocks(kern, p.lds_assign, cus); };
-  if (p.bf16)
+  if (p.split) visit_split<T>(p.kd, [&](auto kern) { r = resident_blocks(kern, 0, cus); });
+  else if (p.bf16)
     visit_screen<T>(
         p.ks, [&](auto kern) { r = resident_blocks(kern, 0, cus, screen_threads(p.ks)); },
         sizeof(T) == 2 && p.d == p.ks * 16);
@@ -4628,8 +5208,27 @@ PassPlan plan_pass(int64_t rows, int32_t d, int32_t k, int dtype, int precision,
   }
   if (!p.mfma && !p.fscreen) {
     p.fused = !p.bf16 && p.dmax != 0 && lds_fused <= budget;
+    // Auto precision where the sums do not fit in LDS: the split screen, when
+    // its copy fits beside the sums and the keys hold the center indices.  The
+    // dims in equal chunks of at most kSplitSteps steps.  One pass against the
+    // FP32 kernels, same call: 1e6 x 64, k = 256: 0.79 against 1.30 ms; 1e6 x
+    // 128, k = 1000: 3.1 against 16.6; 2e5 x 300, k = 40: 0.64 against 13.7;
+    // 1e4 x 64, k = 256: 0.24 against 0.34.  Where the sums do fit, the fused
+    // pass stays: 1e6 x 64, k = 32 takes 0.46 there and 0.56 ms here (the sums
+    // read the rows again).
+    const int steps = (d + 15) / 16, nq = (steps + kSplitSteps - 1) / kSplitSteps;
+    const int kc = (steps + nq - 1) / nq, ks = nq * kc;
+    p.split = precision == 0 && !p.bf16 && !p.fused && k >= 2 && k <= (1 << 14) && d > 16 &&
+              d <= (1 << 16) && rows <= (int64_t)UINT32_MAX && split_copy_fits(k, d, ks);
     const int64_t tile_pts = 256LL * p.ppt;
     if (!p.bf16) work = (rows + tile_pts - 1) / tile_pts;
+    if (p.split) {
+      p.ks = ks;
+      p.kd = kc;
+      p.nt = nq;
+      p.dmax = 0;
+      work = (rows + 255) / 256;
+    }
     if (p.fused) {
       p.lds_assign = lds_fused;
       p.ktile = k;
@@ -4670,6 +5269,9 @@ PassPlan plan_pass(int64_t rows, int32_t d, int32_t k, int dtype, int precision,
   // a persistent grid: no more blocks than stay resident at once
   const int64_t res = dtype == 0 ? plan_blocks<float>(p, cus) : plan_blocks<uint16_t>(p, cus);
   p.blocks = std::max<int64_t>(1, std::min<int64_t>({work, res, (int64_t)kMaxBlocks}));
+  if (p.split)
+    p.rr_blocks = dtype == 0 ? resident_blocks(k_resolve<float>, 0, cus)
+                             : resident_blocks(k_resolve<uint16_t>, 0, cus);
   if (p.bf16) {
     // the re-rank's blocks walk ranges of the points in a grid-stride loop:
     // all of them resident, so none waits for a second round of blocks
@@ -4763,7 +5365,8 @@ static void sorted_update(const PassBufs& b, const PassPlan& p, const int32_t* g
   auto go = [&](auto kern, auto* x) {
     hipLaunchKernelGGL(kern, grid, dim3(256), 0, s, x, b.n, b.d, b.k, glog, p.pg,
                        (const uint32_t*)b.perm, (const long long*)b.rstart,
-                       (const double*)b.c64, (const PassState*)b.st, gate, b.slots, b.jslots);
+                       (const double*)b.c64, (const PassState*)b.st, gate, b.slots, b.jslots,
+                       plan_slots(p));
   };
   if (b.dtype == 0) {
     if (E == 4) go(k_run_sums<float, 4>, (const float*)b.X);
@@ -4817,9 +5420,36 @@ static void dispatch_rescreen(const PassBufs& b, const PassPlan& p, const int32_
   });
 }
 
+// The split screen of all points, and the decision of those it leaves open.
+template <typename T>
+static void dispatch_split(const PassBufs& b, const PassPlan& p, const int32_t* gate,
+                           hipStream_t s) {
+  visit_split<T>(p.kd, [&](auto kern) {
+    hipLaunchKernelGGL(kern, dim3((unsigned)p.blocks), dim3(256), 0, s, (const T*)b.X, b.n, b.d,
+                       b.k, p.nt, split_bits(b.k), (const uint16_t*)copy_hi(b, p),
+                       (const uint16_t*)copy_lo(b, p), (const float*)b.cnB,
+                       (const PassState*)b.st, gate, b.labels, b.Jpart, b.upart);
+  });
+}
+
+template <typename T>
+static void dispatch_resolve(const PassBufs& b, const PassPlan& p, const int32_t* gate,
+                             hipStream_t s) {
+  // ranges of 256 to 4096 points, one per resident block while there are enough
+  const int64_t cap = std::max<int64_t>(1, p.rr_blocks);
+  const int64_t rb = std::min<int64_t>(4096, std::max<int64_t>(256, (b.n / cap + 255) / 256 * 256));
+  const unsigned g = (unsigned)std::max<int64_t>(1, std::min<int64_t>((b.n + rb - 1) / rb, cap));
+  hipLaunchKernelGGL(k_resolve<T>, dim3(g), dim3(256), 0, s, (const T*)b.X, b.n, b.d, b.k,
+                     split_bits(b.k), (int)rb, (const float*)b.cw, (const double*)b.c64,
+                     (const PassState*)b.st, gate, b.labels);
+}
+
 hipError_t pass_assign(const PassBufs& b, const PassPlan& p, bool update, hipStream_t s) {
   const int32_t* gate = update ? &b.st->done : nullptr;
-  if (p.bf16) {
+  if (p.split) {
+    if (b.dtype == 0) dispatch_split<float>(b, p, gate, s);
+    else dispatch_split<uint16_t>(b, p, gate, s);
+  } else if (p.bf16) {
     if (b.dtype == 0) dispatch_bf16<float>(b, p, gate, s);
     else dispatch_bf16<uint16_t>(b, p, gate, s);
   } else if (p.fused) {
@@ -4836,7 +5466,10 @@ hipError_t pass_assign(const PassBufs& b, const PassPlan& p, bool update, hipStr
 hipError_t pass_rest(const PassBufs& b, const PassPlan& p, bool update, hipStream_t s) {
   const int32_t* gate = update ? &b.st->done : nullptr;
   const int64_t nb = p.bf16 ? 2 * p.blocks : p.blocks;
-  if (p.bf16) {
+  if (p.split) {
+    if (b.dtype == 0) dispatch_resolve<float>(b, p, gate, s);
+    else dispatch_resolve<uint16_t>(b, p, gate, s);
+  } else if (p.bf16) {
     if (b.dtype == 0) {
       dispatch_rerank<float>(b, p, gate, s);
       dispatch_rescreen<float>(b, p, gate, s);
@@ -4846,17 +5479,18 @@ hipError_t pass_rest(const PassBufs& b, const PassPlan& p, bool update, hipStrea
     }
   }
   // The sorted update makes the sums of an update pass and, with the BF16
-  // screen, J of every pass; the FP32 kernels add J themselves in a labelling
-  // pass.
-  const bool sorted = !p.fused && (update || p.bf16);
+  // and split screens, J of every pass; the FP32 kernels add J themselves in a
+  // labelling pass.
+  const bool sorted = !p.fused && (update || p.bf16 || p.split);
   if (sorted) sorted_update(b, p, gate, s);
   if (update || sorted) {
     hipLaunchKernelGGL(k_finalize, dim3((unsigned)b.k), dim3(256), 0, s, b.slots,
                        sorted ? b.jslots : nullptr, b.k, b.d, b.st, gate, update ? 1 : 0, b.c64,
                        b.cw, b.cn, b.cnorm, b.shiftj, b.emptyj, b.S_out, b.N_out,
-                       copy16(p) ? b.cb16 : nullptr, copy16(p) ? b.cnB : nullptr, p.ks * 16,
+                       copy_hi(b, p), copy16(p) ? b.cnB : nullptr, p.ks * 16,
                        (const double*)b.Jpart, (const long long*)b.upart, nb, b.J_hist,
-                       b.shift_hist, (p.fscreen && p.fsplit) ? 1 : 0, b.trace_c, b.trace_n);
+                       b.shift_hist, (p.fscreen && p.fsplit) ? 1 : 0, b.trace_c, b.trace_n,
+                       copy_lo(b, p), plan_slots(p));
     if (update && b.fpart) {
       // re-seeding: both kernels return at once unless this pass left a cluster empty
       const unsigned g = (unsigned)std::max<int64_t>(1, std::min<int64_t>((b.n + 255) / 256,
@@ -4866,7 +5500,7 @@ hipError_t pass_rest(const PassBufs& b, const PassPlan& p, bool update, hipStrea
         hipLaunchKernelGGL(k_farthest<T>, dim3(g), dim3(256), 0, s, x, b.n, b.d, b.k,
                            (const double*)b.c64, (const PassState*)b.st, b.fpart, b.fidx);
         hipLaunchKernelGGL(k_reseed<T>, dim3(1), dim3(256), 0, s, x, b.d, b.k, b.c64, b.cw, b.cn,
-                           b.cnorm, copy16(p) ? b.cb16 : nullptr, copy16(p) ? b.cnB : nullptr,
+                           b.cnorm, copy_hi(b, p), copy_lo(b, p), copy16(p) ? b.cnB : nullptr,
                            p.ks * 16, b.st, (const double*)b.fpart, (const long long*)b.fidx,
                            (int)g, b.shift_hist);
       };
@@ -4955,6 +5589,16 @@ hipError_t fill_uniform(void* p, int kind, int64_t count, uint64_t seed, hipStre
   const unsigned g = (unsigned)std::max<int64_t>(1, std::min<int64_t>((count + 255) / 256, 4096));
   hipLaunchKernelGGL(k_fill_uniform, dim3(g), dim3(256), 0, s, p, count, seed, kind);
   return hipGetLastError();
+}
+
+hipError_t zero_sums(const PassBufs& b, const PassPlan& p, hipStream_t s) {
+  return zero_i64(b.slots, (int64_t)plan_slots(p) * b.k * (b.d + 1), s);
+}
+
+hipError_t prep_copy(const PassBufs& b, const PassPlan& p, hipStream_t s) {
+  if (!copy16(p)) return hipSuccess;
+  return prep_bf16(b.c64, b.k, b.d, p.ks * 16, b.st, copy_hi(b, p), b.cnB, s, copy_lo(b, p),
+                   p.split ? split_rows(b.k) : 0);
 }
 
 hipError_t lloyd_pass(const PassBufs& b, const PassPlan& p, bool update, hipStream_t s) {

@@ -136,9 +136,11 @@ hipError_t stage_reset(PassState* st, hipStream_t s);
 hipError_t row_stats(const void* X, int dtype, int64_t rows, int32_t d, bool norms,
                      PassState* st, hipStream_t s);
 hipError_t zero_i64(long long* p, int64_t count, hipStream_t s);
-// cb16lo: when given, -2c is kept as hi + lo (the rest rounded to BF16 again)
+// cb16lo: when given, -2c is kept as hi + lo (the rest rounded to BF16 again);
+// rows: padded rows of the copy (0: bf16_rows(k))
 hipError_t prep_bf16(const double* c64, int32_t k, int32_t d, int kd16, PassState* st,
-                     uint16_t* cb16, float* cnB, hipStream_t s, uint16_t* cb16lo = nullptr);
+                     uint16_t* cb16, float* cnB, hipStream_t s, uint16_t* cb16lo = nullptr,
+                     int64_t rows = 0);
 hipError_t prep_centers(const double* c64, int32_t k, int32_t d, float* cw, float* cn,
                         double* cnorm, hipStream_t s);
 hipError_t stage_begin(PassState* st, int32_t max_iter, double tol, int64_t rows,
@@ -179,9 +181,11 @@ struct PassPlan {
   bool bf16;         // split pass with the BF16 MFMA screen (x.c^T as 32x32x16 tiles)
   bool fscreen;      // fused pass on the BF16 MFMA screen (d <= 16, k <= 128)
   bool fsplit;       // ... with -2c and FP32 points as BF16 hi + lo parts (auto precision)
-  int ks;            // 16-dim K steps of the BF16 screen
+  bool split;        // the split screen for any d, then the sorted update
+  int ks;            // 16-dim K steps of the BF16 screen and of the split screen's copy
   bool mfma;         // fused pass on FP32 MFMA (x.c^T as 32x32x2 tiles)
-  int kd, nt;        // padded dims and 32-center tiles of the MFMA kernels
+  int kd, nt;        // padded dims and 32-center tiles of the MFMA kernels (split: 16-dim
+                     //   steps of a chunk of dims, and chunks)
   int d;             // dims of the rows (the fused screen has a kernel for d == kd)
   bool fused;
   int dmax;          // register tile of a row (0: generic)
@@ -196,7 +200,7 @@ struct PassPlan {
 };
 
 // The pass keeps a BF16 copy of the centers (prep_bf16, then the finalize).
-inline bool copy16(const PassPlan& p) { return p.bf16 || p.fscreen; }
+inline bool copy16(const PassPlan& p) { return p.bf16 || p.fscreen || p.split; }
 // The stage statistics include max ||x||^2 (split paths and the BF16 screens).
 inline bool wants_norms(const PassPlan& p) { return !p.fused || p.fscreen; }
 
@@ -230,6 +234,9 @@ hipError_t fill_uniform(void* p, int kind, int64_t count, uint64_t seed, hipStre
 
 PassPlan plan_pass(int64_t rows, int32_t d, int32_t k, int dtype, int precision,
                    size_t lds_limit, int cus);
+// Clears the slot rows the plan's passes add into, and writes its BF16 center copy.
+hipError_t zero_sums(const PassBufs& b, const PassPlan& p, hipStream_t s);
+hipError_t prep_copy(const PassBufs& b, const PassPlan& p, hipStream_t s);
 hipError_t lloyd_pass(const PassBufs& b, const PassPlan& p, bool update, hipStream_t s);
 // the assignment kernel of a pass (for the BF16 path, its screen of all points), and
 // everything after it (re-screen, update, reduction, stop test)

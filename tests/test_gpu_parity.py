@@ -537,3 +537,85 @@ def test_step_label_sort_ranges_per_chunk():
     assert_centers(out["C_new"].cpu().numpy(), C_exp, Xh, tol=1e-9, name="C_new")
     J_l = float(((X - C[lab]) ** 2).sum())
     assert abs(out["J"] - J_l) <= 1e-9 * J_l, (out["J"], J_l)
+
+
+# ------------------------------------------- split screen beyond the fused passes
+@pytest.mark.parametrize("d,k,dtype", [(33, 170, "f32"), (64, 127, "f32"), (64, 128, "f32"),
+                                       (64, 129, "f32"), (65, 100, "f32"), (97, 64, "f32"),
+                                       (128, 1025, "f32"), (129, 3, "f32"), (150, 65, "f32"),
+                                       (300, 64, "f32"), (785, 10, "f32"), (20, 300, "bf16"),
+                                       (300, 63, "bf16"), (513, 70, "bf16")])
+@pytest.mark.parametrize("n", [1, 255, 257, 3001])
+def test_split_screen_any_d(d, k, dtype, n):
+    """The split screen at the edges of its tiles: one point, one less and more
+    than a block's 256, center groups of 64 full and one over, one to several
+    chunks of dims with whole and ragged last steps."""
+    Xh = _mixture(max(n, k), d, min(k, 40), seed=d + k + n, dtype=dtype)
+    C = _centers_from(Xh, k, seed=k + 3, jitter=0.4)
+    Xh = np.ascontiguousarray(Xh[:n])
+    out = km.km_step(to_device(Xh), torch.from_numpy(C).cuda())
+    ref = oracle.step(Xh, C)
+    # (J: the sorted update's limbs, as on the BF16 path)
+    assert_step(out, Xh, C, ref, jtol=1e-9, name=f"split n={n} d={d} k={k} {dtype}")
+    lab2, J2, _ = km.km_assign(to_device(Xh), torch.from_numpy(C).cuda())
+    assert_step({"labels": lab2, "J": J2}, Xh, C, ref, jtol=1e-9, name="split assign")
+
+
+@pytest.mark.parametrize("copies", [2, 3, 5, 20])
+@pytest.mark.parametrize("d", [64, 300])
+def test_split_screen_crowded_centers(copies, d):
+    """Several centers within the band of one another: two to four candidates in
+    the label, or (too many, or three of one lane half) all centers."""
+    base = max(6, 130 // copies)
+    rng = np.random.default_rng(copies + d)
+    mu = rng.normal(0, 20.0, size=(base, d))
+    C = np.repeat(mu, copies, axis=0) + rng.normal(0, 0.003, size=(base * copies, d))
+    comp = rng.integers(0, base, size=5_000)
+    Xh = (mu[comp] + rng.normal(0, 1.0, size=(5_000, d))).astype(np.float32)
+    out = km.km_step(to_device(Xh), torch.from_numpy(C).cuda())
+    ref = oracle.step(Xh, C)
+    assert_step(out, Xh, C, ref, jtol=1e-9, name=f"split crowded x{copies} d={d}")
+
+
+@pytest.mark.parametrize("d", [64, 144])
+@pytest.mark.parametrize("m", [128, 190, 255])
+def test_split_screen_any_d_band_covers_low_part_rounding(m, d):
+    """As test_split_screen_band_covers_low_part_rounding, on the screen for any
+    d: the dropped remainders of two centers' copies put the farther ahead."""
+    u = 2.0 ** -15
+    t1, t2 = (m + 0.49) * u / 2, (m + 0.51) * u / 2
+    C = np.vstack([np.full((1, d), 1 + t1), np.full((1, d), 1 + t2), _far_centers(d, 120, m)])
+    Xh = np.ones((64, d), np.float32)
+    lab, J, _ = km.km_assign(to_device(Xh), torch.from_numpy(C).cuda())
+    assert (lab.cpu().numpy() == 0).all()
+
+
+@pytest.mark.parametrize("d", [64, 144])
+def test_split_screen_any_d_band_covers_fp32_low_part_rounding(d):
+    """As test_split_screen_band_covers_fp32_low_part_rounding, on the screen for
+    any d: the points' dropped remainders all favour the farther center."""
+    u = 2.0 ** -16
+    half = d // 2
+    mp, mm = np.full(half, 150), np.full(half, 150)
+    mm[: max(1, (31 * d) // 100)] += 1
+    x = np.empty(d, np.float64)
+    x[0::2] = 1 + (mp + 0.5 + 2.0 ** -6) * u
+    x[1::2] = -(1 + (mm + 0.5 - 2.0 ** -6) * u)
+    xs = x.astype(np.float32)
+    assert np.array_equal(xs.astype(np.float64), x) and x.sum() < 0
+    C = np.vstack([np.full((1, d), 0.5), np.full((1, d), -0.5), _far_centers(d, 120, 3)])
+    lab, _, _ = km.km_assign(to_device(np.tile(xs, (64, 1))), torch.from_numpy(C).cuda())
+    assert (lab.cpu().numpy() == 1).all()
+
+
+@pytest.mark.parametrize("scale", [1e19, 1e-22])
+def test_split_screen_any_d_extreme_magnitudes(scale):
+    """Rows whose FP32 squared norms overflow or vanish: no score can certify a
+    label, FP64 decides, and J keeps its precision."""
+    d, k = 300, 12
+    Xh = (_mixture(2_001, d, k, seed=5, spread=3.0) * scale).astype(np.float32)
+    C = _centers_from(Xh, k, seed=6, jitter=0.1 * scale)
+    lab, J, _ = km.km_assign(to_device(Xh), torch.from_numpy(C).cuda())
+    rlab, D1, _ = oracle.assign(Xh, C)
+    assert np.array_equal(lab.cpu().numpy(), rlab)
+    assert abs(J - D1.sum()) <= 1e-9 * D1.sum()
