@@ -3223,9 +3223,8 @@ __device__ __forceinline__ void bf16_parts(float v, uint16_t& a, uint16_t& b, ui
   c = f32_to_bf16(r - __uint_as_float((uint32_t)b << 16));
 }
 
-// Labels of points a screen leaves open are negative: all ones when any center
-// may be the nearest, otherwise the sign bit and up to four candidate centers
-// of bg bits each (the first one repeated in the fields that are not used).
+// Labels of points a screen leaves open are negative: the sign bit and up to four
+// candidate centers of bg bits each (the first one repeated in unused fields).
 __device__ __forceinline__ int open_fields(int bg) { return min(4, 31 / bg); }
 
 // Dims [t0, t0 + 8) of a row, zero from d on.  whole: all eight lie below d
@@ -3262,6 +3261,158 @@ __device__ __forceinline__ void load8_split(const T* __restrict__ row, int t0, i
   for (int e = 0; e < 8; ++e) v[e] = t0 + e < d ? widen<T>(row[t0 + e]) : 0.f;
 }
 
+// Exact decisions of open points by groups of 16 lanes (8 dims a lane of each
+// 128): direct form in FP32 with its error bound, FP64 when the best two are
+// closer than that; lowest index among equal distances.
+template <typename T>
+struct Resolver {
+  const T* X;
+  int d, k;
+  bool vec, cvec;
+  const float* cw;
+  const double* c64;
+  float rel, u2c;
+  // FP32 direct form over a lane's 8 ceil(d / 128) terms and four pairwise adds,
+  // plus 2 sqrt(D) ||c - cw|| for the rounded center
+  __device__ __forceinline__ Resolver(const T* X_, int d_, int k_, bool vec_, const float* cw_,
+                                      const double* c64_, float cmax)
+      : X(X_), d(d_), k(k_), vec(vec_), cvec((d_ & 3) == 0), cw(cw_), c64(c64_),
+        rel((float)(8 * ((d_ + 127) / 128) + 6) * 0x1p-24f * 1.01f),
+        u2c(2.f * 0x1p-24f * 1.01f * cmax) {}
+  __device__ __forceinline__ float err(float D) const { return rel * D + sqrtf(D) * u2c + 1e-30f; }
+  __device__ __forceinline__ bool close(float b, float s) const {
+    return !((s - b) > err(b) + err(s));
+  }
+  // FP32 distances of four centers (those not negative) into the running best two
+  __device__ __forceinline__ void rank4(int64_t i, const int (&cj)[4], float& best, float& sec,
+                                        int& bj) const {
+    const T* xr = X + i * d;
+    float part[4] = {0.f, 0.f, 0.f, 0.f};
+    for (int t0 = 8 * (threadIdx.x & 15); t0 < d; t0 += 128) {
+      const bool in8 = t0 + 8 <= d;
+      float xv[8];
+      load8_split<T>(xr, t0, d, in8, vec, xv);
+      float cv[4][8];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const float* cr = cw + (int64_t)(cj[u] >= 0 ? cj[u] : 0) * d + t0;
+        if (cvec && in8) {
+          const float4 a = *reinterpret_cast<const float4*>(cr);
+          const float4 b = *reinterpret_cast<const float4*>(cr + 4);
+          cv[u][0] = a.x; cv[u][1] = a.y; cv[u][2] = a.z; cv[u][3] = a.w;
+          cv[u][4] = b.x; cv[u][5] = b.y; cv[u][6] = b.z; cv[u][7] = b.w;
+        } else {
+#pragma unroll
+          for (int e = 0; e < 8; ++e) cv[u][e] = t0 + e < d ? cr[e] : 0.f;
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const float diff = xv[e] - cv[u][e];
+          part[u] = __builtin_fmaf(diff, diff, part[u]);
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      float v = part[u];
+      v += __shfl_xor(v, 8);
+      v += __shfl_xor(v, 4);
+      v += __shfl_xor(v, 2);
+      v += __shfl_xor(v, 1);
+      const int j = cj[u];
+      if (j < 0 || j == bj) continue;
+      if (v < best || (v == best && j < bj)) {
+        sec = best;
+        best = v;
+        bj = j;
+      } else if (v < sec) {
+        sec = v;
+      }
+    }
+  }
+  // FP64 distance of center j into the running best
+  __device__ __forceinline__ void rank64(int64_t i, int j, double& bD, int& b64) const {
+    const T* xr = X + i * d;
+    double p = 0.0;
+    for (int t0 = 8 * (threadIdx.x & 15); t0 < d; t0 += 128) {
+      float xv[8];
+      load8_split<T>(xr, t0, d, t0 + 8 <= d, vec, xv);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const double cv = c64[(int64_t)j * d + (t0 + e < d ? t0 + e : 0)];
+        const double diff = t0 + e < d ? (double)xv[e] - cv : 0.0;
+        p = __builtin_fma(diff, diff, p);
+      }
+    }
+    p += __shfl_xor(p, 8);
+    p += __shfl_xor(p, 4);
+    p += __shfl_xor(p, 2);
+    p += __shfl_xor(p, 1);
+    if (p < bD || (p == bD && j < b64)) {
+      bD = p;
+      b64 = j;
+    }
+  }
+  // The nearest of all centers, by the block's 16 groups (every thread calls
+  // it; one group alone would walk k / 4 dependent loads).
+  __device__ int all_centers(int64_t i) const {
+    __shared__ float gbest[16], gsec[16];
+    __shared__ double gD[16];
+    __shared__ int gj[16];
+    const int li = threadIdx.x & 15, grp = threadIdx.x >> 4;
+    float best = INFINITY, sec = INFINITY;
+    int bj = INT_MAX;
+    for (int u0 = 4 * grp; u0 < k; u0 += 64) {
+      int cj[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) cj[u] = u0 + u < k ? u0 + u : -1;
+      rank4(i, cj, best, sec, bj);
+    }
+    __syncthreads();  // an earlier call's results were read
+    if (li == 0) {
+      gbest[grp] = best;
+      gsec[grp] = sec;
+      gj[grp] = bj;
+    }
+    __syncthreads();
+    best = sec = INFINITY;
+    bj = INT_MAX;
+#pragma unroll
+    for (int g = 0; g < 16; ++g) {
+      const float v = gbest[g];
+      if (v < best || (v == best && gj[g] < bj)) {
+        sec = fminf(best, gsec[g]);
+        best = v;
+        bj = gj[g];
+      } else {
+        sec = fminf(sec, v);
+      }
+    }
+    if (bj == INT_MAX || close(best, sec)) {  // the same in every thread
+      double bD = INFINITY;
+      int b64 = INT_MAX;
+      for (int u = grp; u < k; u += 16) rank64(i, u, bD, b64);
+      __syncthreads();
+      if (li == 0) {
+        gD[grp] = bD;
+        gj[grp] = b64;
+      }
+      __syncthreads();
+      bD = INFINITY;
+      bj = INT_MAX;
+#pragma unroll
+      for (int g = 0; g < 16; ++g)
+        if (gD[g] < bD || (gD[g] == bD && gj[g] < bj)) {
+          bD = gD[g];
+          bj = gj[g];
+        }
+    }
+    return bj;
+  }
+};
+
 // The split screen of all points: scores from 32x32x16 BF16 MFMAs over three
 // products per dim, c'lo x^ + c'hi xlo + c'hi x^ (c' = -2c = c'hi + c'lo + e,
 // x = x^ + xlo + r, BF16 parts; BF16 rows: x^ = x, two products), as in the
@@ -3281,19 +3432,33 @@ __device__ __forceinline__ void load8_split(const T* __restrict__ row, int t0, i
 // keys of its half of the centers); a point then knows its best three of both
 // halves.  Certain: the second best is out of the band of the best.  Otherwise,
 // with both halves' thirds out of the band, the (up to four) keys inside it are
-// the candidates; else any center may be.  The label then says so
-// (open_fields), and k_resolve decides.
+// the candidates; the label then holds them (open_fields) and k_resolve decides.
+// Else the point is queued, its label the threshold of its candidates' scores,
+// and the LIST variant sweeps the queued points again: every center at or below
+// the threshold becomes a candidate (up to 16), decided in the same kernel.
 // Why 256 points x 32 CT centers: 2 x CT accumulator tiles per wave reuse every
 // center operand for two point tiles, and two such blocks fit a CU (64 KB of
 // LDS, 256 VGPRs a wave), one wave's key updates beside another's MFMAs.
-template <typename T, int KC>
+template <typename T, int KC, bool LIST>
 __global__ __launch_bounds__(256, 2) void k_screen_split(
     const T* __restrict__ X, int64_t n, int d, int k, int nq, int bg,
     const uint16_t* __restrict__ cb16, const uint16_t* __restrict__ cb16lo,
-    const float* __restrict__ cnB, const PassState* __restrict__ st,
-    const int32_t* __restrict__ gate, int32_t* __restrict__ labels, double* __restrict__ Jpart,
-    long long* __restrict__ upart) {
+    const float* __restrict__ cnB, const float* __restrict__ cw, const double* __restrict__ c64,
+    PassState* __restrict__ st, const int32_t* __restrict__ gate, int32_t* __restrict__ labels,
+    uint32_t* __restrict__ queue, double* __restrict__ Jpart, long long* __restrict__ upart) {
   if (gated(gate)) return;
+  // LIST: the points the first sweep queued
+  if constexpr (LIST)
+    n = (int64_t)ld_agent(reinterpret_cast<const int32_t*>(&st->qcount));
+  constexpr int CMAX = 16;                   // candidates kept per queued point
+  __shared__ int cand_n[LIST ? 256 : 1];
+  __shared__ uint16_t cand_j[LIST ? 256 * CMAX : 1];
+  // the points a block queues gather in LDS: one atomic on the queue's length
+  // per some hundreds of them (one per wave cost more than the whole sweep)
+  constexpr int LQ = 1024;
+  __shared__ uint32_t lq[LIST ? 1 : LQ];
+  __shared__ int lqn;
+  __shared__ unsigned lqpos;
   constexpr int CT = kSplitTiles;
   constexpr int PB = KC * 512;               // elements of one part of a tile's chunk
   // two buffers as separate objects, each read by its own code path, so that
@@ -3323,12 +3488,23 @@ __global__ __launch_bounds__(256, 2) void k_screen_split(
   };
   int64_t nfull = 0, ncand = 0;
   int par = 0;         // buffer of the next chunk
+  int step = 0;        // steps since the block last looked at its queue
   int loaded = 1;      // chunks issued so far, when all of them stay in LDS
   const bool fixed = ns <= 2;
-  const int64_t first = (int64_t)blockIdx.x * 256;
+  // points per block and step: 256, or (LIST) as few as 64 so that a short queue
+  // spreads over the blocks
+  int ppb = 256;
+  if constexpr (LIST)
+    ppb = (int)min<int64_t>(256, max<int64_t>(64, ((n + gridDim.x - 1) / gridDim.x + 63) / 64 * 64));
+  const int wp = ppb >> 2;  // of them, a wave's
+  const int64_t first = (int64_t)blockIdx.x * ppb;
+  if constexpr (!LIST) {
+    if (threadIdx.x == 0) lqn = 0;
+    __syncthreads();
+  }
   if (first < n) issue(0, 0, buf0);
-  for (int64_t base = first; base < n; base += (int64_t)gridDim.x * 256) {
-    const bool last_base = base + (int64_t)gridDim.x * 256 >= n;
+  for (int64_t base = first; base < n; base += (int64_t)gridDim.x * ppb) {
+    const bool last_base = base + (int64_t)gridDim.x * ppb >= n;
     v8bf xh[2][KC], xl[2][KC];
     float s2[2] = {0.f, 0.f}, r2[2] = {0.f, 0.f};
     v8bf xa[2];          // the point's offset as the B operand of the last MFMA
@@ -3337,6 +3513,21 @@ __global__ __launch_bounds__(256, 2) void k_screen_split(
 #pragma unroll
     for (int p = 0; p < 2; ++p) m1[p] = m2[p] = m3[p] = INT_MAX;
     v16f acc[2][CT];
+    int64_t pt[2];       // the lane's points (rows past n read the last one)
+    float thr[2];
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+      const int64_t e = base + wave * wp + p * 32 + pc;
+      pt[p] = min(e, n - 1);
+      if constexpr (LIST) {
+        pt[p] = queue[pt[p]];
+        thr[p] = e < n && p * 32 + pc < wp ? __int_as_float(labels[pt[p]]) : -1.f;
+      }
+    }
+    if constexpr (LIST) {
+      cand_n[threadIdx.x] = 0;
+      __syncthreads();
+    }
     // rows of chunk q, split; the norms on the way in the first group
     auto load_chunk = [&](int q, bool norms) {
 #pragma unroll
@@ -3348,7 +3539,7 @@ __global__ __launch_bounds__(256, 2) void k_screen_split(
         const bool whole = 16 * (KC * q + s) + 16 <= d;
 #pragma unroll
         for (int p = 0; p < 2; ++p) {
-          const T* row = X + min(base + wave * 64 + p * 32 + pc, n - 1) * d;
+          const T* row = X + pt[p] * d;
           float v[8];
           load8_split<T>(row, t0, d, whole, vec, v);
           typedef float f32x2 __attribute__((ext_vector_type(2)));
@@ -3381,7 +3572,8 @@ __global__ __launch_bounds__(256, 2) void k_screen_split(
     // x^.e + xlo.(c' - c'hi) + r.c' (||e|| <= dcn, ||c' - c'hi|| <= 2^-8 ||c||,
     // ||r|| <= 2^-9 ||x - x^|| and ||xlo|| <= (1 + 2^-8) ||x - x^||), the
     // rounding of the FP32 sums (any rounding of every addition: nadd at the
-    // products' magnitude, 16 with the norms joining, the last MFMA), and that
+    // products' magnitude, and the six parts of the norms joining in the last
+    // MFMA, whose other products are zeros), and that
     // of ||c||^2 from cnB = ||c||^2 + B.  An error of the offset is common to
     // all scores of the point.
     auto point_norms = [&]() {
@@ -3393,7 +3585,7 @@ __global__ __launch_bounds__(256, 2) void k_screen_split(
         const float xr =
             sizeof(T) == 4 ? __builtin_amdgcn_sqrtf(sum_halves(r2[p], h)) * 1.01f : 0.f;
         const float xc = xn * cmax, nn = 1.1f * (cmax * cmax + xn2);
-        const float e1 = 0x1.03p-23f * (nadd * 2.05f * xc + 18.f * (nn + 2.05f * xc)) +
+        const float e1 = 0x1.03p-23f * (nadd * 2.05f * xc + 8.f * (nn + 2.05f * xc)) +
                          xn * dcn + 2.1f * 0x1p-8f * xr * cmax +
                          3.f * 0x1p-23f * (B + cmax * cmax) + 1e-30f;
         const float off = xn2 + 1.02f * e1 + (float)(16 * ksl + 16) * 0x1.03p-23f * xn2;
@@ -3490,6 +3682,15 @@ __global__ __launch_bounds__(256, 2) void k_screen_split(
         for (int p = 0; p < 2; ++p)
 #pragma unroll
           for (int r = 0; r < 16; ++r) {
+            if constexpr (LIST) {
+              const int j = (g * CT + t) * 32 + 8 * (r >> 2) + 4 * h + (r & 3);
+              if (acc[p][t][r] <= thr[p] && j < k) {
+                const int slot = wave * wp + p * 32 + pc;
+                const int c = atomicAdd(&cand_n[slot], 1);
+                if (c < CMAX) cand_j[slot * CMAX + c] = (uint16_t)j;
+              }
+              continue;
+            }
             // the lane half's 4h joins after the last group
             const int j = (g * CT + t) * 32 + 8 * (r >> 2) + (r & 3);
             const int kv = (__float_as_int(acc[p][t][r]) & keep) | j;
@@ -3497,6 +3698,43 @@ __global__ __launch_bounds__(256, 2) void k_screen_split(
             m2[p] = med3_i32(m1[p], kv, m2[p]);
             m1[p] = min(m1[p], kv);
           }
+    }
+    if constexpr (LIST) {
+      // decide among the collected centers: a group of 16 lanes per point, four
+      // center rows in flight; more centers than the list holds, or none: all
+      // of them, by the whole block
+      __syncthreads();
+      const int grp = threadIdx.x >> 4;
+      const int here = (int)min<int64_t>(ppb, n - base);
+      const Resolver<T> rs(X, d, k, vec, cw, c64, st->cmax);
+      for (int q = grp; q < here; q += 16) {
+        const int c = cand_n[q];
+        if (c < 1 || c > CMAX) continue;
+        const int64_t i = queue[base + q];
+        float best = INFINITY, sec = INFINITY;
+        int bj = INT_MAX;
+        for (int u0 = 0; u0 < c; u0 += 4) {
+          int cj[4];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) cj[u] = u0 + u < c ? cand_j[q * CMAX + u0 + u] : -1;
+          rs.rank4(i, cj, best, sec, bj);
+        }
+        if (rs.close(best, sec)) {
+          double bD = INFINITY;
+          bj = INT_MAX;
+          for (int u = 0; u < c; ++u) rs.rank64(i, cand_j[q * CMAX + u], bD, bj);
+        }
+        if ((threadIdx.x & 15) == 0) labels[i] = bj < k ? bj : 0;
+      }
+      for (int q = 0; q < here; ++q) {
+        const int c = cand_n[q];
+        if (c >= 1 && c <= CMAX) continue;
+        const int64_t i = queue[base + q];
+        const int bj = rs.all_centers(i);
+        if (threadIdx.x == 0) labels[i] = bj < k ? bj : 0;
+      }
+      __syncthreads();  // the lists are rebuilt for the next points
+      continue;
     }
     // lane l takes point l of the wave's 64: both halves' keys and its own band
     int a[3], b[3];
@@ -3538,23 +3776,44 @@ __global__ __launch_bounds__(256, 2) void k_screen_split(
       }
       for (int u = nc; u < nf; ++u) code |= (code & GM) << (bg * u);
       if (closed && nc >= 1 && nc <= nf) label = (int)(0x80000000u | (uint32_t)code);
-      if (label == -1) nfull += valid ? 1 : 0;
-      else ncand += valid ? 1 : 0;
     }
+    const bool full = valid && label == -1;
+    const unsigned long long bq = __ballot(full);
+    if (bq) {
+      int pos = 0;
+      if (lane == 0) pos = atomicAdd(&lqn, __popcll(bq));
+      pos = __shfl(pos, 0) + __popcll(bq & ((1ull << lane) - 1ull));
+      if (full) {
+        lq[pos] = (uint32_t)i;
+        // a center whose exact distance is at most the best's scores at most E2
+        // above the smallest score, whose key is within delta of it
+        label = __float_as_int((v1 + E2 + delta * (2.f * fabsf(v1) + E2)) * 1.0001f) & INT_MAX;
+      }
+    }
+    // at most 3 x 256 points join between two looks at the count
+    if (++step == 3 || last_base) {
+      step = 0;
+      __syncthreads();
+      const int have = lqn;
+      if (have > LQ - 768 || (last_base && have > 0)) {
+        if (threadIdx.x == 0) lqpos = atomicAdd(&st->qcount, (unsigned)have);
+        __syncthreads();
+        for (int e = threadIdx.x; e < have; e += 256) queue[lqpos + e] = lq[e];
+        __syncthreads();
+        if (threadIdx.x == 0) lqn = 0;
+      }
+      __syncthreads();
+    }
+    nfull += __popcll(bq);
+    ncand += __popcll(__ballot(valid && label < 0));
     if (valid) labels[i] = label;
   }
-  // block_sum_J takes counts that are uniform over a wave
-  block_sum_J(0.0, wave_sum_i64(nfull), wave_sum_i64(ncand), Jpart, upart);
+  if constexpr (!LIST) block_sum_J(0.0, nfull, ncand, Jpart, upart);
 }
 
-// Decides the points that k_screen_split left open: the nearest of a point's
-// candidates (or of all centers), lowest index among equal distances, by the
-// direct form: FP32 first, with its error bound, FP64 when the best two are
-// closer than that.  A block takes ranges of rb points and lists the open ones
-// in LDS; groups of 16 lanes take one point each, four center rows in flight.  A
-// point without candidates is worked on by all 16 groups of the block, each
-// over its share of the centers (one group alone walks k / 4 dependent loads:
-// 2,400 such points of 1e6 x 64, k = 256 took 0.7 ms).
+// Decides the points whose label holds candidates (k_screen_split).  A block
+// takes ranges of rb points and lists the open ones in LDS; groups of 16 lanes
+// take one point each.
 template <typename T>
 __global__ __launch_bounds__(256) void k_resolve(
     const T* __restrict__ X, int64_t n, int d, int k, int bg, int rb,
@@ -3562,93 +3821,14 @@ __global__ __launch_bounds__(256) void k_resolve(
     const PassState* __restrict__ st, const int32_t* __restrict__ gate,
     int32_t* __restrict__ labels) {
   if (gated(gate)) return;
-  __shared__ uint16_t list[4096];  // points with candidates from the front, others from the back
-  __shared__ int cnt, fcnt;
-  __shared__ float gbest[16], gsec[16];
-  __shared__ double gD[16];
-  __shared__ int gj[16];
+  __shared__ uint16_t list[4096];
+  __shared__ int cnt;
   const int li = threadIdx.x & 15, grp = threadIdx.x >> 4;
   const bool vec = (d & 7) == 0 && (reinterpret_cast<uintptr_t>(X) & 15u) == 0;
-  const bool cvec = (d & 3) == 0;
   const int GM = (1 << bg) - 1, nf = open_fields(bg);
-  // FP32 direct form over a lane's 8 ceil(d / 128) terms and four pairwise adds,
-  // plus 2 sqrt(D) ||c - cw|| for the rounded center
-  const float u32 = 0x1p-24f * 1.01f, cmax = st->cmax;
-  const float rel = (float)(8 * ((d + 127) / 128) + 6) * u32;
-  auto err = [&](float D) { return rel * D + 2.f * sqrtf(D) * u32 * cmax + 1e-30f; };
-  auto close = [&](float b, float s) { return !((s - b) > err(b) + err(s)); };
-  // FP32 distances of four centers (those not negative), summed over the group,
-  // into the running best two
-  auto rank4 = [&](const T* xr, const int (&cj)[4], float& best, float& sec, int& bj) {
-    float part[4] = {0.f, 0.f, 0.f, 0.f};
-    for (int t0 = 8 * li; t0 < d; t0 += 128) {
-      const bool in8 = t0 + 8 <= d;
-      float xv[8];
-      load8_split<T>(xr, t0, d, in8, vec, xv);
-      float cv[4][8];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const float* cr = cw + (int64_t)(cj[u] >= 0 ? cj[u] : 0) * d + t0;
-        if (cvec && in8) {
-          const float4 a = *reinterpret_cast<const float4*>(cr);
-          const float4 b = *reinterpret_cast<const float4*>(cr + 4);
-          cv[u][0] = a.x; cv[u][1] = a.y; cv[u][2] = a.z; cv[u][3] = a.w;
-          cv[u][4] = b.x; cv[u][5] = b.y; cv[u][6] = b.z; cv[u][7] = b.w;
-        } else {
-#pragma unroll
-          for (int e = 0; e < 8; ++e) cv[u][e] = t0 + e < d ? cr[e] : 0.f;
-        }
-      }
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const float diff = xv[e] - cv[u][e];
-          part[u] = __builtin_fmaf(diff, diff, part[u]);
-        }
-    }
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      float v = part[u];
-      v += __shfl_xor(v, 8);
-      v += __shfl_xor(v, 4);
-      v += __shfl_xor(v, 2);
-      v += __shfl_xor(v, 1);
-      const int j = cj[u];
-      if (j < 0 || j == bj) continue;
-      if (v < best || (v == best && j < bj)) {
-        sec = best;
-        best = v;
-        bj = j;
-      } else if (v < sec) {
-        sec = v;
-      }
-    }
-  };
-  // FP64 distance of center j, summed over the group, into the running best
-  auto rank64 = [&](const T* xr, int j, double& bD, int& b64) {
-    double p = 0.0;
-    for (int t0 = 8 * li; t0 < d; t0 += 128) {
-      float xv[8];
-      load8_split<T>(xr, t0, d, t0 + 8 <= d, vec, xv);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const double cv = c64[(int64_t)j * d + (t0 + e < d ? t0 + e : 0)];
-        const double diff = t0 + e < d ? (double)xv[e] - cv : 0.0;
-        p = __builtin_fma(diff, diff, p);
-      }
-    }
-    p += __shfl_xor(p, 8);
-    p += __shfl_xor(p, 4);
-    p += __shfl_xor(p, 2);
-    p += __shfl_xor(p, 1);
-    if (p < bD || (p == bD && j < b64)) {
-      bD = p;
-      b64 = j;
-    }
-  };
+  const Resolver<T> rs(X, d, k, vec, cw, c64, st->cmax);
   for (int64_t r0 = (int64_t)blockIdx.x * rb; r0 < n; r0 += (int64_t)gridDim.x * rb) {
-    if (threadIdx.x == 0) cnt = fcnt = 0;
+    if (threadIdx.x == 0) cnt = 0;
     __syncthreads();
     const int rn = (int)min<int64_t>(rb, n - r0);
 #pragma unroll 1
@@ -3660,18 +3840,14 @@ __global__ __launch_bounds__(256) void k_resolve(
         lv[u] = o < rn ? labels[r0 + o] : 0;
       }
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const uint16_t o = (uint16_t)(u0 + u * 256 + threadIdx.x);
-        if (lv[u] == -1) list[4095 - atomicAdd(&fcnt, 1)] = o;
-        else if (lv[u] < 0) list[atomicAdd(&cnt, 1)] = o;
-      }
+      for (int u = 0; u < 4; ++u)
+        if (lv[u] < 0) list[atomicAdd(&cnt, 1)] = (uint16_t)(u0 + u * 256 + threadIdx.x);
     }
     __syncthreads();
-    const int m = cnt, mf = fcnt;
+    const int m = cnt;
     for (int q = grp; q < m; q += 16) {
       const int64_t pt = r0 + list[q];
       const int code = labels[pt];
-      const T* xr = X + pt * d;
       int cj[4];
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
@@ -3680,69 +3856,17 @@ __global__ __launch_bounds__(256) void k_resolve(
       }
       float best = INFINITY, sec = INFINITY;
       int bj = INT_MAX;
-      rank4(xr, cj, best, sec, bj);
-      if (close(best, sec)) {
+      rs.rank4(pt, cj, best, sec, bj);
+      if (rs.close(best, sec)) {
         double bD = INFINITY;
         bj = INT_MAX;
 #pragma unroll
         for (int u = 0; u < 4; ++u)
-          if (cj[u] >= 0 && cj[u] != bj) rank64(xr, cj[u], bD, bj);
+          if (cj[u] >= 0 && cj[u] != bj) rs.rank64(pt, cj[u], bD, bj);
       }
       if (li == 0) labels[pt] = bj < k ? bj : 0;
     }
-    for (int q = 0; q < mf; ++q) {
-      const int64_t pt = r0 + list[4095 - q];
-      const T* xr = X + pt * d;
-      float best = INFINITY, sec = INFINITY;
-      int bj = INT_MAX;
-      for (int u0 = 4 * grp; u0 < k; u0 += 64) {
-        int cj[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) cj[u] = u0 + u < k ? u0 + u : -1;
-        rank4(xr, cj, best, sec, bj);
-      }
-      if (li == 0) {
-        gbest[grp] = best;
-        gsec[grp] = sec;
-        gj[grp] = bj;
-      }
-      __syncthreads();
-      best = sec = INFINITY;
-      bj = INT_MAX;
-#pragma unroll
-      for (int g = 0; g < 16; ++g) {
-        const float v = gbest[g];
-        if (v < best || (v == best && gj[g] < bj)) {
-          sec = fminf(best, gsec[g]);
-          best = v;
-          bj = gj[g];
-        } else {
-          sec = fminf(sec, v);
-        }
-      }
-      if (bj == INT_MAX || close(best, sec)) {  // the same in every thread
-        double bD = INFINITY;
-        int b64 = INT_MAX;
-        for (int u = grp; u < k; u += 16) rank64(xr, u, bD, b64);
-        __syncthreads();
-        if (li == 0) {
-          gD[grp] = bD;
-          gj[grp] = b64;
-        }
-        __syncthreads();
-        bD = INFINITY;
-        bj = INT_MAX;
-#pragma unroll
-        for (int g = 0; g < 16; ++g)
-          if (gD[g] < bD || (gD[g] == bD && gj[g] < bj)) {
-            bD = gD[g];
-            bj = gj[g];
-          }
-      }
-      if (threadIdx.x == 0) labels[pt] = bj < k ? bj : 0;
-      __syncthreads();  // the groups' results are read before the next point's
-    }
-    __syncthreads();  // the lists are rebuilt for the next range
+    __syncthreads();  // the list is rebuilt for the next range
   }
 }
 
@@ -5088,13 +5212,13 @@ static void visit_rescreen(int ks, F&& f) {
 
 // Split screen for a plan's 16-dim steps per chunk (p.kd; p.nt chunks, p.ks steps
 // in all).
-template <typename T, typename F>
+template <typename T, bool LIST, typename F>
 static void visit_split(int kc, F&& f) {
   switch (kc) {
-    case 1: f(k_screen_split<T, 1>); break;
-    case 2: f(k_screen_split<T, 2>); break;
-    case 3: f(k_screen_split<T, 3>); break;
-    default: f(k_screen_split<T, 4>); break;
+    case 1: f(k_screen_split<T, 1, LIST>); break;
+    case 2: f(k_screen_split<T, 2, LIST>); break;
+    case 3: f(k_screen_split<T, 3, LIST>); break;
+    default: f(k_screen_split<T, 4, LIST>); break;
   }
 }
 // Rows of its center copy (whole groups) and the index bits of its keys.
@@ -5124,7 +5248,7 @@ template <typename T>
 static int64_t plan_blocks(const PassPlan& p, int cus) {
   int64_t r = 0;
   auto f = [&](auto kern) { r = resident_blocks(kern, p.lds_assign, cus); };
-  if (p.split) visit_split<T>(p.kd, [&](auto kern) { r = resident_blocks(kern, 0, cus); });
+  if (p.split) visit_split<T, false>(p.kd, [&](auto kern) { r = resident_blocks(kern, 0, cus); });
   else if (p.bf16)
     visit_screen<T>(
         p.ks, [&](auto kern) { r = resident_blocks(kern, 0, cus, screen_threads(p.ks)); },
@@ -5420,21 +5544,24 @@ static void dispatch_rescreen(const PassBufs& b, const PassPlan& p, const int32_
   });
 }
 
-// The split screen of all points, and the decision of those it leaves open.
-template <typename T>
+// The split screen of all points, or (LIST) of those its first sweep queued; the
+// queue is the label order's buffer, which the sorted update fills later.
+template <typename T, bool LIST>
 static void dispatch_split(const PassBufs& b, const PassPlan& p, const int32_t* gate,
                            hipStream_t s) {
-  visit_split<T>(p.kd, [&](auto kern) {
+  visit_split<T, LIST>(p.kd, [&](auto kern) {
     hipLaunchKernelGGL(kern, dim3((unsigned)p.blocks), dim3(256), 0, s, (const T*)b.X, b.n, b.d,
                        b.k, p.nt, split_bits(b.k), (const uint16_t*)copy_hi(b, p),
-                       (const uint16_t*)copy_lo(b, p), (const float*)b.cnB,
-                       (const PassState*)b.st, gate, b.labels, b.Jpart, b.upart);
+                       (const uint16_t*)copy_lo(b, p), (const float*)b.cnB, (const float*)b.cw,
+                       (const double*)b.c64, b.st, gate, b.labels, b.perm, b.Jpart, b.upart);
   });
 }
 
+// The points the screen's first sweep left open.
 template <typename T>
 static void dispatch_resolve(const PassBufs& b, const PassPlan& p, const int32_t* gate,
                              hipStream_t s) {
+  dispatch_split<T, true>(b, p, gate, s);
   // ranges of 256 to 4096 points, one per resident block while there are enough
   const int64_t cap = std::max<int64_t>(1, p.rr_blocks);
   const int64_t rb = std::min<int64_t>(4096, std::max<int64_t>(256, (b.n / cap + 255) / 256 * 256));
@@ -5447,8 +5574,8 @@ static void dispatch_resolve(const PassBufs& b, const PassPlan& p, const int32_t
 hipError_t pass_assign(const PassBufs& b, const PassPlan& p, bool update, hipStream_t s) {
   const int32_t* gate = update ? &b.st->done : nullptr;
   if (p.split) {
-    if (b.dtype == 0) dispatch_split<float>(b, p, gate, s);
-    else dispatch_split<uint16_t>(b, p, gate, s);
+    if (b.dtype == 0) dispatch_split<float, false>(b, p, gate, s);
+    else dispatch_split<uint16_t, false>(b, p, gate, s);
   } else if (p.bf16) {
     if (b.dtype == 0) dispatch_bf16<float>(b, p, gate, s);
     else dispatch_bf16<uint16_t>(b, p, gate, s);
