@@ -371,36 +371,48 @@ hipError_t stage_reset(PassState* st, hipStream_t s) {
   return hipGetLastError();
 }
 
-// E consecutive elements of a row widened to FP32: one 16-byte load when E
-// elements fill 16 bytes (the caller guarantees the alignment), else E loads.
+// A piece of E consecutive elements of a row as packed words (one element: FP32
+// bits, or BF16 bits in the low half), loaded as one vector of dwords (rows need
+// only start on a dword).
+typedef uint32_t u32x4a4 __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t u32x2a4 __attribute__((ext_vector_type(2), aligned(4)));
 template <typename T, int E>
-__device__ __forceinline__ void load_vec(const T* __restrict__ p, bool ok, float (&v)[E]) {
-  if constexpr (E * sizeof(T) == 16) {
-    uint4 w = make_uint4(0u, 0u, 0u, 0u);
-    if (ok) w = *reinterpret_cast<const uint4*>(p);
-    const uint32_t w4[4] = {w.x, w.y, w.z, w.w};
+struct Piece {
+  static constexpr int W = (E * (int)sizeof(T) + 3) / 4;
+  uint32_t w[W];
+  __device__ __forceinline__ void load(const T* __restrict__ p) {
+    if constexpr (E * sizeof(T) == 16) {
+      const u32x4a4 v = *reinterpret_cast<const u32x4a4*>(p);
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      if constexpr (sizeof(T) == 4) {
-        v[u] = __uint_as_float(w4[u]);
-      } else {
-        v[2 * u] = __uint_as_float(w4[u] << 16);
-        v[2 * u + 1] = __uint_as_float(w4[u] & 0xffff0000u);
-      }
+      for (int u = 0; u < 4; ++u) w[u] = v[u];
+    } else if constexpr (E * sizeof(T) == 8) {
+      const u32x2a4 v = *reinterpret_cast<const u32x2a4*>(p);
+      w[0] = v[0];
+      w[1] = v[1];
+    } else if constexpr (E * sizeof(T) == 4) {
+      w[0] = *reinterpret_cast<const uint32_t*>(p);
+    } else {
+      w[0] = p[0];
     }
-  } else {
-#pragma unroll
-    for (int e = 0; e < E; ++e) v[e] = ok ? widen<T>(p[e]) : 0.f;
   }
-}
+  __device__ __forceinline__ void zero() {
+#pragma unroll
+    for (int u = 0; u < W; ++u) w[u] = 0u;
+  }
+  __device__ __forceinline__ float at(int e) const {
+    if constexpr (sizeof(T) == 4) return __uint_as_float(w[e]);
+    else return __uint_as_float((e & 1) ? w[e >> 1] & 0xffff0000u : w[e >> 1] << 16);
+  }
+};
 
-// Elements per lane of the row-group kernels: 16 bytes when every row starts
-// on a 16-byte boundary, else one.
+// Elements per lane of the row-group kernels: the largest piece of at most 16
+// bytes that a row holds, loaded as dwords (BF16 rows must then start on one:
+// an even d and a dword-aligned X; otherwise one element).  A row's last piece
+// ends with the row and overlaps the one before when d is not a multiple of it.
 int row_vec(int dtype, int32_t d, const void* X) {
-  const int E = dtype == 0 ? 4 : 8;
-  const size_t s = dtype == 0 ? 4 : 2;
-  const bool aligned = ((size_t)d * s) % 16 == 0 && (reinterpret_cast<uintptr_t>(X) & 15u) == 0;
-  return aligned ? E : 1;
+  if (dtype == 0) return d >= 4 ? 4 : d >= 2 ? 2 : 1;
+  if ((d & 1) || (reinterpret_cast<uintptr_t>(X) & 3u)) return 1;
+  return d >= 8 ? 8 : d >= 4 ? 4 : 2;
 }
 
 // log2 of the lanes that cover one row: E*G >= d, G a power of two <= 64.
@@ -413,37 +425,50 @@ int row_glog(int32_t d, int E) {
 
 // Per stage: max |x| over all elements (NaN/Inf show as bits >= 0x7f800000) and,
 // with norms, max ||x||^2 over the rows.  A group of G = 2^glog lanes covers a
-// row, each lane E consecutive elements per column step, so a wave reads whole
-// rows with 16-byte loads.
+// row, each lane a piece of E elements per column step, four rows in flight per
+// lane (one row at a time, read element by element where rows are not whole
+// 16-byte pieces, took 201 us for 1e6 x 64 FP32 and 249 us for 1e6 x 100 BF16).
+// Both maxima are upper bounds wherever they are used, so a piece that overlaps
+// its neighbour only has to leave the shared elements out of the norm.
 template <typename T, int E>
 __global__ __launch_bounds__(256) void k_row_stats(const T* __restrict__ X, int64_t rows, int d,
                                                    int glog, int norms,
                                                    PassState* __restrict__ st) {
+  constexpr int R = 4;
   const int G = 1 << glog;
   const int lane = threadIdx.x & 63, gi = lane >> glog, gl = lane & (G - 1);
+  const int rpw = 64 >> glog;  // rows of a wave's step
   const int64_t wave = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  const int64_t step = (int64_t)gridDim.x * 4 * (64 >> glog);
+  const int64_t step = (int64_t)gridDim.x * 4 * rpw * R;
   uint32_t mx = 0u;
   float xn2 = 0.f;
-  for (int64_t base = wave * (64 >> glog); base < rows; base += step) {
-    const int64_t r = base + gi;
-    const bool valid = r < rows;
-    const T* xr = X + (valid ? r : 0) * d;
-    float s2 = 0.f;
-    for (int c0 = gl * E; c0 < d; c0 += G * E) {
-      float v[E];
-      load_vec<T, E>(xr + c0, valid, v);
+  for (int64_t base = wave * rpw * R; base < rows; base += step) {
+    float s2[R] = {0.f, 0.f, 0.f, 0.f};
+    const T* xr[R];
 #pragma unroll
-      for (int e = 0; e < E; ++e) {
-        const bool in = E == 1 || c0 + e < d;
-        const float f = in ? v[e] : 0.f;
-        mx = max(mx, __float_as_uint(f) & 0x7fffffffu);
-        s2 = __builtin_fmaf(f, f, s2);
-      }
+    for (int r = 0; r < R; ++r)  // (rows past the end read the last one again)
+      xr[r] = X + min(base + r * rpw + gi, rows - 1) * d;
+    for (int c0 = gl * E; c0 < d; c0 += G * E) {
+      const int col = min(c0, d - E), skip = c0 - col;
+      Piece<T, E> v[R];
+#pragma unroll
+      for (int r = 0; r < R; ++r) v[r].load(xr[r] + col);
+#pragma unroll
+      for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+          const float f = v[r].at(e);
+          mx = max(mx, __float_as_uint(f) & 0x7fffffffu);
+          const float g = e >= skip ? f : 0.f;
+          s2[r] = __builtin_fmaf(g, g, s2[r]);
+        }
     }
     if (norms) {
-      for (int o = G >> 1; o > 0; o >>= 1) s2 += __shfl_xor(s2, o);
-      xn2 = fmaxf(xn2, s2);
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        for (int o = G >> 1; o > 0; o >>= 1) s2[r] += __shfl_xor(s2[r], o);
+        xn2 = fmaxf(xn2, s2[r]);
+      }
     }
   }
   for (int o = 32; o > 0; o >>= 1) {
@@ -465,21 +490,32 @@ __global__ __launch_bounds__(256) void k_row_stats(const T* __restrict__ X, int6
   }
 }
 
+// Calls f with the piece size as a constant.
+template <typename F>
+static void visit_vec(int dtype, int E, F&& f) {
+  switch (E) {
+    case 8: f(std::integral_constant<int, 8>()); break;
+    case 4: f(std::integral_constant<int, 4>()); break;
+    case 2: f(std::integral_constant<int, 2>()); break;
+    default: f(std::integral_constant<int, 1>()); break;
+  }
+}
+
 hipError_t row_stats(const void* X, int dtype, int64_t rows, int32_t d, bool norms,
                      PassState* st, hipStream_t s) {
   const int E = row_vec(dtype, d, X), glog = row_glog(d, E);
-  const int64_t waves = (rows + (64 >> glog) - 1) / (64 >> glog);
-  const unsigned g = (unsigned)std::max<int64_t>(1, std::min<int64_t>((waves + 3) / 4, 8192));
+  const int64_t waves = (rows + 4 * (64 >> glog) - 1) / (4 * (64 >> glog));
+  const unsigned g = (unsigned)std::max<int64_t>(1, std::min<int64_t>((waves + 3) / 4, 2048));
   auto go = [&](auto kern, auto* x) {
     hipLaunchKernelGGL(kern, dim3(g), dim3(256), 0, s, x, rows, d, glog, norms ? 1 : 0, st);
   };
-  if (dtype == 0) {
-    if (E == 4) go(k_row_stats<float, 4>, (const float*)X);
-    else go(k_row_stats<float, 1>, (const float*)X);
-  } else {
-    if (E == 8) go(k_row_stats<uint16_t, 8>, (const uint16_t*)X);
-    else go(k_row_stats<uint16_t, 1>, (const uint16_t*)X);
-  }
+  visit_vec(dtype, E, [&](auto e) {
+    if (dtype == 0) {
+      if constexpr (e() <= 4) go(k_row_stats<float, e()>, (const float*)X);
+    } else {
+      go(k_row_stats<uint16_t, e()>, (const uint16_t*)X);
+    }
+  });
   return hipGetLastError();
 }
 
@@ -1195,29 +1231,24 @@ __global__ __launch_bounds__(256) void k_lab_scatter_lds(const int32_t* __restri
   }
 }
 
-// The E center coordinates of a lane (FP64).
-template <int E>
-__device__ __forceinline__ void load_center(const double* __restrict__ c64, int j, int d, int col,
-                                            bool act, double (&c)[E]) {
-#pragma unroll
-  for (int e = 0; e < E; ++e) c[e] = act ? c64[(int64_t)j * d + col + e] : 0.0;
-}
-
 // A group of G = 2^glog lanes walks positions [p0, p0 + pg) of the label order
 // (pg <= 2^13); lane gl owns the E dims at col = blockIdx.y*G*E + gl*E.  Per run
 // of equal labels it adds rint(x * 2^F) in FP64 registers (exact integers below
-// 2^43) and flushes them to slot row (group mod kSlots) with 64-bit atomics when
+// 2^43) and flushes them to slot row (group mod nslots) with 64-bit atomics when
 // the run ends.  J: each lane's part of a point's squared distance to the run's
 // center, rounded to a multiple of 2^-FJ (below 2^80 units), is added as two
 // 40-bit limbs (exact in FP64 over 2^13 points); the group's limbs are summed
 // once at the end into jslots.  Every sum is an exact integer, so neither the
 // order of the label sort nor that of the atomics changes a bit of the result.
-template <typename T, int E>
+// TAIL (E does not divide d): a row's last piece is loaded so that it ends with
+// the row, and the elements that the piece before owns are left out.
+// update = 0 (a labelling pass): J alone.
+template <typename T, int E, bool TAIL>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k_run_sums(
     const T* __restrict__ X, int64_t n, int d, int k, int glog, int64_t pg,
     const uint32_t* __restrict__ perm, const long long* __restrict__ start,
     const double* __restrict__ c64, const PassState* __restrict__ st,
-    const int32_t* __restrict__ gate, long long* __restrict__ slots,
+    const int32_t* __restrict__ gate, int update, long long* __restrict__ slots,
     long long* __restrict__ jslots, int nslots) {
   if (gated(gate)) return;
   const int G = 1 << glog;
@@ -1225,8 +1256,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k
   const int64_t group = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * (64 >> glog) + gi;
   // groups past the end walk nothing but still take part in the final reduction
   const int64_t p0 = min(n, group * pg), p1 = min(n, p0 + pg);
-  const int col = (int)blockIdx.y * G * E + gl * E;
-  const bool act = col < d;  // E > 1 divides d
+  const int own = (int)blockIdx.y * G * E + gl * E;
+  const bool act = own < d;
+  const int col = TAIL ? max(0, min(own, d - E)) : own;
+  const int skip = TAIL ? own - col : 0;  // elements of the piece that are not its own
   const float scale = st->scale;
   const double sj = ldexp(1.0, st->FJ);
   // the label of position p0: the largest j with start[j] <= p0 (start[k] = n > p0)
@@ -1239,7 +1272,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k
   int j = lo;
   int64_t run_end = p0 < n ? start[j + 1] : n;
   double c[E], acc[E];
-  load_center<E>(c64, j, d, col, act && p0 < n, c);
+  auto load_center = [&](int jj, bool ok) {
+#pragma unroll
+    for (int e = 0; e < E; ++e) c[e] = ok ? c64[(int64_t)jj * d + col + e] : 0.0;
+  };
+  load_center(j, act && p0 < n);
 #pragma unroll
   for (int e = 0; e < E; ++e) acc[e] = 0.0;
   double j0 = 0.0, j1 = 0.0;  // J limbs: units of 2^-FJ and of 2^(40-FJ)
@@ -1248,44 +1285,38 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k
   long long* srow = slots + (int64_t)slot * k * (d + 1);
   auto flush = [&]() {
     if (cnt == 0) return;
-    long long* row = srow + (int64_t)j * (d + 1);
+    if (update) {
+      long long* row = srow + (int64_t)j * (d + 1);
 #pragma unroll
-    for (int e = 0; e < E; ++e) {
-      const long long v = (long long)acc[e];
-      if (act && v) atomicAdd(reinterpret_cast<unsigned long long*>(&row[col + e]),
-                              (unsigned long long)v);
-      acc[e] = 0.0;
+      for (int e = 0; e < E; ++e) {
+        const long long v = (long long)acc[e];
+        if (act && v && (!TAIL || e >= skip))
+          atomicAdd(reinterpret_cast<unsigned long long*>(&row[col + e]), (unsigned long long)v);
+        acc[e] = 0.0;
+      }
+      if (blockIdx.y == 0 && gl == 0)
+        atomicAdd(reinterpret_cast<unsigned long long*>(&row[d]), (unsigned long long)cnt);
     }
-    if (blockIdx.y == 0 && gl == 0)
-      atomicAdd(reinterpret_cast<unsigned long long*>(&row[d]), (unsigned long long)cnt);
     cnt = 0;
   };
-  // Rows in flight per group.  Whole 16-byte pieces stay packed until added,
-  // and only two are in flight, which fits the kernel in five waves per SIMD:
+  // Rows in flight per group.  Pieces stay packed until added, and of 16-byte
+  // ones only two are in flight, which fits the kernel in five waves per SIMD:
   // the gathered rows are served faster by more resident groups than by
   // deeper batches per group (8 rows at three waves per SIMD, or 16 at two,
   // measured slower; the 8-element form spills a few registers at five waves
   // and is still the fastest).
-  constexpr bool PK = E * sizeof(T) == 16;
-  constexpr int R = PK ? 2 : 8;
+  constexpr int R = E * sizeof(T) == 16 ? 2 : E * sizeof(T) == 8 ? 4 : 8;
   // the label order's row indices of the next R positions, loaded one batch
   // ahead so that the row loads do not wait for them
   uint32_t pidx[R];
 #pragma unroll
   for (int r = 0; r < R; ++r) pidx[r] = p0 + r < p1 ? perm[p0 + r] : 0u;
   for (int64_t p = p0; p < p1; p += R) {
-    uint4 xw[PK ? R : 1];
-    float xf[PK ? 1 : R][E];
+    Piece<T, E> xw[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-      const bool in = p + r < p1;
-      const T* src = X + (int64_t)pidx[r] * d + col;
-      if constexpr (PK) {
-        xw[r] = make_uint4(0u, 0u, 0u, 0u);
-        if (in && act) xw[r] = *reinterpret_cast<const uint4*>(src);
-      } else {
-        load_vec<T, E>(src, in && act, xf[r]);
-      }
+      xw[r].zero();
+      if (p + r < p1 && act) xw[r].load(X + (int64_t)pidx[r] * d + col);
     }
 #pragma unroll
     for (int r = 0; r < R; ++r) pidx[r] = p + R + r < p1 ? perm[p + R + r] : 0u;
@@ -1299,29 +1330,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k
             ++j;
             run_end = start[j + 1];
           } while (pr >= run_end);
-          load_center<E>(c64, j, d, col, act, c);
-        }
-        float x[E];
-        if constexpr (PK) {
-          const uint32_t w4[4] = {xw[r].x, xw[r].y, xw[r].z, xw[r].w};
-#pragma unroll
-          for (int u = 0; u < 4; ++u) {
-            if constexpr (sizeof(T) == 4) {
-              x[u] = __uint_as_float(w4[u]);
-            } else {
-              x[2 * u] = __uint_as_float(w4[u] << 16);
-              x[2 * u + 1] = __uint_as_float(w4[u] & 0xffff0000u);
-            }
-          }
-        } else {
-#pragma unroll
-          for (int e = 0; e < E; ++e) x[e] = xf[r][e];
+          load_center(j, act);
         }
         double part = 0.0;
 #pragma unroll
         for (int e = 0; e < E; ++e) {
-          acc[e] += (double)rintf(x[e] * scale);
-          const double df = (double)x[e] - c[e];
+          const float x = xw[r].at(e);
+          acc[e] += (double)rintf(x * scale);
+          double df = (double)x - c[e];
+          if (TAIL && e < skip) df = 0.0;
           part = part + df * df;
         }
         const double q = rint(part * sj);
@@ -4334,11 +4351,12 @@ __global__ __launch_bounds__(256) void k_reseed(const T* __restrict__ X, int d, 
   }
 }
 
-// J and FP64-check counts of a labelling pass of the fused paths.  One block.
+// J and FP64-check counts of a labelling pass.  One block.
 __global__ __launch_bounds__(256) void k_sum_J(PassState* __restrict__ st,
                                                const double* __restrict__ Jpart,
-                                               const long long* __restrict__ upart, int64_t nb) {
-  conclude_block(st, Jpart, upart, nb, nullptr, nullptr, nullptr, nullptr, 0, false, nullptr,
+                                               const long long* __restrict__ upart, int64_t nb,
+                                               long long* __restrict__ jslots) {
+  conclude_block(st, Jpart, upart, nb, jslots, nullptr, nullptr, nullptr, 0, false, nullptr,
                  nullptr);
 }
 
@@ -5374,20 +5392,17 @@ PassPlan plan_pass(int64_t rows, int32_t d, int32_t k, int dtype, int precision,
       p.pg = std::min<int64_t>(1 << 13, std::max<int64_t>(64, (rows + 65535) / 65536));
       // every group walks pg positions, so the groups are sized to fill whole
       // generations of resident run-sum blocks (a last, partly filled one
-      // leaves most of the GPU idle); rows of whole 16-byte pieces assumed,
-      // and any pg in [64, 2^13] is correct
-      const int E = dtype == 0 ? 4 : 8;
-      if (((int64_t)d * (dtype == 0 ? 4 : 2)) % 16 == 0) {
-        const int glog = row_glog(d, E);
-        const int64_t ncb = (d + (E << glog) - 1) / (E << glog);
-        const int64_t res = dtype == 0 ? resident_blocks(k_run_sums<float, 4>, 0, cus)
-                                       : resident_blocks(k_run_sums<uint16_t, 8>, 0, cus);
-        const int64_t gpg = std::max<int64_t>(1, res / ncb) * 4 * (64 >> glog);
-        int64_t gens = std::max<int64_t>(1, (65536 + gpg / 2) / gpg);
-        gens = std::max(gens, (rows + gpg * 8192 - 1) / (gpg * 8192));
-        p.pg = std::min<int64_t>(1 << 13,
-                                 std::max<int64_t>(64, (rows + gens * gpg - 1) / (gens * gpg)));
-      }
+      // leaves most of the GPU idle); any pg in [64, 2^13] is correct
+      // (rows on dwords assumed)
+      const int E = row_vec(dtype, d, nullptr), glog = row_glog(d, E);
+      const int64_t ncb = (d + (E << glog) - 1) / (E << glog);
+      const int64_t res = dtype == 0 ? resident_blocks(k_run_sums<float, 4, false>, 0, cus)
+                                     : resident_blocks(k_run_sums<uint16_t, 8, false>, 0, cus);
+      const int64_t gpg = std::max<int64_t>(1, res / ncb) * 4 * (64 >> glog);
+      int64_t gens = std::max<int64_t>(1, (65536 + gpg / 2) / gpg);
+      gens = std::max(gens, (rows + gpg * 8192 - 1) / (gpg * 8192));
+      p.pg = std::min<int64_t>(1 << 13,
+                               std::max<int64_t>(64, (rows + gens * gpg - 1) / (gens * gpg)));
     }
   }
   // a persistent grid: no more blocks than stay resident at once
@@ -5456,7 +5471,7 @@ int row_vec(int dtype, int32_t d, const void* X);
 int row_glog(int32_t d, int E);
 
 // Counting sort of the point indices by label, then the run sums.
-static void sorted_update(const PassBufs& b, const PassPlan& p, const int32_t* gate,
+static void sorted_update(const PassBufs& b, const PassPlan& p, bool update, const int32_t* gate,
                           hipStream_t s) {
   const int64_t G = p.sort_chunks, cn = (int64_t)b.k * G;
   const size_t lds = b.k <= kHistLds ? (size_t)b.k * 4 : 0;
@@ -5489,16 +5504,21 @@ static void sorted_update(const PassBufs& b, const PassPlan& p, const int32_t* g
   auto go = [&](auto kern, auto* x) {
     hipLaunchKernelGGL(kern, grid, dim3(256), 0, s, x, b.n, b.d, b.k, glog, p.pg,
                        (const uint32_t*)b.perm, (const long long*)b.rstart,
-                       (const double*)b.c64, (const PassState*)b.st, gate, b.slots, b.jslots,
-                       plan_slots(p));
+                       (const double*)b.c64, (const PassState*)b.st, gate, update ? 1 : 0,
+                       b.slots, b.jslots, plan_slots(p));
   };
-  if (b.dtype == 0) {
-    if (E == 4) go(k_run_sums<float, 4>, (const float*)b.X);
-    else go(k_run_sums<float, 1>, (const float*)b.X);
-  } else {
-    if (E == 8) go(k_run_sums<uint16_t, 8>, (const uint16_t*)b.X);
-    else go(k_run_sums<uint16_t, 1>, (const uint16_t*)b.X);
-  }
+  const bool tail = b.d % E != 0;
+  visit_vec(b.dtype, E, [&](auto e) {
+    if (b.dtype == 0) {
+      if constexpr (e() <= 4) {
+        if (tail) go(k_run_sums<float, e(), true>, (const float*)b.X);
+        else go(k_run_sums<float, e(), false>, (const float*)b.X);
+      }
+    } else {
+      if (tail) go(k_run_sums<uint16_t, e(), true>, (const uint16_t*)b.X);
+      else go(k_run_sums<uint16_t, e(), false>, (const uint16_t*)b.X);
+    }
+  });
 }
 
 template <typename T>
@@ -5609,8 +5629,8 @@ hipError_t pass_rest(const PassBufs& b, const PassPlan& p, bool update, hipStrea
   // and split screens, J of every pass; the FP32 kernels add J themselves in a
   // labelling pass.
   const bool sorted = !p.fused && (update || p.bf16 || p.split);
-  if (sorted) sorted_update(b, p, gate, s);
-  if (update || sorted) {
+  if (sorted) sorted_update(b, p, update, gate, s);
+  if (update) {
     hipLaunchKernelGGL(k_finalize, dim3((unsigned)b.k), dim3(256), 0, s, b.slots,
                        sorted ? b.jslots : nullptr, b.k, b.d, b.st, gate, update ? 1 : 0, b.c64,
                        b.cw, b.cn, b.cnorm, b.shiftj, b.emptyj, b.S_out, b.N_out,
@@ -5636,7 +5656,7 @@ hipError_t pass_rest(const PassBufs& b, const PassPlan& p, bool update, hipStrea
     }
   } else {
     hipLaunchKernelGGL(k_sum_J, dim3(1), dim3(256), 0, s, b.st, (const double*)b.Jpart,
-                       (const long long*)b.upart, nb);
+                       (const long long*)b.upart, nb, sorted ? b.jslots : nullptr);
   }
   return hipGetLastError();
 }

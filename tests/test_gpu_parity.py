@@ -619,3 +619,24 @@ def test_split_screen_any_d_extreme_magnitudes(scale):
     rlab, D1, _ = oracle.assign(Xh, C)
     assert np.array_equal(lab.cpu().numpy(), rlab)
     assert abs(J - D1.sum()) <= 1e-9 * D1.sum()
+
+
+@pytest.mark.parametrize("d", [1, 2, 3, 5, 6, 7, 10, 13, 30, 66, 130, 258])
+@pytest.mark.parametrize("dtype,offset", [("f32", 0), ("f32", 1), ("bf16", 0), ("bf16", 1),
+                                          ("bf16", 2)])
+def test_row_pieces_any_alignment(d, dtype, offset):
+    """Stage statistics and sorted sums over rows whose last piece overlaps the
+    one before, of odd length, and starting `offset` elements past a 16-byte
+    boundary: sums, movement and J as the oracle's."""
+    n, k = 3_001, 300 if d <= 130 else 70
+    Xh = _mixture(n, d, 20, seed=d + offset, dtype=dtype)
+    Xd = to_device(Xh).reshape(-1)
+    flat = torch.zeros(n * d + offset, dtype=Xd.dtype, device="cuda")
+    flat[offset:] = Xd
+    X = flat[offset:].view(n, d)
+    C = _centers_from(Xh, k, seed=d, jitter=0.4)
+    out = km.km_step(X, torch.from_numpy(C).cuda())
+    ref = oracle.step(Xh, C)
+    assert_step(out, Xh, C, ref, jtol=1e-9, name=f"pieces d={d} {dtype} +{offset}")
+    lab2, J2, _ = km.km_assign(X, torch.from_numpy(C).cuda())
+    assert_step({"labels": lab2, "J": J2}, Xh, C, ref, jtol=1e-9, name="pieces assign")
