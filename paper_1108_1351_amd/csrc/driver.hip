@@ -215,7 +215,6 @@ km_status run_stage(PassBufs b, const PassPlan& plan, int32_t max_iter, double t
                       reseed));
   HIP_TRY(prep_copy(b, plan, s));
   HIP_TRY(zero_sums(b, plan, s));
-  HIP_TRY(zero_i64(b.jslots, (int64_t)kSlots * 2, s));
   // Passes go out in chunks (2, 4, 8, then 16), each followed by a copy of the
   // pass state.  One more chunk is queued before the host waits for a chunk's
   // state, so the device does not idle while the host reads it; passes queued
@@ -727,7 +726,6 @@ static km_status one_pass(const void* X, km_dtype dtype, int64_t n, int32_t d, c
   HIP_TRY(stage_begin(b.st, 1, 0.0, n, b.cnorm, k, d, p.fused ? 0 : p.pg, s));
   HIP_TRY(prep_copy(b, p, s));
   HIP_TRY(zero_sums(b, p, s));
-  HIP_TRY(zero_i64(b.jslots, (int64_t)kSlots * 2, s));
   HIP_TRY(hipMemcpyAsync(&hs, b.st, sizeof hs, hipMemcpyDeviceToHost, s));
   HIP_TRY(hipStreamSynchronize(s));
   if (hs.nonfinite) return fail(KM_EINVAL, "X contains NaN or Inf");

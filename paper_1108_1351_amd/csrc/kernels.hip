@@ -374,34 +374,28 @@ hipError_t stage_reset(PassState* st, hipStream_t s) {
 // A piece of E consecutive elements of a row as packed words (one element: FP32
 // bits, or BF16 bits in the low half), loaded as one vector of dwords (rows need
 // only start on a dword).
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4a4 __attribute__((ext_vector_type(4), aligned(4)));
 typedef uint32_t u32x2a4 __attribute__((ext_vector_type(2), aligned(4)));
 template <typename T, int E>
 struct Piece {
-  static constexpr int W = (E * (int)sizeof(T) + 3) / 4;
-  uint32_t w[W];
+  static constexpr int B = E * (int)sizeof(T);
+  using V = std::conditional_t<B == 16, u32x4, std::conditional_t<B == 8, u32x2, uint32_t>>;
+  V w;
   __device__ __forceinline__ void load(const T* __restrict__ p) {
-    if constexpr (E * sizeof(T) == 16) {
-      const u32x4a4 v = *reinterpret_cast<const u32x4a4*>(p);
-#pragma unroll
-      for (int u = 0; u < 4; ++u) w[u] = v[u];
-    } else if constexpr (E * sizeof(T) == 8) {
-      const u32x2a4 v = *reinterpret_cast<const u32x2a4*>(p);
-      w[0] = v[0];
-      w[1] = v[1];
-    } else if constexpr (E * sizeof(T) == 4) {
-      w[0] = *reinterpret_cast<const uint32_t*>(p);
-    } else {
-      w[0] = p[0];
-    }
+    if constexpr (B == 16) w = *reinterpret_cast<const u32x4a4*>(p);
+    else if constexpr (B == 8) w = *reinterpret_cast<const u32x2a4*>(p);
+    else if constexpr (B == 4) w = *reinterpret_cast<const uint32_t*>(p);
+    else w = p[0];
   }
-  __device__ __forceinline__ void zero() {
-#pragma unroll
-    for (int u = 0; u < W; ++u) w[u] = 0u;
-  }
+  __device__ __forceinline__ void zero() { w = V{}; }
   __device__ __forceinline__ float at(int e) const {
-    if constexpr (sizeof(T) == 4) return __uint_as_float(w[e]);
-    else return __uint_as_float((e & 1) ? w[e >> 1] & 0xffff0000u : w[e >> 1] << 16);
+    uint32_t u;
+    if constexpr (B >= 8) u = w[sizeof(T) == 4 ? e : e >> 1];
+    else u = w;
+    if constexpr (sizeof(T) == 4) return __uint_as_float(u);
+    else return __uint_as_float((e & 1) ? u & 0xffff0000u : u << 16);
   }
 };
 
@@ -519,15 +513,21 @@ hipError_t row_stats(const void* X, int dtype, int64_t rows, int32_t d, bool nor
   return hipGetLastError();
 }
 
-__global__ __launch_bounds__(256) void k_zero_i64(long long* __restrict__ p, int64_t count) {
+// Clears up to three arrays.
+__global__ __launch_bounds__(256) void k_zero_i64(long long* __restrict__ p, int64_t count,
+                                                  long long* __restrict__ q, int64_t qcount,
+                                                  long long* __restrict__ r, int64_t rcount) {
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < count; e += stride)
-    p[e] = 0;
+  const int64_t e0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  for (int64_t e = e0; e < count; e += stride) p[e] = 0;
+  for (int64_t e = e0; e < qcount; e += stride) q[e] = 0;
+  for (int64_t e = e0; e < rcount; e += stride) r[e] = 0;
 }
 
-hipError_t zero_i64(long long* p, int64_t count, hipStream_t s) {
+hipError_t zero_i64(long long* p, int64_t count, hipStream_t s, long long* q, int64_t qcount,
+                    long long* r, int64_t rcount) {
   const unsigned g = (unsigned)std::max<int64_t>(1, std::min<int64_t>((count + 255) / 256, 4096));
-  hipLaunchKernelGGL(k_zero_i64, dim3(g), dim3(256), 0, s, p, count);
+  hipLaunchKernelGGL(k_zero_i64, dim3(g), dim3(256), 0, s, p, count, q, qcount, r, rcount);
   return hipGetLastError();
 }
 
@@ -1139,21 +1139,101 @@ __global__ __launch_bounds__(256) void k_lab_scatter(const int32_t* __restrict__
   }
 }
 
-// As k_lab_scatter, for k <= kScatterLdsK: each range of S points of chunk b
+// Counts of all labels and their runs' first positions, for k <= 4096: every
+// block adds its chunk's histogram to tot, and the last one turns the totals
+// into the runs' starts and, in tot, the positions the scatter hands out (the
+// order of the points of one label does not matter, so a chunk needs no place of
+// its own).  Where a pass is short its launches are what it waits for: this
+// replaces five (per-chunk counts, three scan kernels, the starts), about 4.7 us
+// each.
+__global__ __launch_bounds__(256) void k_lab_total(const int32_t* __restrict__ labels, int64_t n,
+                                                   int k, int64_t chunk,
+                                                   unsigned long long* __restrict__ tot,
+                                                   long long* __restrict__ start,
+                                                   PassState* __restrict__ st,
+                                                   const int32_t* __restrict__ gate) {
+  if (gated(gate)) return;
+  extern __shared__ uint32_t h[];
+  __shared__ long long wtot[4];
+  __shared__ int last;
+  const int64_t i0 = (int64_t)blockIdx.x * chunk, i1 = min(n, i0 + chunk);
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  for (int j = t; j < k; j += 256) h[j] = 0u;
+  __syncthreads();
+  // labels four at a time per thread, so the loads overlap
+  for (int64_t i0t = i0 + t; i0t < i1; i0t += 1024) {
+    int jv[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int64_t i = i0t + 256 * u;
+      jv[u] = i < i1 ? labels[i] : -1;
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if ((unsigned)jv[u] < (unsigned)k) atomicAdd(&h[jv[u]], 1u);
+  }
+  __syncthreads();
+  for (int j = t; j < k; j += 256)
+    if (h[j]) atomicAdd(&tot[j], (unsigned long long)h[j]);
+  __syncthreads();
+  if (t == 0) {
+    __threadfence();
+    last = atomicAdd(&st->ticket, 1u) == gridDim.x - 1 ? 1 : 0;
+  }
+  __syncthreads();
+  if (!last) return;
+  __threadfence();
+  // thread t takes entries [t * kc, t * kc + kc), kc <= 16
+  const int kc = (k + 255) / 256;
+  long long v[16], sum = 0;
+#pragma unroll
+  for (int q = 0; q < 16; ++q) {
+    const int j = t * kc + q;
+    v[q] = q < kc && j < k ? ld_agent(reinterpret_cast<const long long*>(&tot[j])) : 0;
+    sum += v[q];
+  }
+  long long inc = sum;
+  for (int o = 1; o < 64; o <<= 1) {
+    const long long u = __shfl_up(inc, o);
+    if (lane >= o) inc += u;
+  }
+  if (lane == 63) wtot[wave] = inc;
+  __syncthreads();
+  long long pre = inc - sum;
+  for (int w = 0; w < wave; ++w) pre += wtot[w];
+#pragma unroll
+  for (int q = 0; q < 16; ++q) {
+    const int j = t * kc + q;
+    if (q < kc && j < k) {
+      start[j] = pre;
+      tot[j] = (unsigned long long)pre;
+      pre += v[q];
+    }
+  }
+  if (t == 0) {
+    start[k] = n;
+    st->ticket = 0u;
+  }
+}
+
+// As k_lab_scatter, for k <= 4096: each range of S points of chunk b
 // is first sorted by label in LDS (histogram, exclusive scan, placement), then
 // written out in that order, so the indices of one label go to consecutive
 // words of perm (runs of about S/k) instead of one scattered word per point.
 // LDS: base, lcnt, lst (k words each) and the sorted range (S words); S <= 2^14
-// and k <= 2^18 so a sorted entry packs (label << 14) | offset.
+// and k <= 2^18 so a sorted entry packs (label << 14) | offset.  CLAIM: a range's
+// places come from the label totals (k_lab_total) instead of its chunk's offsets.
+template <bool CLAIM>
 __global__ __launch_bounds__(256) void k_lab_scatter_lds(const int32_t* __restrict__ labels,
                                                          int64_t n, int k, int64_t chunk,
                                                          int64_t G, int S,
                                                          const long long* __restrict__ off,
+                                                         unsigned long long* __restrict__ tot,
                                                          uint32_t* __restrict__ perm,
                                                          const int32_t* __restrict__ gate) {
   if (gated(gate)) return;
   extern __shared__ uint32_t sm[];
-  uint32_t* base = sm;          // next position of label j in perm for this chunk
+  uint32_t* base = sm;          // the range's first position of label j in perm
   uint32_t* lcnt = sm + k;      // the range's count of label j
   uint32_t* lst = sm + 2 * k;   // its first place in the sorted range (after
                                 // placement: one past its last)
@@ -1162,7 +1242,8 @@ __global__ __launch_bounds__(256) void k_lab_scatter_lds(const int32_t* __restri
   const int64_t b = blockIdx.x, i0 = b * chunk, i1 = min(n, i0 + chunk);
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int kc = (k + 255) / 256;  // scan entries per thread
-  for (int j = t; j < k; j += 256) base[j] = (uint32_t)off[(int64_t)j * G + b];
+  if constexpr (!CLAIM)
+    for (int j = t; j < k; j += 256) base[j] = (uint32_t)off[(int64_t)j * G + b];
   for (int64_t s0 = i0; s0 < i1; s0 += S) {
     const int m = (int)min((int64_t)S, i1 - s0);
     for (int j = t; j < k; j += 256) lcnt[j] = 0u;
@@ -1200,6 +1281,8 @@ __global__ __launch_bounds__(256) void k_lab_scatter_lds(const int32_t* __restri
       if (j < k) {
         lst[j] = pre;
         pre += lcnt[j];
+        // the range's places in label j's run (its run lies below 2^32)
+        if (CLAIM && lcnt[j]) base[j] = (uint32_t)atomicAdd(&tot[j], (unsigned long long)lcnt[j]);
       }
     }
     __syncthreads();
@@ -1226,8 +1309,10 @@ __global__ __launch_bounds__(256) void k_lab_scatter_lds(const int32_t* __restri
       perm[(uint64_t)base[j] + (q - first)] = (uint32_t)(s0 + (int64_t)(w & 0x3fffu));
     }
     __syncthreads();
-    for (int j = t; j < k; j += 256) base[j] += lcnt[j];
-    __syncthreads();
+    if constexpr (!CLAIM) {
+      for (int j = t; j < k; j += 256) base[j] += lcnt[j];
+      __syncthreads();
+    }
   }
 }
 
@@ -1249,8 +1334,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k
     const uint32_t* __restrict__ perm, const long long* __restrict__ start,
     const double* __restrict__ c64, const PassState* __restrict__ st,
     const int32_t* __restrict__ gate, int update, long long* __restrict__ slots,
-    long long* __restrict__ jslots, int nslots) {
+    long long* __restrict__ jslots, int nslots, long long* __restrict__ tot) {
   if (gated(gate)) return;
+  // the label totals start the next pass at zero
+  if (tot && blockIdx.x == 0 && blockIdx.y == 0)
+    for (int q = threadIdx.x; q < k; q += 256) tot[q] = 0;
   const int G = 1 << glog;
   const int lane = threadIdx.x & 63, gi = lane >> glog, gl = lane & (G - 1);
   const int64_t group = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * (64 >> glog) + gi;
@@ -1313,6 +1401,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k
   for (int r = 0; r < R; ++r) pidx[r] = p0 + r < p1 ? perm[p0 + r] : 0u;
   for (int64_t p = p0; p < p1; p += R) {
     Piece<T, E> xw[R];
+    // the row indices have arrived (vmcnt 0; requested a batch ago): said here,
+    // where nothing else is in flight, or each of the conditional row loads
+    // below would wait for the one before it as well (28 % of the kernel)
+    __builtin_amdgcn_s_waitcnt(0x0f70);
 #pragma unroll
     for (int r = 0; r < R; ++r) {
       xw[r].zero();
@@ -5288,6 +5380,15 @@ static int scatter_range(int k) {
   return k >= 1 && S >= 4096 ? S : 0;
 }
 
+// The label sort hands out places from label totals (two launches) instead of
+// scanning per-chunk counts (six): while there are at most 512 chunks, the pass
+// waits for its launches (1e6 x 64, k = 256: 20 against 32 us); with more, the
+// chunks' atomics on the k totals cost more than the scans (5e7 points, k =
+// 1024, 3,100 chunks: 677 against 406 us).
+static bool sort_claims(const PassPlan& p, int k) {
+  return !p.fused && scatter_range(k) > 0 && p.sort_chunks <= 512;
+}
+
 PassPlan plan_pass(int64_t rows, int32_t d, int32_t k, int dtype, int precision,
                    size_t lds_limit, int cus) {
   PassPlan p{};
@@ -5474,28 +5575,40 @@ int row_glog(int32_t d, int E);
 static void sorted_update(const PassBufs& b, const PassPlan& p, bool update, const int32_t* gate,
                           hipStream_t s) {
   const int64_t G = p.sort_chunks, cn = (int64_t)b.k * G;
-  const size_t lds = b.k <= kHistLds ? (size_t)b.k * 4 : 0;
-  if (!lds) (void)zero_i64(b.scnt, cn, s);
-  hipLaunchKernelGGL(k_lab_count, dim3((unsigned)G), dim3(256), lds, s, (const int32_t*)b.labels,
-                     b.n, b.k, p.sort_chunk, G, b.scnt, gate);
-  const int64_t tiles = (cn + 2047) / 2048;
-  hipLaunchKernelGGL(k_scan_tiles, dim3((unsigned)tiles), dim3(256), 0, s, b.scnt, cn, b.stot,
-                     gate);
-  hipLaunchKernelGGL(k_scan_excl, dim3(1), dim3(256), 0, s, reinterpret_cast<int64_t*>(b.stot),
-                     tiles);
-  hipLaunchKernelGGL(k_scan_add, dim3((unsigned)((cn + 255) / 256)), dim3(256), 0, s, b.scnt, cn,
-                     (const long long*)b.stot, gate);
-  hipLaunchKernelGGL(k_run_starts, dim3((unsigned)((b.k + 256) / 256)), dim3(256), 0, s,
-                     (const long long*)b.scnt, b.k, G, b.n, b.rstart, gate);
   const int S = scatter_range(b.k);
-  if (S > 0)
-    hipLaunchKernelGGL(k_lab_scatter_lds, dim3((unsigned)G), dim3(256),
-                       (size_t)(3 * b.k + S) * 4, s, (const int32_t*)b.labels, b.n, b.k,
-                       p.sort_chunk, G, S, (const long long*)b.scnt, b.perm, gate);
-  else
-    hipLaunchKernelGGL(k_lab_scatter, dim3((unsigned)G), dim3(256), lds, s,
-                       (const int32_t*)b.labels, b.n, b.k, p.sort_chunk, G, b.scnt, b.perm,
+  const bool claim = sort_claims(p, b.k);
+  if (claim) {
+    unsigned long long* tot = reinterpret_cast<unsigned long long*>(b.scnt);
+    hipLaunchKernelGGL(k_lab_total, dim3((unsigned)G), dim3(256), (size_t)b.k * 4, s,
+                       (const int32_t*)b.labels, b.n, b.k, p.sort_chunk, tot, b.rstart, b.st,
                        gate);
+    hipLaunchKernelGGL(k_lab_scatter_lds<true>, dim3((unsigned)G), dim3(256),
+                       (size_t)(3 * b.k + S) * 4, s, (const int32_t*)b.labels, b.n, b.k,
+                       p.sort_chunk, G, S, (const long long*)nullptr, tot, b.perm, gate);
+  } else {
+    const size_t lds = b.k <= kHistLds ? (size_t)b.k * 4 : 0;
+    if (!lds) (void)zero_i64(b.scnt, cn, s);
+    hipLaunchKernelGGL(k_lab_count, dim3((unsigned)G), dim3(256), lds, s,
+                       (const int32_t*)b.labels, b.n, b.k, p.sort_chunk, G, b.scnt, gate);
+    const int64_t tiles = (cn + 2047) / 2048;
+    hipLaunchKernelGGL(k_scan_tiles, dim3((unsigned)tiles), dim3(256), 0, s, b.scnt, cn, b.stot,
+                       gate);
+    hipLaunchKernelGGL(k_scan_excl, dim3(1), dim3(256), 0, s, reinterpret_cast<int64_t*>(b.stot),
+                       tiles);
+    hipLaunchKernelGGL(k_scan_add, dim3((unsigned)((cn + 255) / 256)), dim3(256), 0, s, b.scnt,
+                       cn, (const long long*)b.stot, gate);
+    hipLaunchKernelGGL(k_run_starts, dim3((unsigned)((b.k + 256) / 256)), dim3(256), 0, s,
+                       (const long long*)b.scnt, b.k, G, b.n, b.rstart, gate);
+    if (S > 0)
+      hipLaunchKernelGGL(k_lab_scatter_lds<false>, dim3((unsigned)G), dim3(256),
+                         (size_t)(3 * b.k + S) * 4, s, (const int32_t*)b.labels, b.n, b.k,
+                         p.sort_chunk, G, S, (const long long*)b.scnt,
+                         (unsigned long long*)nullptr, b.perm, gate);
+    else
+      hipLaunchKernelGGL(k_lab_scatter, dim3((unsigned)G), dim3(256), lds, s,
+                         (const int32_t*)b.labels, b.n, b.k, p.sort_chunk, G, b.scnt, b.perm,
+                         gate);
+  }
   const int E = row_vec(b.dtype, b.d, b.X), glog = row_glog(b.d, E);
   const int64_t groups = (b.n + p.pg - 1) / p.pg;
   const int64_t waves = (groups + (64 >> glog) - 1) / (64 >> glog);
@@ -5505,7 +5618,7 @@ static void sorted_update(const PassBufs& b, const PassPlan& p, bool update, con
     hipLaunchKernelGGL(kern, grid, dim3(256), 0, s, x, b.n, b.d, b.k, glog, p.pg,
                        (const uint32_t*)b.perm, (const long long*)b.rstart,
                        (const double*)b.c64, (const PassState*)b.st, gate, update ? 1 : 0,
-                       b.slots, b.jslots, plan_slots(p));
+                       b.slots, b.jslots, plan_slots(p), claim ? b.scnt : nullptr);
   };
   const bool tail = b.d % E != 0;
   visit_vec(b.dtype, E, [&](auto e) {
@@ -5739,7 +5852,8 @@ hipError_t fill_uniform(void* p, int kind, int64_t count, uint64_t seed, hipStre
 }
 
 hipError_t zero_sums(const PassBufs& b, const PassPlan& p, hipStream_t s) {
-  return zero_i64(b.slots, (int64_t)plan_slots(p) * b.k * (b.d + 1), s);
+  return zero_i64(b.slots, (int64_t)plan_slots(p) * b.k * (b.d + 1), s, b.jslots, kSlots * 2,
+                  b.scnt, sort_claims(p, b.k) ? b.k : 0);
 }
 
 hipError_t prep_copy(const PassBufs& b, const PassPlan& p, hipStream_t s) {

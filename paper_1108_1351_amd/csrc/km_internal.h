@@ -135,7 +135,8 @@ hipError_t centers_from_rows(const void* X, int64_t nrows, int dtype, int32_t d,
 hipError_t stage_reset(PassState* st, hipStream_t s);
 hipError_t row_stats(const void* X, int dtype, int64_t rows, int32_t d, bool norms,
                      PassState* st, hipStream_t s);
-hipError_t zero_i64(long long* p, int64_t count, hipStream_t s);
+hipError_t zero_i64(long long* p, int64_t count, hipStream_t s, long long* q = nullptr,
+                    int64_t qcount = 0, long long* r = nullptr, int64_t rcount = 0);
 // cb16lo: when given, -2c is kept as hi + lo (the rest rounded to BF16 again);
 // rows: padded rows of the copy (0: bf16_rows(k))
 hipError_t prep_bf16(const double* c64, int32_t k, int32_t d, int kd16, PassState* st,
@@ -154,7 +155,8 @@ struct PassBufs {
   long long* slots;    // [kSlots][k][d+1] exact cluster sums (counts last); zero between passes
   long long* jslots;   // [kSlots][2] J of the sorted update as limbs of 2^-FJ, 2^(40-FJ); zeroed
   uint32_t* perm;      // [n] point indices in label order (sorted update)
-  long long* scnt;     // [k * sort_chunks] label counts per chunk, then their offsets
+  long long* scnt;     // [k * sort_chunks] label counts per chunk, then their offsets; for
+                       //   k <= 4096 the first k: label totals, then positions, 0 between passes
   long long* stot;     // [scan tiles + 1] tile totals of the offset scan
   long long* rstart;   // [k + 1] first position of every label's run
   uint16_t* cb16;      // bf16_rows(k) x ks*16 BF16 (-2 c) of the BF16 screen, tiled (cb16_at)
@@ -234,7 +236,8 @@ hipError_t fill_uniform(void* p, int kind, int64_t count, uint64_t seed, hipStre
 
 PassPlan plan_pass(int64_t rows, int32_t d, int32_t k, int dtype, int precision,
                    size_t lds_limit, int cus);
-// Clears the slot rows the plan's passes add into, and writes its BF16 center copy.
+// Clears the sums the plan's passes add into (slot rows, J limbs, label totals),
+// and writes its BF16 center copy.
 hipError_t zero_sums(const PassBufs& b, const PassPlan& p, hipStream_t s);
 hipError_t prep_copy(const PassBufs& b, const PassPlan& p, hipStream_t s);
 hipError_t lloyd_pass(const PassBufs& b, const PassPlan& p, bool update, hipStream_t s);
