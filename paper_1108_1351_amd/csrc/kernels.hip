@@ -1371,16 +1371,36 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k
   long long cnt = 0;
   const int slot = (int)(group & (nslots - 1));
   long long* srow = slots + (int64_t)slot * k * (d + 1);
+  // A run's sums go out with a group's lanes on consecutive words, through LDS: a
+  // lane's own E words side by side make each atomic instruction touch E times
+  // the cache lines, and the atomics are what a pass of few points per run waits
+  // for (1e6 x 64, k = 256: 106 us so, 54 us now, with the J limbs in two atomics
+  // a block instead of two a group; 2e5 x 300, k = 40: 127 and 69 us).
+  __shared__ long long stage[E > 1 ? 256 * E : 1];
+  long long* sg = stage + (E > 1 ? ((threadIdx.x >> 6) * 64 + gi * G) * E : 0);
+  const int ybase = (int)blockIdx.y * G * E;
   auto flush = [&]() {
     if (cnt == 0) return;
     if (update) {
       long long* row = srow + (int64_t)j * (d + 1);
+      if constexpr (E > 1) {
+#pragma unroll
+        for (int e = 0; e < E; ++e)
+          if (act && (!TAIL || e >= skip)) sg[col - ybase + e] = (long long)acc[e];
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+      }
 #pragma unroll
       for (int e = 0; e < E; ++e) {
-        const long long v = (long long)acc[e];
-        if (act && v && (!TAIL || e >= skip))
-          atomicAdd(reinterpret_cast<unsigned long long*>(&row[col + e]), (unsigned long long)v);
+        const int t = ybase + e * G + gl;
+        const long long v = E > 1 ? sg[e * G + gl] : (long long)acc[0];
+        if (t < d && v)
+          atomicAdd(reinterpret_cast<unsigned long long*>(&row[t]), (unsigned long long)v);
         acc[e] = 0.0;
+      }
+      if constexpr (E > 1) {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
       }
       if (blockIdx.y == 0 && gl == 0)
         atomicAdd(reinterpret_cast<unsigned long long*>(&row[d]), (unsigned long long)cnt);
@@ -1443,15 +1463,28 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k
   }
   flush();
   long long l0 = (long long)j0, l1 = (long long)j1;
-  for (int o = G >> 1; o > 0; o >>= 1) {
+  // the block's limbs in two atomics (below 2^53 each over its lanes' parts)
+  l1 += l0 >> 40;
+  l0 &= (1ll << 40) - 1;
+  for (int o = 32; o > 0; o >>= 1) {
     l0 += __shfl_xor(l0, o);
     l1 += __shfl_xor(l1, o);
   }
-  if (gl == 0 && (l0 | l1)) {
+  __shared__ long long wl[2][4];
+  if (lane == 0) {
+    wl[0][threadIdx.x >> 6] = l0;
+    wl[1][threadIdx.x >> 6] = l1;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    l0 = (wl[0][0] + wl[0][1]) + (wl[0][2] + wl[0][3]);
+    l1 = (wl[1][0] + wl[1][1]) + (wl[1][2] + wl[1][3]);
     l1 += l0 >> 40;
     l0 &= (1ll << 40) - 1;
-    atomicAdd(reinterpret_cast<unsigned long long*>(&jslots[2 * slot]), (unsigned long long)l0);
-    atomicAdd(reinterpret_cast<unsigned long long*>(&jslots[2 * slot + 1]), (unsigned long long)l1);
+    const int js = 2 * (int)(blockIdx.x % kSlots);
+    if (l0) atomicAdd(reinterpret_cast<unsigned long long*>(&jslots[js]), (unsigned long long)l0);
+    if (l1)
+      atomicAdd(reinterpret_cast<unsigned long long*>(&jslots[js + 1]), (unsigned long long)l1);
   }
 }
 
@@ -5048,12 +5081,11 @@ __global__ __launch_bounds__(1024, 8) void k_batch_sums(const BatchHead* __restr
     __syncthreads();
     unsigned long long* row = reinterpret_cast<unsigned long long*>(
         b.slots + (int64_t)(pb & (b.nslots - 1)) * k * ws + (int64_t)c0 * ws);
-    for (int e = threadIdx.x; e < cn * w; e += 1024) {
-      const unsigned long long v = S[e];
-      if (!v) continue;
-      const int c = e / w, q = e - c * w;
-      const int p = q / np, t = q == 8 * np ? d : 8 * (q - p * np) + p;
-      atomicAdd(&row[(int64_t)c * ws + t], v);
+    // in the order of the slot row: a wave's atomics touch whole cache lines
+    for (int e = threadIdx.x; e < cn * ws; e += 1024) {
+      const int c = e / ws, t = e - c * ws;
+      const unsigned long long v = S[c * w + (t == d ? 8 * np : (t & 7) * np + (t >> 3))];
+      if (v) atomicAdd(&row[e], v);
     }
     __syncthreads();
   }

@@ -449,10 +449,12 @@ class Engine {
                      : 0;
       sunits += b.sunits;
       {
-        // one slot row per writer (tile flushes or point ranges), at most kSlots
+        // one slot row per writer (tile flushes or point ranges), at most 8: more
+        // rows cost the finalize more than they save the writers (55 against
+        // 39 us a pass on 30 problems of 32 and 128 dims, the sums unchanged)
         const int64_t writers = b.sunits ? (b.n + spts - 1) / spts : b.units;
         int ns = 1;
-        while (ns < kSlots && ns < writers) ns <<= 1;
+        while (ns < 8 && ns < writers) ns <<= 1;
         b.nslots = ns;
       }
       units[g] += b.units;
