@@ -74,7 +74,7 @@ __device__ __forceinline__ uint16_t f32_to_bf16(float f) {
 // Sampling: the r smallest keys among `count` candidates (indices 0..count-1,
 // or the indices listed in idx_arr), by 12-bit digits from the top.
 // ============================================================================
-__global__ void k_sel_init(SelState* st, int64_t r, int64_t count) {
+__device__ __forceinline__ void sel_init(SelState* st, int64_t r, int64_t count) {
   st->prefix = 0;
   st->bits = 0;
   st->need = r;
@@ -82,10 +82,14 @@ __global__ void k_sel_init(SelState* st, int64_t r, int64_t count) {
   st->done = r >= count ? 1 : 0;
 }
 
-__global__ __launch_bounds__(256) void k_sel_hist(const int64_t* __restrict__ idx_arr,
-                                                  int64_t count, uint64_t seed,
-                                                  const SelState* __restrict__ st,
-                                                  unsigned long long* __restrict__ hist) {
+__global__ void k_sel_init(SelState* st, int64_t r, int64_t count) {
+  sel_init(st, r, count);
+}
+
+__device__ __forceinline__ void sel_hist(const int64_t* __restrict__ idx_arr, int64_t count,
+                                         uint64_t seed, const SelState* __restrict__ st,
+                                         unsigned long long* __restrict__ hist, unsigned bx,
+                                         unsigned gx) {
   if (st->done) return;
   __shared__ uint32_t h[kSelBins];
   const int bits = st->bits;
@@ -95,8 +99,8 @@ __global__ __launch_bounds__(256) void k_sel_hist(const int64_t* __restrict__ id
   const uint64_t mask = (1ull << next) - 1ull;
   for (int b = threadIdx.x; b < kSelBins; b += blockDim.x) h[b] = 0;
   __syncthreads();
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < count; e += stride) {
+  const int64_t stride = (int64_t)gx * blockDim.x;
+  for (int64_t e = (int64_t)bx * blockDim.x + threadIdx.x; e < count; e += stride) {
     int64_t i = idx_arr ? idx_arr[e] : e;
     uint64_t key = split_key(seed, i);
     if (bits > 0 && (key >> (64 - bits)) != prefix) continue;
@@ -107,9 +111,16 @@ __global__ __launch_bounds__(256) void k_sel_hist(const int64_t* __restrict__ id
     if (h[b]) atomicAdd(&hist[b], (unsigned long long)h[b]);
 }
 
-// One block of 256 threads: choose the bin holding the need-th smallest key.
-__global__ __launch_bounds__(256) void k_sel_pick(SelState* __restrict__ st,
+__global__ __launch_bounds__(256) void k_sel_hist(const int64_t* __restrict__ idx_arr,
+                                                  int64_t count, uint64_t seed,
+                                                  const SelState* __restrict__ st,
                                                   unsigned long long* __restrict__ hist) {
+  sel_hist(idx_arr, count, seed, st, hist, blockIdx.x, gridDim.x);
+}
+
+// One block of 256 threads: choose the bin holding the need-th smallest key.
+__device__ __forceinline__ void sel_pick(SelState* __restrict__ st,
+                                         unsigned long long* __restrict__ hist) {
   if (st->done) return;
   constexpr int per = kSelBins / 256;
   __shared__ unsigned long long part[256];
@@ -137,16 +148,20 @@ __global__ __launch_bounds__(256) void k_sel_pick(SelState* __restrict__ st,
   for (int q = 0; q < per; ++q) hist[tid * per + q] = 0ull;
 }
 
+__global__ __launch_bounds__(256) void k_sel_pick(SelState* __restrict__ st,
+                                                  unsigned long long* __restrict__ hist) {
+  sel_pick(st, hist);
+}
+
 __device__ __forceinline__ bool sel_take(uint64_t key, const SelState& st) {
   return st.bits == 0 ? true : ((key >> (64 - st.bits)) <= st.prefix);
 }
 
-__global__ __launch_bounds__(256) void k_sel_count(const int64_t* __restrict__ idx_arr,
-                                                   int64_t count, uint64_t seed,
-                                                   const SelState* __restrict__ st_,
-                                                   int64_t* __restrict__ blk) {
+__device__ __forceinline__ void sel_count(const int64_t* __restrict__ idx_arr, int64_t count,
+                                          uint64_t seed, const SelState* __restrict__ st_,
+                                          int64_t* __restrict__ blk, unsigned bx) {
   const SelState st = *st_;
-  const int64_t base = (int64_t)blockIdx.x * kSelChunk;
+  const int64_t base = (int64_t)bx * kSelChunk;
   const int64_t end = min(base + kSelChunk, count);
   int c = 0;
   for (int64_t e = base + threadIdx.x; e < end; e += blockDim.x) {
@@ -160,11 +175,18 @@ __global__ __launch_bounds__(256) void k_sel_count(const int64_t* __restrict__ i
     if ((int)threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
     __syncthreads();
   }
-  if (threadIdx.x == 0) blk[blockIdx.x] = red[0];
+  if (threadIdx.x == 0) blk[bx] = red[0];
+}
+
+__global__ __launch_bounds__(256) void k_sel_count(const int64_t* __restrict__ idx_arr,
+                                                   int64_t count, uint64_t seed,
+                                                   const SelState* __restrict__ st_,
+                                                   int64_t* __restrict__ blk) {
+  sel_count(idx_arr, count, seed, st_, blk, blockIdx.x);
 }
 
 // Exclusive scan of a[0..nb) in place; a[nb] receives the total.  One block of 256.
-__global__ __launch_bounds__(256) void k_scan_excl(int64_t* __restrict__ a, int64_t nb) {
+__device__ __forceinline__ void scan_excl(int64_t* __restrict__ a, int64_t nb) {
   __shared__ int64_t part[256];
   const int tid = threadIdx.x;
   const int64_t per = (nb + 255) / 256;
@@ -191,16 +213,19 @@ __global__ __launch_bounds__(256) void k_scan_excl(int64_t* __restrict__ a, int6
   }
 }
 
+__global__ __launch_bounds__(256) void k_scan_excl(int64_t* __restrict__ a, int64_t nb) {
+  scan_excl(a, nb);
+}
+
 // Ordered compaction: selected indices of each chunk, in index order.  256 threads.
-__global__ __launch_bounds__(256) void k_sel_write(const int64_t* __restrict__ idx_arr,
-                                                   int64_t count, uint64_t seed,
-                                                   const SelState* __restrict__ st_,
-                                                   const int64_t* __restrict__ blk, int64_t r,
-                                                   int64_t* __restrict__ out) {
+__device__ __forceinline__ void sel_write(const int64_t* __restrict__ idx_arr, int64_t count,
+                                          uint64_t seed, const SelState* __restrict__ st_,
+                                          const int64_t* __restrict__ blk, int64_t r,
+                                          int64_t* __restrict__ out, unsigned bx) {
   const SelState st = *st_;
-  const int64_t base = (int64_t)blockIdx.x * kSelChunk;
+  const int64_t base = (int64_t)bx * kSelChunk;
   const int64_t end = min(base + kSelChunk, count);
-  int64_t off = blk[blockIdx.x];
+  int64_t off = blk[bx];
   __shared__ int wtot[4];
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
   for (int64_t e0 = base; e0 < end; e0 += 256) {
@@ -225,11 +250,19 @@ __global__ __launch_bounds__(256) void k_sel_write(const int64_t* __restrict__ i
   }
 }
 
+__global__ __launch_bounds__(256) void k_sel_write(const int64_t* __restrict__ idx_arr,
+                                                   int64_t count, uint64_t seed,
+                                                   const SelState* __restrict__ st_,
+                                                   const int64_t* __restrict__ blk, int64_t r,
+                                                   int64_t* __restrict__ out) {
+  sel_write(idx_arr, count, seed, st_, blk, r, out, blockIdx.x);
+}
+
 // out[rank of key] = sel[e]: the selected indices ordered by key (keys are distinct).
-__global__ __launch_bounds__(256) void k_rank(const int64_t* __restrict__ sel, int32_t k,
-                                              uint64_t seed, int64_t* __restrict__ out) {
+__device__ __forceinline__ void rank_keys(const int64_t* __restrict__ sel, int32_t k,
+                                          uint64_t seed, int64_t* __restrict__ out, unsigned bx) {
   __shared__ uint64_t kk[256];
-  const int e = blockIdx.x * blockDim.x + threadIdx.x;
+  const int e = bx * blockDim.x + threadIdx.x;
   const uint64_t mine = e < k ? split_key(seed, sel[e]) : 0ull;
   int rank = 0;
   for (int c0 = 0; c0 < k; c0 += 256) {
@@ -241,6 +274,11 @@ __global__ __launch_bounds__(256) void k_rank(const int64_t* __restrict__ sel, i
       for (int q = 0; q < lim; ++q) rank += kk[q] < mine ? 1 : 0;
   }
   if (e < k && rank < k) out[rank] = sel[e];
+}
+
+__global__ __launch_bounds__(256) void k_rank(const int64_t* __restrict__ sel, int32_t k,
+                                              uint64_t seed, int64_t* __restrict__ out) {
+  rank_keys(sel, k, seed, out, blockIdx.x);
 }
 
 hipError_t sel_run(const int64_t* idx_arr, int64_t count, uint64_t seed, int64_t r,
@@ -277,13 +315,31 @@ __device__ __forceinline__ int64_t clamp_row(int64_t i, int64_t nrows) {
 }
 
 template <typename T>
+__device__ __forceinline__ void gather_body(const T* __restrict__ X, int64_t nrows, int32_t d,
+                                            const int64_t* __restrict__ idx, int64_t m,
+                                            T* __restrict__ out, unsigned bx, unsigned gx) {
+  const int64_t total = m * d, stride = (int64_t)gx * blockDim.x;
+  for (int64_t e = (int64_t)bx * blockDim.x + threadIdx.x; e < total; e += stride) {
+    const int64_t r = e / d, t = e - r * d;
+    out[e] = X[clamp_row(idx[r], nrows) * d + t];
+  }
+}
+
+template <typename T>
 __global__ __launch_bounds__(256) void k_gather(const T* __restrict__ X, int64_t nrows,
                                                 int32_t d, const int64_t* __restrict__ idx,
                                                 int64_t m, T* __restrict__ out) {
-  const int64_t total = m * d, stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += stride) {
-    const int64_t r = e / d, t = e - r * d;
-    out[e] = X[clamp_row(idx[r], nrows) * d + t];
+  gather_body<T>(X, nrows, d, idx, m, out, blockIdx.x, gridDim.x);
+}
+
+template <typename T>
+__device__ __forceinline__ void centers_body(const T* __restrict__ X, int64_t nrows, int32_t d,
+                                             const int64_t* __restrict__ idx, int32_t k,
+                                             double* __restrict__ c64, unsigned bx, unsigned gx) {
+  const int64_t total = (int64_t)k * d, stride = (int64_t)gx * blockDim.x;
+  for (int64_t e = (int64_t)bx * blockDim.x + threadIdx.x; e < total; e += stride) {
+    const int64_t j = e / d, t = e - j * d;
+    c64[e] = (double)widen<T>(X[clamp_row(idx[j], nrows) * d + t]);
   }
 }
 
@@ -292,11 +348,7 @@ __global__ __launch_bounds__(256) void k_centers_from_rows(const T* __restrict__
                                                            int64_t nrows, int32_t d,
                                                            const int64_t* __restrict__ idx,
                                                            int32_t k, double* __restrict__ c64) {
-  const int64_t total = (int64_t)k * d, stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += stride) {
-    const int64_t j = e / d, t = e - j * d;
-    c64[e] = (double)widen<T>(X[clamp_row(idx[j], nrows) * d + t]);
-  }
+  centers_body<T>(X, nrows, d, idx, k, c64, blockIdx.x, gridDim.x);
 }
 
 hipError_t gather_rows(const void* X, int64_t nrows, int dtype, int32_t d, const int64_t* idx,
@@ -325,7 +377,7 @@ hipError_t centers_from_rows(const void* X, int64_t nrows, int dtype, int32_t d,
   return hipGetLastError();
 }
 
-__global__ void k_stage_reset(PassState* st) {
+__device__ __forceinline__ void reset_state(PassState* st) {
   st->maxabs_bits = 0u;
   st->xn2max_bits = 0u;
   st->qcount = 0u;
@@ -333,6 +385,10 @@ __global__ void k_stage_reset(PassState* st) {
   st->dcn_bits = 0u;
   st->done = 0;
   st->reseed_j = -1;
+}
+
+__global__ void k_stage_reset(PassState* st) {
+  reset_state(st);
 }
 
 // Rounding error of one BF16 entry of the screen's center copy: the stored
@@ -425,15 +481,15 @@ int row_glog(int32_t d, int E) {
 // Both maxima are upper bounds wherever they are used, so a piece that overlaps
 // its neighbour only has to leave the shared elements out of the norm.
 template <typename T, int E>
-__global__ __launch_bounds__(256) void k_row_stats(const T* __restrict__ X, int64_t rows, int d,
-                                                   int glog, int norms,
-                                                   PassState* __restrict__ st) {
+__device__ __forceinline__ void row_stats_body(const T* __restrict__ X, int64_t rows, int d,
+                                               int glog, int norms, PassState* __restrict__ st,
+                                               unsigned bx, unsigned gx) {
   constexpr int R = 4;
   const int G = 1 << glog;
   const int lane = threadIdx.x & 63, gi = lane >> glog, gl = lane & (G - 1);
   const int rpw = 64 >> glog;  // rows of a wave's step
-  const int64_t wave = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  const int64_t step = (int64_t)gridDim.x * 4 * rpw * R;
+  const int64_t wave = (int64_t)bx * 4 + (threadIdx.x >> 6);
+  const int64_t step = (int64_t)gx * 4 * rpw * R;
   uint32_t mx = 0u;
   float xn2 = 0.f;
   for (int64_t base = wave * rpw * R; base < rows; base += step) {
@@ -484,6 +540,13 @@ __global__ __launch_bounds__(256) void k_row_stats(const T* __restrict__ X, int6
   }
 }
 
+template <typename T, int E>
+__global__ __launch_bounds__(256) void k_row_stats(const T* __restrict__ X, int64_t rows, int d,
+                                                   int glog, int norms,
+                                                   PassState* __restrict__ st) {
+  row_stats_body<T, E>(X, rows, d, glog, norms, st, blockIdx.x, gridDim.x);
+}
+
 // Calls f with the piece size as a constant.
 template <typename F>
 static void visit_vec(int dtype, int E, F&& f) {
@@ -532,11 +595,10 @@ hipError_t zero_i64(long long* p, int64_t count, hipStream_t s, long long* q, in
 }
 
 // FP32 working copy of the centers, ||c||^2 (FP32) and ||c|| (FP64).  One wave per center.
-__global__ __launch_bounds__(64) void k_prep_centers(const double* __restrict__ c64, int32_t k,
-                                                     int32_t d, float* __restrict__ cw,
-                                                     float* __restrict__ cn,
-                                                     double* __restrict__ cnorm) {
-  const int j = blockIdx.x, lane = threadIdx.x;
+__device__ __forceinline__ void prep_center(const double* __restrict__ c64, int32_t k, int32_t d,
+                                            float* __restrict__ cw, float* __restrict__ cn,
+                                            double* __restrict__ cnorm, int j) {
+  const int lane = threadIdx.x;
   double acc = 0.0;
   for (int t = lane; t < d; t += 64) {
     const double c = c64[(int64_t)j * d + t];
@@ -548,6 +610,13 @@ __global__ __launch_bounds__(64) void k_prep_centers(const double* __restrict__ 
     cn[j] = (float)acc;
     cnorm[j] = sqrt(acc);
   }
+}
+
+__global__ __launch_bounds__(64) void k_prep_centers(const double* __restrict__ c64, int32_t k,
+                                                     int32_t d, float* __restrict__ cw,
+                                                     float* __restrict__ cn,
+                                                     double* __restrict__ cnorm) {
+  prep_center(c64, k, d, cw, cn, cnorm, blockIdx.x);
 }
 
 hipError_t prep_centers(const double* c64, int32_t k, int32_t d, float* cw, float* cn,
@@ -563,11 +632,10 @@ __device__ __forceinline__ int ceil_log2(int64_t v) {
   return b;
 }
 
-__global__ __launch_bounds__(256) void k_stage_begin(PassState* __restrict__ st,
-                                                     int32_t max_iter, double tol, int64_t rows,
-                                                     const double* __restrict__ cnorm,
-                                                     int32_t k, int32_t d_, int64_t pg,
-                                                     int reseed) {
+__device__ __forceinline__ void begin_state(PassState* __restrict__ st, int32_t max_iter,
+                                            double tol, int64_t rows,
+                                            const double* __restrict__ cnorm, int32_t k,
+                                            int32_t d_, int64_t pg, int reseed) {
   __shared__ double red[256];
   double m = 0.0;
   for (int j = threadIdx.x; j < k; j += 256) m = fmax(m, cnorm[j]);
@@ -634,6 +702,14 @@ __global__ __launch_bounds__(256) void k_stage_begin(PassState* __restrict__ st,
     st->reseed = reseed;
     st->reseed_j = -1;
   }
+}
+
+__global__ __launch_bounds__(256) void k_stage_begin(PassState* __restrict__ st,
+                                                     int32_t max_iter, double tol, int64_t rows,
+                                                     const double* __restrict__ cnorm,
+                                                     int32_t k, int32_t d_, int64_t pg,
+                                                     int reseed) {
+  begin_state(st, max_iter, tol, rows, cnorm, k, d_, pg, reseed);
 }
 
 hipError_t stage_begin(PassState* st, int32_t max_iter, double tol, int64_t rows,
@@ -5147,12 +5223,12 @@ __global__ __launch_bounds__(256) void k_fill_uniform(void* __restrict__ p, int6
 // BF16 copy of -2 c (dims padded with zeros to kd16) and ||c||^2 + B; the
 // largest rounding-error norm of a row becomes st->dcn (the last block
 // publishes it).
-__global__ __launch_bounds__(64) void k_prep_bf16(const double* __restrict__ c64, int k, int d,
-                                                  int kd16, PassState* __restrict__ st,
-                                                  uint16_t* __restrict__ cb16,
-                                                  float* __restrict__ cnB,
-                                                  uint16_t* __restrict__ cb16lo) {
-  const int j = blockIdx.x, lane = threadIdx.x;
+__device__ __forceinline__ void prep_bf16_row(const double* __restrict__ c64, int k, int d,
+                                              int kd16, PassState* __restrict__ st,
+                                              uint16_t* __restrict__ cb16, float* __restrict__ cnB,
+                                              uint16_t* __restrict__ cb16lo, int j,
+                                              unsigned rows) {
+  const int lane = threadIdx.x;
   double acc = 0.0, e2 = 0.0;
   for (int t = lane; t < kd16; t += 64) {
     const double c = (t < d && j < k) ? c64[(int64_t)j * d + t] : 0.0;
@@ -5178,7 +5254,7 @@ __global__ __launch_bounds__(64) void k_prep_bf16(const double* __restrict__ c64
     cnB[j] = j < k ? (float)(acc + (double)st->B) : INFINITY;
     dcn_max(st, e2);
     __threadfence();
-    if (atomicAdd(&st->ticket, 1u) == gridDim.x - 1) {
+    if (atomicAdd(&st->ticket, 1u) == rows - 1) {
       __threadfence();
       dcn_publish(st);
       st->ticket = 0u;
@@ -5186,11 +5262,183 @@ __global__ __launch_bounds__(64) void k_prep_bf16(const double* __restrict__ c64
   }
 }
 
+__global__ __launch_bounds__(64) void k_prep_bf16(const double* __restrict__ c64, int k, int d,
+                                                  int kd16, PassState* __restrict__ st,
+                                                  uint16_t* __restrict__ cb16,
+                                                  float* __restrict__ cnB,
+                                                  uint16_t* __restrict__ cb16lo) {
+  prep_bf16_row(c64, k, d, kd16, st, cb16, cnB, cb16lo, blockIdx.x, gridDim.x);
+}
+
 hipError_t prep_bf16(const double* c64, int32_t k, int32_t d, int kd16, PassState* st,
                      uint16_t* cb16, float* cnB, hipStream_t s, uint16_t* cb16lo, int64_t rows) {
   hipLaunchKernelGGL(k_prep_bf16, dim3((unsigned)(rows ? rows : bf16_rows(k))), dim3(64), 0, s, c64, k, d, kd16,
                      st, cb16, cnB, cb16lo);
   return hipGetLastError();
+}
+
+// ----------------------------------------------------------------------------
+// Starts of many problems in shared launches: sampling, initial centers, subset
+// copies and stage set-ups of all problems admitted together, blockIdx.y the
+// problem.  A start is about 40 launches of 2 to 3 us each, whatever the
+// problem's size; one problem at a time, the starts of 30 small problems took 4
+// ms of a 16 ms batch, and as much of the host.
+// ----------------------------------------------------------------------------
+// which: 0 the subset of all points, 1 the initial centers of the subset
+__global__ __launch_bounds__(256) void k_many_sel_init(const StartInst* __restrict__ v,
+                                                       int which) {
+  const StartInst& b = v[blockIdx.y];
+  if (threadIdx.x == 0) sel_init(b.sel, which ? b.k : b.m, which ? b.m : b.n);
+  if (!which)
+    for (int e = threadIdx.x; e < kSelBins; e += 256) b.hist[e] = 0ull;
+}
+__global__ __launch_bounds__(256) void k_many_sel_hist(const StartInst* __restrict__ v,
+                                                       int which) {
+  const StartInst& b = v[blockIdx.y];
+  const int64_t count = which ? b.m : b.n;
+  if ((int64_t)blockIdx.x * 256 >= count) return;
+  sel_hist(which ? b.sub : nullptr, count, b.seed, b.sel, b.hist, blockIdx.x, gridDim.x);
+}
+__global__ __launch_bounds__(256) void k_many_sel_pick(const StartInst* __restrict__ v) {
+  sel_pick(v[blockIdx.y].sel, v[blockIdx.y].hist);
+}
+__global__ __launch_bounds__(256) void k_many_sel_count(const StartInst* __restrict__ v,
+                                                        int which) {
+  const StartInst& b = v[blockIdx.y];
+  const int64_t count = which ? b.m : b.n, nb = (count + kSelChunk - 1) / kSelChunk;
+  for (int64_t c = blockIdx.x; c < nb; c += gridDim.x) {
+    sel_count(which ? b.sub : nullptr, count, b.seed, b.sel, b.blk, (unsigned)c);
+    __syncthreads();
+  }
+}
+__global__ __launch_bounds__(256) void k_many_sel_scan(const StartInst* __restrict__ v,
+                                                       int which) {
+  const StartInst& b = v[blockIdx.y];
+  scan_excl(b.blk, ((which ? b.m : b.n) + kSelChunk - 1) / kSelChunk);
+}
+__global__ __launch_bounds__(256) void k_many_sel_write(const StartInst* __restrict__ v,
+                                                        int which) {
+  const StartInst& b = v[blockIdx.y];
+  const int64_t count = which ? b.m : b.n, nb = (count + kSelChunk - 1) / kSelChunk;
+  for (int64_t c = blockIdx.x; c < nb; c += gridDim.x)
+    sel_write(which ? b.sub : nullptr, count, b.seed, b.sel, b.blk, which ? b.k : b.m,
+              which ? b.init_sel : b.sub, (unsigned)c);
+}
+__global__ __launch_bounds__(256) void k_many_rank(const StartInst* __restrict__ v) {
+  const StartInst& b = v[blockIdx.y];
+  for (int64_t c = blockIdx.x; c * 256 < b.k; c += gridDim.x)
+    rank_keys(b.init_sel, b.k, b.seed, b.init_key, (unsigned)c);
+}
+// the initial centers' rows and the subset's
+__global__ __launch_bounds__(256) void k_many_rows(const StartInst* __restrict__ v) {
+  const StartInst& b = v[blockIdx.y];
+  if (b.dtype == 0) {
+    const float* X = static_cast<const float*>(b.X);
+    centers_body<float>(X, b.n, b.d, b.init_key, b.k, b.c64, blockIdx.x, gridDim.x);
+    gather_body<float>(X, b.n, b.d, b.sub, b.m, static_cast<float*>(b.xs), blockIdx.x, gridDim.x);
+  } else {
+    const uint16_t* X = static_cast<const uint16_t*>(b.X);
+    centers_body<uint16_t>(X, b.n, b.d, b.init_key, b.k, b.c64, blockIdx.x, gridDim.x);
+    gather_body<uint16_t>(X, b.n, b.d, b.sub, b.m, static_cast<uint16_t*>(b.xs), blockIdx.x,
+                          gridDim.x);
+  }
+}
+__global__ __launch_bounds__(64) void k_many_prep_centers(const StartInst* __restrict__ v) {
+  const StartInst& b = v[blockIdx.y];
+  for (int j = blockIdx.x; j < b.k; j += gridDim.x)
+    prep_center(b.c64, b.k, b.d, b.cw, b.cn, b.cnorm, j);
+}
+// a stage's set-up: cleared sums and state, ...
+__global__ __launch_bounds__(256) void k_many_reset(const StartInst* __restrict__ v) {
+  const StartInst& b = v[blockIdx.y];
+  if (blockIdx.x == 0 && threadIdx.x == 0) reset_state(b.st);
+  const int64_t stride = (int64_t)gridDim.x * 256;
+  for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < b.nsums; e += stride)
+    b.slots[e] = 0;
+}
+// ... the statistics of its rows, ...
+template <typename T>
+__device__ __forceinline__ void many_stats(const StartInst& b, const void* X, int64_t rows, int E,
+                                           int glog) {
+  const T* x = static_cast<const T*>(X);
+  const unsigned bx = blockIdx.x, gx = gridDim.x;
+  if constexpr (sizeof(T) == 2)
+    if (E == 8) return row_stats_body<T, 8>(x, rows, b.d, glog, b.norms, b.st, bx, gx);
+  if (E == 4) row_stats_body<T, 4>(x, rows, b.d, glog, b.norms, b.st, bx, gx);
+  else if (E == 2) row_stats_body<T, 2>(x, rows, b.d, glog, b.norms, b.st, bx, gx);
+  else row_stats_body<T, 1>(x, rows, b.d, glog, b.norms, b.st, bx, gx);
+}
+__global__ __launch_bounds__(256) void k_many_stats(const StartInst* __restrict__ v, int stage) {
+  const StartInst& b = v[blockIdx.y];
+  const int64_t rows = stage ? b.n : b.m;
+  const int E = b.vec[stage], glog = b.glog[stage];
+  // blocks past the rows have nothing to add
+  if ((int64_t)blockIdx.x * 16 * (64 >> glog) >= rows) return;
+  const void* X = stage ? b.X : b.xs;
+  if (b.dtype == 0) many_stats<float>(b, X, rows, E, glog);
+  else many_stats<uint16_t>(b, X, rows, E, glog);
+}
+// ... its state from them, and the BF16 center copy
+__global__ __launch_bounds__(256) void k_many_begin(const StartInst* __restrict__ v, int stage) {
+  const StartInst& b = v[blockIdx.y];
+  begin_state(b.st, b.max_iter[stage], b.tol[stage], stage ? b.n : b.m, b.cnorm, b.k, b.d, 0, 0);
+}
+__global__ __launch_bounds__(64) void k_many_prep_bf16(const StartInst* __restrict__ v) {
+  const StartInst& b = v[blockIdx.y];
+  if (!b.cb16) return;
+  for (int j = blockIdx.x; j < b.brows; j += gridDim.x)
+    prep_bf16_row(b.c64, b.k, b.d, b.kd16, b.st, b.cb16, b.cnB, b.cb16lo, j, (unsigned)b.brows);
+}
+
+// Blocks per problem: one per `per` units of the largest problem's work, about
+// 8192 in all.
+static unsigned many_grid(int64_t most, int64_t per, int nj) {
+  return (unsigned)std::max<int64_t>(
+      1, std::min<int64_t>((most + per - 1) / per, std::max<int64_t>(1, 8192 / nj)));
+}
+
+hipError_t many_begin(const StartInst* dv, const StartInst* hv, int nj, int stage, hipStream_t s) {
+  int64_t sums = 1, waves = 1, brows = 0;
+  for (int i = 0; i < nj; ++i) {
+    sums = std::max(sums, hv[i].nsums);
+    waves = std::max(waves, (stage ? hv[i].n : hv[i].m) / (64 >> hv[i].glog[stage]) + 1);
+    if (hv[i].cb16) brows = std::max<int64_t>(brows, hv[i].brows);
+  }
+  const unsigned y = (unsigned)nj;
+  hipLaunchKernelGGL(k_many_reset, dim3(many_grid(sums, 2048, nj), y), dim3(256), 0, s, dv);
+  hipLaunchKernelGGL(k_many_stats, dim3(many_grid(waves, 16, nj), y), dim3(256), 0, s, dv, stage);
+  hipLaunchKernelGGL(k_many_begin, dim3(1, y), dim3(256), 0, s, dv, stage);
+  if (brows)
+    hipLaunchKernelGGL(k_many_prep_bf16, dim3(many_grid(brows, 1, nj), y), dim3(64), 0, s, dv);
+  return hipGetLastError();
+}
+
+hipError_t many_start(const StartInst* dv, const StartInst* hv, int nj, hipStream_t s) {
+  int64_t n = 1, m = 1, k = 1, el = 1;
+  for (int i = 0; i < nj; ++i) {
+    n = std::max(n, hv[i].n);
+    m = std::max(m, hv[i].m);
+    k = std::max<int64_t>(k, hv[i].k);
+    el = std::max(el, (hv[i].m + hv[i].k) * hv[i].d);
+  }
+  const unsigned y = (unsigned)nj;
+  for (int which = 0; which < 2; ++which) {
+    const int64_t count = which ? m : n;
+    hipLaunchKernelGGL(k_many_sel_init, dim3(1, y), dim3(256), 0, s, dv, which);
+    for (int level = 0; level < 6; ++level) {
+      hipLaunchKernelGGL(k_many_sel_hist, dim3(many_grid(count, 2048, nj), y), dim3(256), 0, s,
+                         dv, which);
+      hipLaunchKernelGGL(k_many_sel_pick, dim3(1, y), dim3(256), 0, s, dv);
+    }
+    const unsigned cg = many_grid(count, kSelChunk, nj);
+    hipLaunchKernelGGL(k_many_sel_count, dim3(cg, y), dim3(256), 0, s, dv, which);
+    hipLaunchKernelGGL(k_many_sel_scan, dim3(1, y), dim3(256), 0, s, dv, which);
+    hipLaunchKernelGGL(k_many_sel_write, dim3(cg, y), dim3(256), 0, s, dv, which);
+  }
+  hipLaunchKernelGGL(k_many_rank, dim3(many_grid(k, 256, nj), y), dim3(256), 0, s, dv);
+  hipLaunchKernelGGL(k_many_rows, dim3(many_grid(el, 1024, nj), y), dim3(256), 0, s, dv);
+  hipLaunchKernelGGL(k_many_prep_centers, dim3(many_grid(k, 1, nj), y), dim3(64), 0, s, dv);
+  return many_begin(dv, hv, nj, 0, s);
 }
 
 // ============================================================================

@@ -115,6 +115,25 @@ struct BatchHead {
   int64_t units;    // sum of the instances' units (assignment) ...
   int64_t centers;  // ... and of their k (finalize)
 };
+// One problem of a shared start (sampling, initial centers, stage set-ups).
+struct StartInst {
+  const void* X;
+  int64_t n, m;
+  int32_t d, k;
+  int32_t dtype, norms;   // norms: the stage statistics include max ||x||^2
+  uint64_t seed;
+  int32_t vec[2], glog[2];  // row pieces and lanes per row (subset copy, X)
+  int32_t max_iter[2];
+  double tol[2];
+  SelState* sel; unsigned long long* hist;
+  int64_t *blk, *sub, *init_sel, *init_key;
+  void* xs;
+  double* c64; float* cw; float* cn; double* cnorm;
+  PassState* st;
+  long long* slots; int64_t nsums;
+  uint16_t* cb16; uint16_t* cb16lo; float* cnB;  // NULL without the BF16 screen
+  int32_t kd16, brows;
+};
 // Compact per-instance status after a batched pass, for the host scheduler.
 struct BatchStatus {
   int32_t done, iter, converged, empty, nonfinite, pad;
@@ -231,6 +250,13 @@ hipError_t batch_sums(const BatchHead* hd, const BatchInst* bi, int blocks, hipS
 hipError_t batch_finalize(const BatchHead* hd, const BatchInst* bi, int blocks, hipStream_t s);
 hipError_t batch_status(const BatchHead* hd, const BatchInst* bi, BatchStatus* out,
                         hipStream_t s);
+// Starts of nj problems (dv: device copy of hv), through their fast stage's set-up;
+// and the set-up of a stage (0 fast, 1 slow) alone.
+hipError_t many_start(const StartInst* dv, const StartInst* hv, int nj, hipStream_t s);
+hipError_t many_begin(const StartInst* dv, const StartInst* hv, int nj, int stage, hipStream_t s);
+// elements per lane and log2 of the lanes per row of the row-group kernels
+int row_vec(int dtype, int32_t d, const void* X);
+int row_glog(int32_t d, int E);
 // uniform [-1, 1) values: kind 0 FP32, 1 BF16 bits, 2 FP64
 hipError_t fill_uniform(void* p, int kind, int64_t count, uint64_t seed, hipStream_t s);
 

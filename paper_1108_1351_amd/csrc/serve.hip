@@ -292,46 +292,45 @@ size_t job_layout(Job& j, void* base) {
   return c.off;
 }
 
-// Puts a problem's stage on the device: row statistics of its data, the stop
-// rule, zeroed sums.  stage 1: the subset, stage 2: all points.
-km_status begin_stage(Job& j, int stage, hipStream_t s) {
-  km_status rc = KM_OK;
+// A problem's entry of a shared start or stage set-up.
+StartInst start_inst(const Job& j) {
   const km_request& r = j.rq;
-  const int dt = r.dtype == KM_F32 ? 0 : 1;
-  const void* X = stage == 1 ? j.xs : j.X;
-  const int64_t rows = stage == 1 ? j.m : r.n;
-  HIP_TRY(stage_reset(j.st, s));
-  // the screen's score offset needs max ||x||^2 of the stage's rows
-  HIP_TRY(row_stats(X, dt, rows, r.d, j.screen != 0, j.st, s));
-  HIP_TRY(stage_begin(j.st, r.max_iter[stage - 1], r.tol[stage - 1], rows, j.cnorm, r.k, r.d, 0,
-                      s));
-  if (j.screen)
-    HIP_TRY(prep_bf16(j.c64, r.k, r.d, 16 * j.screen, j.st, j.cb16, j.cnB, s, j.cb16lo));
-  HIP_TRY(zero_i64(j.slots, (int64_t)kSlots * r.k * (r.d + 1), s));
-  j.phase = stage;
-  j.iter_now = 0;
-done:
-  return rc;
-}
-
-// Sampling, initial centers, the subset copy and the first stage.
-km_status start_job(Job& j, hipStream_t s) {
-  km_status rc = KM_OK;
-  const km_request& r = j.rq;
-  const int dt = r.dtype == KM_F32 ? 0 : 1;
-  if (j.copy_x)
-    HIP_TRY(hipMemcpyAsync(const_cast<void*>(j.X), r.X, (size_t)r.n * r.d * elt_size(r.dtype),
-                           r.x_on_host ? hipMemcpyHostToDevice : hipMemcpyDeviceToDevice, s));
-  HIP_TRY(hipMemsetAsync(j.hist, 0, sizeof(unsigned long long) * kSelBins, s));
-  HIP_TRY(sel_run(nullptr, r.n, r.seed, j.m, j.sel, j.hist, j.blk, j.sub, s));
-  HIP_TRY(sel_run(j.sub, j.m, r.seed, r.k, j.sel, j.hist, j.blk, j.init_sel, s));
-  HIP_TRY(rank_by_key(j.init_sel, r.k, r.seed, j.init_key, s));
-  HIP_TRY(centers_from_rows(j.X, r.n, dt, r.d, j.init_key, r.k, j.c64, s));
-  HIP_TRY(gather_rows(j.X, r.n, dt, r.d, j.sub, j.m, j.xs, s));
-  HIP_TRY(prep_centers(j.c64, r.k, r.d, j.cw, j.cn, j.cnorm, s));
-  rc = begin_stage(j, 1, s);
-done:
-  return rc;
+  StartInst b{};
+  b.X = j.X;
+  b.n = r.n;
+  b.m = j.m;
+  b.d = r.d;
+  b.k = r.k;
+  b.dtype = r.dtype == KM_F32 ? 0 : 1;
+  b.norms = j.screen != 0;  // the screen's score offset needs max ||x||^2 of the stage's rows
+  b.seed = r.seed;
+  const void* rows[2] = {j.xs, j.X};
+  for (int s = 0; s < 2; ++s) {
+    b.vec[s] = row_vec(b.dtype, r.d, rows[s]);
+    b.glog[s] = row_glog(r.d, b.vec[s]);
+    b.max_iter[s] = r.max_iter[s];
+    b.tol[s] = r.tol[s];
+  }
+  b.sel = j.sel;
+  b.hist = j.hist;
+  b.blk = j.blk;
+  b.sub = j.sub;
+  b.init_sel = j.init_sel;
+  b.init_key = j.init_key;
+  b.xs = j.xs;
+  b.c64 = j.c64;
+  b.cw = j.cw;
+  b.cn = j.cn;
+  b.cnorm = j.cnorm;
+  b.st = j.st;
+  b.slots = j.slots;
+  b.nsums = (int64_t)kSlots * r.k * (r.d + 1);
+  b.cb16 = j.cb16;
+  b.cb16lo = j.cb16lo;
+  b.cnB = j.cnB;
+  b.kd16 = 16 * j.screen;
+  b.brows = j.screen ? (int32_t)bf16_rows(r.k) : 0;
+  return b;
 }
 
 // ------------------------------------------------------------------ engine
@@ -347,23 +346,61 @@ class Engine {
     int screen;  // K steps of the batched BF16 screen, 0 for the FP32 kernel
   };
 
-  explicit Engine(hipStream_t s) : s_(s) {}
+  // cap: problems advanced together, at most kTableCap (the tables' size)
+  Engine(hipStream_t s, int cap) : s_(s), cap_(std::min(kTableCap, std::max(1, cap))) {}
   ~Engine() { release(); }
 
   km_status init() {
     km_status rc = KM_OK;
     const size_t heads = sizeof(BatchHead) * (kMaxShapes + 2);
-    const size_t insts = sizeof(BatchInst) * (size_t)kTableCap * (kMaxShapes + 1);
-    const size_t stat = sizeof(BatchStatus) * kTableCap;
-    bytes_ = heads + insts + stat;
+    const size_t insts = sizeof(BatchInst) * (size_t)cap_ * (kMaxShapes + 1);
+    const size_t stat = sizeof(BatchStatus) * cap_;
+    const size_t starts = sizeof(StartInst) * (size_t)cap_ * 2;
+    bytes_ = heads + insts + starts + stat;
     HIP_TRY(hipMalloc(&dev_, bytes_));
-    HIP_TRY(hipHostMalloc(&host_, heads + insts, hipHostMallocDefault));
+    HIP_TRY(hipHostMalloc(&host_, heads + insts + starts, hipHostMallocDefault));
     HIP_TRY(hipHostMalloc(&hstat_, stat, hipHostMallocDefault));
     d_heads_ = static_cast<BatchHead*>(dev_);
     d_insts_ = reinterpret_cast<BatchInst*>(static_cast<char*>(dev_) + heads);
-    d_stat_ = reinterpret_cast<BatchStatus*>(static_cast<char*>(dev_) + heads + insts);
+    d_start_ = reinterpret_cast<StartInst*>(static_cast<char*>(dev_) + heads + insts);
+    d_stat_ = reinterpret_cast<BatchStatus*>(static_cast<char*>(dev_) + heads + insts + starts);
     h_heads_ = static_cast<BatchHead*>(host_);
     h_insts_ = reinterpret_cast<BatchInst*>(static_cast<char*>(host_) + heads);
+    h_start_ = reinterpret_cast<StartInst*>(static_cast<char*>(host_) + heads + insts);
+  done:
+    return rc;
+  }
+
+  int cap() const { return cap_; }
+
+  // Starts the problems (at most cap): sampling, initial centers, the subset copy
+  // and the first stage.  Between two rounds (which wait for the device) there
+  // is at most one start and one set-up of second stages, each with its table.
+  km_status start(const std::vector<Job*>& js) {
+    km_status rc = KM_OK;
+    const int n = (int)js.size();
+    if (n == 0) return KM_OK;
+    for (int i = 0; i < n; ++i) {
+      Job& j = *js[i];
+      h_start_[i] = start_inst(j);
+      j.phase = 1;
+      j.iter_now = 0;
+    }
+    HIP_TRY(hipMemcpyAsync(d_start_, h_start_, sizeof(StartInst) * n, hipMemcpyHostToDevice, s_));
+    HIP_TRY(many_start(d_start_, h_start_, n, s_));
+  done:
+    return rc;
+  }
+
+  // Puts the problems' second stage on the device.
+  km_status second_stage(const std::vector<Job*>& js) {
+    km_status rc = KM_OK;
+    const int n = (int)js.size();
+    StartInst *h = h_start_ + cap_, *d = d_start_ + cap_;
+    if (n == 0) return KM_OK;
+    for (int i = 0; i < n; ++i) h[i] = start_inst(*js[i]);
+    HIP_TRY(hipMemcpyAsync(d, h, sizeof(StartInst) * n, hipMemcpyHostToDevice, s_));
+    HIP_TRY(many_begin(d, h, n, 1, s_));
   done:
     return rc;
   }
@@ -390,7 +427,7 @@ class Engine {
                   std::vector<BatchStatus>& st) {
     km_status rc = KM_OK;
     const int na = (int)act.size();
-    if (na > kTableCap) return fail(KM_EINVAL, "more than %d active problems", kTableCap);
+    if (na > cap_) return fail(KM_EINVAL, "more than %d active problems", cap_);
     const int ns = (int)shapes_.size();
     std::vector<int> cnt(ns, 0);
     std::vector<int64_t> units(ns, 0);
@@ -459,8 +496,8 @@ class Engine {
       }
       units[g] += b.units;
       centers += b.k;
-      h_insts_[(size_t)g * kTableCap + cnt[g]++] = b;
-      h_insts_[(size_t)kMaxShapes * kTableCap + a] = b;
+      h_insts_[(size_t)g * cap_ + cnt[g]++] = b;
+      h_insts_[(size_t)kMaxShapes * cap_ + a] = b;
       mask |= 1u << g;
     }
     for (int g = 0; g < ns; ++g) h_heads_[g] = BatchHead{cnt[g], 0, units[g], 0};
@@ -469,10 +506,10 @@ class Engine {
     // descriptors: only the used prefix of each table travels
     for (int g = 0; g < ns; ++g)
       if (cnt[g])
-        HIP_TRY(hipMemcpyAsync(d_insts_ + (size_t)g * kTableCap, h_insts_ + (size_t)g * kTableCap,
+        HIP_TRY(hipMemcpyAsync(d_insts_ + (size_t)g * cap_, h_insts_ + (size_t)g * cap_,
                                sizeof(BatchInst) * cnt[g], hipMemcpyHostToDevice, s_));
-    HIP_TRY(hipMemcpyAsync(d_insts_ + (size_t)kMaxShapes * kTableCap,
-                           h_insts_ + (size_t)kMaxShapes * kTableCap, sizeof(BatchInst) * na,
+    HIP_TRY(hipMemcpyAsync(d_insts_ + (size_t)kMaxShapes * cap_,
+                           h_insts_ + (size_t)kMaxShapes * cap_, sizeof(BatchInst) * na,
                            hipMemcpyHostToDevice, s_));
     HIP_TRY(hipMemcpyAsync(d_heads_, h_heads_, sizeof(BatchHead) * (kMaxShapes + 2),
                            hipMemcpyHostToDevice, s_));
@@ -505,13 +542,13 @@ class Engine {
       if (!(mask & (1u << g))) continue;
       const Shape& sh = shapes_[g];
       BatchShape bs{sh.dtype, sh.dmax, sh.ppt, sh.lds, sh.blocks, sh.screen};
-      HIP_TRY(batch_assign(d_heads_ + g, d_insts_ + (size_t)g * kTableCap, bs, s_));
+      HIP_TRY(batch_assign(d_heads_ + g, d_insts_ + (size_t)g * cap_, bs, s_));
     }
-    HIP_TRY(batch_sums(d_heads_ + kMaxShapes + 1, d_insts_ + (size_t)kMaxShapes * kTableCap,
+    HIP_TRY(batch_sums(d_heads_ + kMaxShapes + 1, d_insts_ + (size_t)kMaxShapes * cap_,
                        2 * device_cus(), s_));
-    HIP_TRY(batch_finalize(d_heads_ + kMaxShapes, d_insts_ + (size_t)kMaxShapes * kTableCap,
+    HIP_TRY(batch_finalize(d_heads_ + kMaxShapes, d_insts_ + (size_t)kMaxShapes * cap_,
                            kFinalizeBlocks, s_));
-    HIP_TRY(batch_status(d_heads_ + kMaxShapes, d_insts_ + (size_t)kMaxShapes * kTableCap, d_stat_,
+    HIP_TRY(batch_status(d_heads_ + kMaxShapes, d_insts_ + (size_t)kMaxShapes * cap_, d_stat_,
                          s_));
   done:
     return rc;
@@ -557,19 +594,21 @@ class Engine {
   }
 
   hipStream_t s_;
+  int cap_;
   size_t bytes_ = 0;
   void* dev_ = nullptr;
   void* host_ = nullptr;
   BatchStatus* hstat_ = nullptr;
   BatchHead *d_heads_ = nullptr, *h_heads_ = nullptr;
   BatchInst *d_insts_ = nullptr, *h_insts_ = nullptr;
+  StartInst *d_start_ = nullptr, *h_start_ = nullptr;  // [2][cap]: starts, second stages
   BatchStatus* d_stat_ = nullptr;
   std::vector<Shape> shapes_;
   std::unordered_map<uint64_t, hipGraphExec_t> graphs_;
   int64_t rounds_ = 0, syncs_ = 0;
 };
 
-// Admission of a problem: shape from the autotuner, workspace, the first stage.
+// Admission of a problem: shape from the autotuner, workspace, its copy of X.
 km_status admit(Engine& eng, Job& j, hipStream_t s) {
   km_status rc = KM_OK;
   const km_request& r = j.rq;
@@ -588,11 +627,16 @@ km_status admit(Engine& eng, Job& j, hipStream_t s) {
   rc = j.mem.get(j.bytes, nullptr, 0, s);
   if (rc != KM_OK) return rc;
   job_layout(j, j.mem.ptr);
-  return start_job(j, s);
+  if (j.copy_x)
+    HIP_TRY(hipMemcpyAsync(const_cast<void*>(j.X), r.X, (size_t)r.n * r.d * elt_size(r.dtype),
+                           r.x_on_host ? hipMemcpyHostToDevice : hipMemcpyDeviceToDevice, s));
+done:
+  return rc;
 }
 
-// After a round: stage changes and completion.  Returns true when finished.
-bool advance(Job& j, const BatchStatus& b, hipStream_t s) {
+// After a round: stage changes and completion.  Returns true when finished; a
+// problem whose fast stage ended joins `second` (its slow stage is to be set up).
+bool advance(Job& j, const BatchStatus& b, hipStream_t s, std::vector<Job*>& second) {
   const km_request& r = j.rq;
   j.iter_now = b.iter;
   if (b.nonfinite) {
@@ -608,13 +652,9 @@ bool advance(Job& j, const BatchStatus& b, hipStream_t s) {
     j.info.shift[0] = b.shift;
     j.info.J_stage1 = b.J;
     j.info.uncertain += b.uncertain;
-    km_status rc = begin_stage(j, 2, s);
-    if (rc != KM_OK) {
-      j.status = rc;
-      j.err = g_err;
-      j.phase = 4;
-      return true;
-    }
+    j.phase = 2;
+    j.iter_now = 0;
+    second.push_back(&j);
   } else if (j.phase == 2 && b.done == 1) {
     j.info.iters[1] = b.iter;
     j.info.converged[1] = b.converged;
@@ -719,6 +759,8 @@ void km_server::loop() {
       ctr.pending = (int64_t)pending.size();
     }
     std::vector<std::unique_ptr<Job>> failed_now;
+    const size_t old = active.size();
+    std::vector<Job*> fresh;
     for (auto& jp : admitted_now) {
       jp->t_admit = now_s();
       const km_status rc = admit(*eng, *jp, s);
@@ -728,8 +770,18 @@ void km_server::loop() {
         jp->phase = 4;
         failed_now.push_back(std::move(jp));
       } else {
+        fresh.push_back(jp.get());
         active.push_back(std::move(jp));
       }
+    }
+    if (const km_status rc = eng->start(fresh); rc != KM_OK) {
+      for (size_t a = old; a < active.size(); ++a) {
+        active[a]->status = rc;
+        active[a]->err = g_err;
+        active[a]->phase = 4;
+        failed_now.push_back(std::move(active[a]));
+      }
+      active.resize(old);
     }
     std::vector<std::unique_ptr<Job>> done_now = std::move(failed_now);
     if (!active.empty()) {
@@ -738,6 +790,7 @@ void km_server::loop() {
       const int passes = chunk_passes(act, cfg.passes_per_sync);
       const km_status rc = eng->round(act, cfg.use_graphs != 0, passes, stat);
       std::vector<std::unique_ptr<Job>> keep;
+      std::vector<Job*> second;
       for (size_t a = 0; a < active.size(); ++a) {
         bool fin;
         if (rc != KM_OK) {
@@ -745,12 +798,26 @@ void km_server::loop() {
           active[a]->err = g_err;
           fin = true;
         } else {
-          fin = advance(*active[a], stat[a], s);
+          fin = advance(*active[a], stat[a], s, second);
         }
         if (fin) done_now.push_back(std::move(active[a]));
         else keep.push_back(std::move(active[a]));
       }
       active = std::move(keep);
+      if (const km_status rs = eng->second_stage(second); rs != KM_OK) {
+        // the set-up's launches failed: the problems that needed it end here
+        keep.clear();
+        for (auto& jp : active) {
+          const bool hit = std::find(second.begin(), second.end(), jp.get()) != second.end();
+          if (hit) {
+            jp->status = rs;
+            jp->err = g_err;
+            jp->phase = 4;
+          }
+          (hit ? done_now : keep).push_back(std::move(jp));
+        }
+        active = std::move(keep);
+      }
       if (!done_now.empty()) (void)hipStreamSynchronize(s);
     }
     if (!done_now.empty() || !admitted_now.empty()) {
@@ -815,7 +882,7 @@ namespace {
 // The batch on a private stream (graph capture needs one that is not the null stream).
 km_status fit_batch_on(const km_request* reqs, int32_t count, km_result* results, hipStream_t s) {
   const double t0 = now_s();
-  Engine eng(s);
+  Engine eng(s, count);
   km_status rc = eng.init();
   if (rc != KM_OK) return rc;
   std::vector<std::unique_ptr<Job>> jobs(count);
@@ -845,19 +912,27 @@ km_status fit_batch_on(const km_request* reqs, int32_t count, km_result* results
   }
   std::vector<BatchStatus> stat;
   // problems beyond the table capacity wait for earlier ones to finish
-  std::vector<Job*> run, waiting;
-  for (Job* j : act) (run.size() < (size_t)kTableCap ? run : waiting).push_back(j);
-  while (!run.empty()) {
-    rc = eng.round(run, true, chunk_passes(run, 8), stat);
-    if (rc != KM_OK) break;
-    std::vector<Job*> keep;
-    for (size_t a = 0; a < run.size(); ++a)
-      if (!advance(*run[a], stat[a], s)) keep.push_back(run[a]);
-    run = std::move(keep);
-    while (!waiting.empty() && run.size() < (size_t)kTableCap) {
+  std::vector<Job*> run, waiting(act.rbegin(), act.rend()), fresh, second;
+  auto join = [&]() {
+    fresh.clear();
+    while (!waiting.empty() && run.size() < (size_t)eng.cap()) {
+      fresh.push_back(waiting.back());
       run.push_back(waiting.back());
       waiting.pop_back();
     }
+    return eng.start(fresh);
+  };
+  rc = join();
+  while (rc == KM_OK && !run.empty()) {
+    rc = eng.round(run, true, chunk_passes(run, 8), stat);
+    if (rc != KM_OK) break;
+    std::vector<Job*> keep;
+    second.clear();
+    for (size_t a = 0; a < run.size(); ++a)
+      if (!advance(*run[a], stat[a], s, second)) keep.push_back(run[a]);
+    run = std::move(keep);
+    rc = eng.second_stage(second);
+    if (rc == KM_OK) rc = join();
   }
   const hipError_t e = hipStreamSynchronize(s);
   if (rc == KM_OK && e != hipSuccess)
@@ -910,7 +985,7 @@ km_status km_server_create(const km_server_cfg* cfg, km_server** out) {
   srv->budget = srv->cfg.hbm_budget_bytes ? srv->cfg.hbm_budget_bytes : fr / 4 * 3;
   if (hipStreamCreateWithFlags(&srv->s, hipStreamNonBlocking) != hipSuccess)
     return fail(KM_EDEVICE, "hipStreamCreate failed");
-  srv->eng = std::make_unique<Engine>(srv->s);
+  srv->eng = std::make_unique<Engine>(srv->s, srv->cfg.max_active);
   const km_status rc = srv->eng->init();
   if (rc != KM_OK) {
     (void)hipStreamDestroy(srv->s);

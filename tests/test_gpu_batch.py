@@ -297,3 +297,21 @@ def test_batch_sums_unit_edges(d, dtype, ks):
     for Xh, (C, L, info), (n, k) in zip(data, out, specs):
         _check_against_oracle(Xh, C, L, info, k, 0.5, 3, (3, 4), (0.0, 0.0),
                               f"n={n} d={d} k={k} {dtype}")
+
+
+def test_shared_starts_any_sizes():
+    """Problems of very different sizes started together (one point, one
+    selection chunk more or less, a subset of all points, k = n) take the same
+    initial centers and fits as alone."""
+    specs = [(1, 3, 1, 1.0), (2, 1, 2, 1.0), (8191, 2, 5, 0.1), (8192, 5, 7, 1.0),
+             (8193, 8, 3, 0.001), (100_003, 2, 64, 0.02), (257, 16, 257, 0.3), (70, 30, 9, 0.5)]
+    data = [_problem(n, d, k, 300 + n, "f32") for n, d, k, _ in specs]
+    probs = [(to_device(Xh), k, f, 11 + i, (6, 7), (1e-4, 1e-4))
+             for i, (Xh, (n, d, k, f)) in enumerate(zip(data, specs))]
+    together = km.kmeans_fit_batch(probs)
+    for i, (p, (C, L, info)) in enumerate(zip(probs, together)):
+        (C1, L1, info1), = km.kmeans_fit_batch([p])
+        assert torch.equal(C, C1) and torch.equal(L, L1), specs[i]
+        assert info["iters"] == info1["iters"] and info["J"] == info1["J"]
+        _check_against_oracle(data[i], C, L, info, p[1], p[2], p[3], (6, 7), (1e-4, 1e-4),
+                              f"start {specs[i]}")
