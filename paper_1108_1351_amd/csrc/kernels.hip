@@ -4643,6 +4643,248 @@ __global__ __launch_bounds__(256) void k_batch_assign(const BatchHead* __restric
   }
 }
 
+// The batched pass of small dims (d <= 16, k <= 256) on the split BF16 screen of
+// k_fused_pair: one launch per padded row length KD for all its instances.  A
+// work unit is 512 points of one instance; the block first lays the instance's
+// FP64 centers, split A operands and C input out in LDS (about 4 us), then each
+// wave takes 64 points at a time as two 32-point tiles.  A lane ranks 16 scores of
+// both tiles per 32 centers with four VALU operations each, where the FP32 form
+// (k_batch_assign) spends 2 + 2d and its LDS reads on a score and point: the
+// assignment of 30 problems of 2 and 8 dims took 129 us a pass there (in six
+// launches, one per register tile).
+// A point knows the best three keys of both lane halves (even and odd blocks of 16
+// centers).  Certain: the second best is out of the band of the best; with both
+// halves' thirds out of it, FP64 decides among the (up to four) keys inside;
+// otherwise the FP64 check over all centers.
+template <typename T, int KD>
+__global__ __launch_bounds__(256, 2) void k_batch_pair(const BatchHead* __restrict__ hd,
+                                                       const BatchInst* __restrict__ bi) {
+  constexpr int H = KD / 2, HW = H / 2;
+  constexpr int NS = sizeof(T) == 4 ? 3 : 2;
+  constexpr int NM = (NS * H + 7) / 8, NE = NM * 8;
+  constexpr int CSS = KD + 2;
+  constexpr int KM = kPairCenters;
+  extern __shared__ __align__(16) unsigned char smem[];
+  double* cs = reinterpret_cast<double*>(smem);                          // [KM][CSS]
+  v8bf* aop = reinterpret_cast<v8bf*>(cs + KM * CSS);                    // [KM / 32][NM][64]
+  float* cbias = reinterpret_cast<float*>(aop + KM / 32 * NM * 64);      // [KM]
+  unsigned long long* S = reinterpret_cast<unsigned long long*>(cbias + KM);  // [k][d + 1]
+  const int lane = threadIdx.x & 63, h = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int ninst = hd->ninst;
+  const int64_t units = hd->units;
+  for (int64_t u = blockIdx.x; u < units; u += gridDim.x) {
+    const BatchInst& b = bi[batch_find(bi, ninst, u, 0)];
+    PassState* st = b.st;
+    const int dn = ld_agent(&st->done);
+    if ((b.mode == 1 && dn) || (b.mode == 2 && dn == 2)) continue;
+    const int64_t tile = u - b.unit0, n = b.n;
+    const int d = b.d, k = b.k, nt = (k + 31) >> 5;
+    const bool lds = b.mode == 1 && b.lds_sums;
+    const T* X = reinterpret_cast<const T*>(b.X);
+    const float B = st->B, cmax = st->cmax, scale = st->scale;
+    for (int e = threadIdx.x; e < k * KD; e += 256) {
+      const int j = e / KD, t = e - j * KD;
+      cs[j * CSS + t] = t < d ? b.c64[(int64_t)j * d + t] : 0.0;
+    }
+    for (int e = threadIdx.x; e < 32 * nt; e += 256) cbias[e] = e < k ? b.cn[e] + B : 1e30f;
+    if (lds)
+      for (int e = threadIdx.x; e < k * (d + 1); e += 256) S[e] = 0ull;
+    __syncthreads();
+    // A operands as in k_fused_pair: register r of lane half h is center 32t + 16h + r
+    for (int e = threadIdx.x; e < nt * 64; e += 256) {
+      const int t = e >> 6, ln = e & 63, hh = ln >> 5, i = ln & 31;
+      const int j = 32 * t + 16 * ((i >> 2) & 1) + 4 * (i >> 3) + (i & 3);
+      uint16_t e16[NE];
+#pragma unroll
+      for (int q = 0; q < NE; ++q) e16[q] = 0;
+#pragma unroll
+      for (int q = 0; q < H; ++q) {
+        uint16_t hi, lo;
+        (void)bf16_split(j < k ? cs[j * CSS + hh * H + q] : 0.0, hi, lo);
+        e16[q] = hi;
+        e16[H + q] = lo;
+        if constexpr (NS == 3) e16[2 * H + q] = hi;
+      }
+#pragma unroll
+      for (int m = 0; m < NM; ++m) {
+        u16x8 v;
+#pragma unroll
+        for (int q = 0; q < 8; ++q) v[q] = e16[8 * m + q];
+        aop[(t * NM + m) * 64 + ln] = __builtin_bit_cast(v8bf, v);
+      }
+    }
+    __syncthreads();
+    // the band of two scores as in k_fused_pair, with ||c' - c'hi|| <= 2^-8 ||c||
+    // for its exact maximum and two more roundings of the C input
+    const int bg = nt == 1 ? 5 : nt == 2 ? 6 : nt <= 4 ? 7 : 8;
+    const int GM = (1 << bg) - 1, keep = opaque_vgpr(~GM);
+    const float dcn = cmax * 0x1.03p-8f;
+    const float ea = (float)(16 * NM + 12) * 0x1p-23f * 1.01f;
+    const float cc = 2.f * cmax + 2.004f * dcn;
+    const float c0 = (2.f * ea * (cmax * cmax + B) + 1e-30f) * 1.0001f;
+    const float c1 = (2.f * dcn * 0x1p-8f * 1.001f + 2.f * ea * cc) * 1.0001f;
+    const float c2 = (2.f * dcn * 1.004f + 0x1p-6f * cmax + 2.f * ea * 1.004f * cc) * 1.0001f;
+    const float delta = (float)(1 << bg) * 0x1p-23f * 1.01f;
+    const bool whole = d == KD && (reinterpret_cast<uintptr_t>(X) & 15u) == 0;
+    double Jacc = 0.0;
+    int64_t ucnt = 0;
+#pragma unroll 1
+    for (int it = 0; it < kPairPoints / 256; ++it) {
+      const int64_t p0 = tile * kPairPoints + it * 256 + wave * 64;
+      if (p0 >= n) break;
+      const int64_t i = p0 + lane;
+      const bool valid = i < n;
+      float x[KD];
+      if (whole) load_row_full<T, KD, true>(X, min(i, n - 1), d, x);
+      else load_row_full<T, KD, false>(X, min(i, n - 1), d, x);
+      typedef float f32x2 __attribute__((ext_vector_type(2)));
+      typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+      uint32_t xw[H], lw[H] = {};
+      float s2 = 0.f, r2 = 0.f;
+#pragma unroll
+      for (int q = 0; q < H; ++q) {
+        const f32x2 pr = {x[2 * q], x[2 * q + 1]};
+        xw[q] = __builtin_bit_cast(uint32_t, __builtin_convertvector(pr, bf16x2));
+        const float lo = bf16_lo(xw[q]), hi = bf16_hi(xw[q]);
+        s2 = __builtin_fmaf(lo, lo, s2);
+        s2 = __builtin_fmaf(hi, hi, s2);
+        if constexpr (sizeof(T) == 4) {
+          const f32x2 rr = {x[2 * q] - lo, x[2 * q + 1] - hi};
+          r2 = __builtin_fmaf(rr.x, rr.x, r2);
+          r2 = __builtin_fmaf(rr.y, rr.y, r2);
+          lw[q] = __builtin_bit_cast(uint32_t, __builtin_convertvector(rr, bf16x2));
+        }
+      }
+      uint32_t wA[NE / 2], wB[NE / 2];
+#pragma unroll
+      for (int q = 0; q < NE / 2; ++q) wA[q] = wB[q] = 0u;
+#pragma unroll
+      for (int q = 0; q < HW; ++q) {
+        const auto r = __builtin_amdgcn_permlane32_swap(xw[q], xw[HW + q], false, false);
+        wA[q] = wA[HW + q] = r[0];
+        wB[q] = wB[HW + q] = r[1];
+        if constexpr (NS == 3) {
+          const auto l = __builtin_amdgcn_permlane32_swap(lw[q], lw[HW + q], false, false);
+          wA[2 * HW + q] = l[0];
+          wB[2 * HW + q] = l[1];
+        }
+      }
+      v8bf oA[NM], oB[NM];
+#pragma unroll
+      for (int m = 0; m < NM; ++m) {
+        const uint32_t a4[4] = {wA[4 * m], wA[4 * m + 1], wA[4 * m + 2], wA[4 * m + 3]};
+        const uint32_t b4[4] = {wB[4 * m], wB[4 * m + 1], wB[4 * m + 2], wB[4 * m + 3]};
+        oA[m] = __builtin_bit_cast(v8bf, a4);
+        oB[m] = __builtin_bit_cast(v8bf, b4);
+      }
+      int ka[3] = {INT_MAX, INT_MAX, INT_MAX}, kb[3] = {INT_MAX, INT_MAX, INT_MAX};
+      for (int t = 0; t < nt; ++t) {
+        v16f bias;
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          const float4 v = *reinterpret_cast<const float4*>(&cbias[32 * t + 16 * h + 4 * g]);
+          bias[4 * g] = v.x; bias[4 * g + 1] = v.y; bias[4 * g + 2] = v.z; bias[4 * g + 3] = v.w;
+        }
+        v16f accA = bias, accB = bias;
+#pragma unroll
+        for (int m = 0; m < NM; ++m) {
+          const v8bf at = aop[(t * NM + m) * 64 + lane];
+          accA = __builtin_amdgcn_mfma_f32_32x32x16_bf16(at, oA[m], accA, 0, 0, 0);
+          accB = __builtin_amdgcn_mfma_f32_32x32x16_bf16(at, oB[m], accB, 0, 0, 0);
+        }
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int va = (__float_as_int(accA[r]) & keep) | (32 * t + r);
+          ka[2] = med3_i32(ka[1], va, ka[2]);
+          ka[1] = med3_i32(ka[0], va, ka[1]);
+          ka[0] = min(ka[0], va);
+          const int vb = (__float_as_int(accB[r]) & keep) | (32 * t + r);
+          kb[2] = med3_i32(kb[1], vb, kb[2]);
+          kb[1] = med3_i32(kb[0], vb, kb[1]);
+          kb[0] = min(kb[0], vb);
+        }
+      }
+      // lane l gets both halves' keys of its own point
+      int k0[3], k1[3];
+#pragma unroll
+      for (int q = 0; q < 3; ++q) {
+        const auto w = __builtin_amdgcn_permlane32_swap(ka[q] | (h << 4), kb[q] | (h << 4), false,
+                                                        false);
+        k0[q] = (int)w[0];
+        k1[q] = (int)w[1];
+      }
+      const float xn = __builtin_amdgcn_sqrtf(s2) * 1.01f;
+      const float xr = sizeof(T) == 4 ? __builtin_amdgcn_sqrtf(r2) * 1.01f : 0.f;
+      const float E2 = __builtin_fmaf(c2, xr, __builtin_fmaf(c1, xn, c0));
+      const int best = min(k0[0], k1[0]);
+      const float v1 = __int_as_float(best & ~GM);
+      auto apart = [&](int key) {
+        const float v = __int_as_float(key & ~GM);
+        return (v - v1) > E2 + delta * (fabsf(v) + fabsf(v1));
+      };
+      int l = best & GM;
+      const int others[3] = {max(k0[0], k1[0]), k0[1], k1[1]};
+      const bool certain = k == 1 || (l < k && apart(min(others[0], min(k0[1], k1[1]))));
+      const bool closed = l < k && apart(k0[2]) && apart(k1[2]);
+      const bool few = valid && !certain && closed, full = valid && !certain && !closed;
+      if (l >= k) l = 0;
+      double x64[KD];
+#pragma unroll
+      for (int q = 0; q < KD; ++q) x64[q] = (double)x[q];
+      auto dist64 = [&](int j) {  // FP64 direct form over the whole row (zero past d)
+        const double* cj = cs + j * CSS;
+        double p = 0.0;
+#pragma unroll
+        for (int q = 0; q < KD; ++q) {
+          const double e = x64[q] - cj[q];
+          p = __builtin_fma(e, e, p);
+        }
+        return p;
+      };
+      double D = dist64(l);
+#pragma unroll
+      for (int q = 0; q < 3; ++q) {
+        const int j = others[q] & GM;
+        const bool in = few && j < k && !apart(others[q]);
+        if (__ballot(in)) {
+          const double Dj = dist64(in ? j : 0);
+          if (in && (Dj < D || (Dj == D && j < l))) {
+            D = Dj;
+            l = j;
+          }
+        }
+      }
+      if (__ballot(full)) {
+        ucnt += row_fp64_check<KD, CSS>(full, x, k, cs, l);
+        if (full) D = dist64(l);
+      }
+      if (valid) {
+        Jacc += D;
+        if (b.labels) b.labels[i] = l;
+        if (lds) {
+          unsigned long long* Sr = S + l * (d + 1);
+#pragma unroll
+          for (int q = 0; q < KD; ++q)
+            if (q < d)
+              atomicAdd(&Sr[q], (unsigned long long)(long long)__float2int_rn(x[q] * scale));
+          atomicAdd(&Sr[d], 1ull);
+        }
+      }
+    }
+    __syncthreads();
+    if (lds) {
+      unsigned long long* row = reinterpret_cast<unsigned long long*>(
+          b.slots + (tile & (b.nslots - 1)) * k * (d + 1));
+      for (int e = threadIdx.x; e < k * (d + 1); e += 256) {
+        const unsigned long long v = S[e];
+        if (v) atomicAdd(&row[e], v);
+      }
+    }
+    block_sum_J(Jacc, ucnt, 0, b.Jpart, b.upart, tile);  // ends with a barrier
+  }
+}
+
 // The batched BF16 screen: one launch scores the points of every listed
 // BF16 instance with d in (16, 16 KS] and k <= 256 on the matrix cores.  A work
 // unit is a tile of 256 points of one instance; each wave takes 64 of them as
@@ -6076,6 +6318,27 @@ int batch_screen_ks(int dtype, int32_t d, int32_t k) {
   return d <= 32 ? 2 : d <= 64 ? 4 : 8;
 }
 
+int batch_pair_kd(int32_t d, int32_t k) {
+  if (d > 16 || k > kPairCenters) return 0;
+  return d <= 4 ? 4 : d <= 8 ? 8 : 16;
+}
+
+size_t batch_pair_lds(int dtype, int kd, size_t sums) {
+  const int nm = ((dtype == 0 ? 3 : 2) * (kd / 2) + 7) / 8;
+  return (size_t)kPairCenters * (kd + 2) * 8 + (size_t)kPairCenters / 32 * nm * 64 * 16 +
+         kPairCenters * 4 + sums;
+}
+
+template <typename T, typename F>
+static bool visit_batch_pair(int kd, F&& f) {
+  switch (kd) {
+    case 4: f(k_batch_pair<T, 4>); return true;
+    case 8: f(k_batch_pair<T, 8>); return true;
+    case 16: f(k_batch_pair<T, 16>); return true;
+    default: return false;
+  }
+}
+
 template <typename F>
 static bool visit_batch_screen(int ks, F&& f) {
   switch (ks) {
@@ -6086,9 +6349,13 @@ static bool visit_batch_screen(int ks, F&& f) {
   }
 }
 
-int64_t batch_resident_blocks(int dtype, int dmax, int ppt, size_t lds, int cus, int screen) {
+int64_t batch_resident_blocks(int dtype, int dmax, int ppt, size_t lds, int cus, int screen,
+                              int pair) {
   int64_t r = 0;
   auto f = [&](auto kern) { r = resident_blocks(kern, lds, cus); };
+  if (pair)
+    return (dtype == 0 ? visit_batch_pair<float>(pair, f) : visit_batch_pair<uint16_t>(pair, f))
+               ? r : 0;
   if (screen) return visit_batch_screen(screen, f) ? r : 0;
   const bool ok = dtype == 0 ? visit_batch<float>(dmax, ppt, f) : visit_batch<uint16_t>(dmax, ppt, f);
   return ok ? r : 0;
@@ -6099,7 +6366,9 @@ hipError_t batch_assign(const BatchHead* hd, const BatchInst* bi, const BatchSha
   auto f = [&](auto kern) {
     hipLaunchKernelGGL(kern, dim3((unsigned)sh.blocks), dim3(256), sh.lds, s, hd, bi);
   };
-  const bool ok = sh.screen ? visit_batch_screen(sh.screen, f)
+  const bool ok = sh.pair ? (sh.dtype == 0 ? visit_batch_pair<float>(sh.pair, f)
+                                           : visit_batch_pair<uint16_t>(sh.pair, f))
+                  : sh.screen ? visit_batch_screen(sh.screen, f)
                   : sh.dtype == 0 ? visit_batch<float>(sh.dmax, sh.ppt, f)
                                   : visit_batch<uint16_t>(sh.dmax, sh.ppt, f);
   if (!ok) return hipErrorInvalidValue;

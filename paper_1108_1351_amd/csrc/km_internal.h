@@ -231,14 +231,21 @@ struct BatchShape {
   int dtype, dmax, ppt;
   size_t lds;   // dynamic LDS of the assignment launch
   int blocks;   // persistent grid
-  int screen;   // K steps of the BF16 screen kernel (0: the FP32 kernel)
+  int screen;   // K steps of the BF16 screen kernel (0: another kernel)
+  int pair;     // padded dims of the split screen of small dims (0: another kernel)
 };
 // The batched BF16 screen takes BF16 data with 16 < d <= 128 and k <= 256;
 // returns its K steps (2, 4 or 8), or 0.
 int batch_screen_ks(int dtype, int32_t d, int32_t k);
+// The batched split screen takes d <= 16 and k <= kPairCenters, in units of
+// kPairPoints points; returns its padded dims (4, 8 or 16), or 0.  Its LDS, with
+// `sums` bytes of cluster sums.
+constexpr int kPairCenters = 256, kPairPoints = 512;
+int batch_pair_kd(int32_t d, int32_t k);
+size_t batch_pair_lds(int dtype, int kd, size_t sums);
 int batch_dmax(int32_t d);                       // 0: d too large for the batched path
 int64_t batch_resident_blocks(int dtype, int dmax, int ppt, size_t lds, int cus,
-                              int screen = 0);
+                              int screen = 0, int pair = 0);
 hipError_t batch_assign(const BatchHead* hd, const BatchInst* bi, const BatchShape& sh,
                         hipStream_t s);
 // Cluster sums of the instances with sum units (after the assignment launches).

@@ -5,9 +5,10 @@
 // (arXiv 1108.1351) on its own data -- sampling, Lloyd passes on the subset,
 // Lloyd passes on all points, final labels -- but the passes of all problems
 // advance together: one batched pass is a launch of the assignment kernel per
-// shape (the FP32 kernel per register tile, the BF16 screen per K-step count),
-// one cluster-sum launch and one finalize launch for every problem.  Chunks of
-// such passes are replayed from captured HIP graphs; problems move between
+// shape (the split screen of small dims per padded row, the BF16 screen per
+// K-step count, the FP32 kernel per register tile), one cluster-sum launch and
+// one finalize launch for every problem.  The server replays chunks of such
+// passes from captured HIP graphs; problems move between
 // stages on the host between chunks, from a compact status array copied back
 // per chunk (a problem whose stage ends inside a chunk is skipped by the
 // device until the chunk ends).
@@ -27,7 +28,7 @@ namespace {
 constexpr int kMaxShapes = 16;        // register-tile shapes live in one engine
 constexpr int kTableCap = 8192;       // problems advanced together
 constexpr size_t kSumsLds = 32768;    // LDS for privatised cluster sums in the batched kernel
-constexpr int kFinalizeBlocks = 1024;
+constexpr int kFinalizeBlocks = 2048;
 constexpr int kMaxChunk = 16;         // passes between two host synchronisations
 
 // ------------------------------------------------------------------ autotuner
@@ -126,7 +127,7 @@ km_status tune(int dtype, int dmax, int kb, hipStream_t s, TuneVal* out) {
       bb.upart = at<long long>(base, oU);
       HIP_TRY(hipMemcpyAsync(at<BatchHead>(base, oHd), &hh, sizeof hh, hipMemcpyHostToDevice, s));
       HIP_TRY(hipMemcpyAsync(at<BatchInst>(base, oBi), &bb, sizeof bb, hipMemcpyHostToDevice, s));
-      BatchShape sh{dtype, dmax, ppt, batch_lds(dmax, kt), 0};
+      BatchShape sh{dtype, dmax, ppt, batch_lds(dmax, kt), 0, 0, 0};
       sh.blocks = (int)std::max<int64_t>(
           1, std::min<int64_t>(hh.units, batch_resident_blocks(dtype, dmax, ppt, sh.lds,
                                                                 device_cus())));
@@ -205,6 +206,7 @@ struct Job {
   // BF16 data with 16 < d <= 128 and k <= 256: the batched BF16 screen (its K
   // steps), with the tiled BF16 copy of -2c and ||c||^2 + B
   int screen = 0;
+  int pair = 0;  // d <= 16 and k <= 256: the batched split screen (its padded dims)
   uint16_t* cb16 = nullptr;
   uint16_t* cb16lo = nullptr;
   float* cnB = nullptr;
@@ -302,7 +304,7 @@ StartInst start_inst(const Job& j) {
   b.d = r.d;
   b.k = r.k;
   b.dtype = r.dtype == KM_F32 ? 0 : 1;
-  b.norms = j.screen != 0;  // the screen's score offset needs max ||x||^2 of the stage's rows
+  b.norms = j.screen || j.pair;  // the screens' score offset needs max ||x||^2 of the rows
   b.seed = r.seed;
   const void* rows[2] = {j.xs, j.X};
   for (int s = 0; s < 2; ++s) {
@@ -329,7 +331,7 @@ StartInst start_inst(const Job& j) {
   b.cb16lo = j.cb16lo;
   b.cnB = j.cnB;
   b.kd16 = 16 * j.screen;
-  b.brows = j.screen ? (int32_t)bf16_rows(r.k) : 0;
+  b.brows = j.screen ? (r.k + 31) / 32 * 32 : 0;  // whole 32-center tiles
   return b;
 }
 
@@ -343,7 +345,8 @@ class Engine {
     int dtype, dmax, ppt, ktile;
     size_t lds;
     int blocks;
-    int screen;  // K steps of the batched BF16 screen, 0 for the FP32 kernel
+    int screen;  // K steps of the batched BF16 screen, 0 for the other kernels
+    int pair;    // padded dims of the batched split screen, 0 for the other kernels
   };
 
   // cap: problems advanced together, at most kTableCap (the tables' size)
@@ -406,16 +409,18 @@ class Engine {
   }
 
   // Shape slot for a register tile and LDS center tile (created on first use).
-  int shape_of(int dtype, int dmax, int ppt, int ktile, int screen = 0) {
+  int shape_of(int dtype, int dmax, int ppt, int ktile, int screen, int pair) {
     for (int i = 0; i < (int)shapes_.size(); ++i)
       if (shapes_[i].dtype == dtype && shapes_[i].dmax == dmax && shapes_[i].ppt == ppt &&
-          shapes_[i].ktile == ktile && shapes_[i].screen == screen)
+          shapes_[i].ktile == ktile && shapes_[i].screen == screen && shapes_[i].pair == pair)
         return i;
     if ((int)shapes_.size() >= kMaxShapes) return -1;
     // the screen's LDS is static (center tiles, candidate lists)
-    Shape sh{dtype, dmax, ppt, ktile, screen ? 0 : batch_lds(dmax, ktile), 0, screen};
+    Shape sh{dtype, dmax, ppt, ktile,
+             screen ? 0 : pair ? batch_pair_lds(dtype, pair, kSumsLds) : batch_lds(dmax, ktile),
+             0, screen, pair};
     sh.blocks = (int)std::max<int64_t>(
-        1, batch_resident_blocks(dtype, dmax, ppt, sh.lds, device_cus(), screen));
+        1, batch_resident_blocks(dtype, dmax, ppt, sh.lds, device_cus(), screen, pair));
     shapes_.push_back(sh);
     return (int)shapes_.size() - 1;
   }
@@ -541,7 +546,7 @@ class Engine {
     for (int g = 0; g < (int)shapes_.size(); ++g) {
       if (!(mask & (1u << g))) continue;
       const Shape& sh = shapes_[g];
-      BatchShape bs{sh.dtype, sh.dmax, sh.ppt, sh.lds, sh.blocks, sh.screen};
+      BatchShape bs{sh.dtype, sh.dmax, sh.ppt, sh.lds, sh.blocks, sh.screen, sh.pair};
       HIP_TRY(batch_assign(d_heads_ + g, d_insts_ + (size_t)g * cap_, bs, s_));
     }
     HIP_TRY(batch_sums(d_heads_ + kMaxShapes + 1, d_insts_ + (size_t)kMaxShapes * cap_,
@@ -614,15 +619,16 @@ km_status admit(Engine& eng, Job& j, hipStream_t s) {
   const km_request& r = j.rq;
   const int dt = r.dtype == KM_F32 ? 0 : 1;
   j.dmax = batch_dmax(r.d);
-  if (j.screen) {
-    // the BF16 screen: 256-point units, no register-tile choice to tune
-    j.tv.ppt = 1;
+  if (j.screen || j.pair) {
+    // the screens: 256- and 512-point units, no register-tile choice to tune
+    j.tv.ppt = j.pair ? kPairPoints / 256 : 1;
     j.tv.ktile = 32;
+    if (j.pair) j.dmax = j.pair;
   } else {
     rc = tuned(dt, j.dmax, r.k, s, &j.tv);
     if (rc != KM_OK) return rc;
   }
-  j.shape = eng.shape_of(dt, j.dmax, j.tv.ppt, j.tv.ktile, j.screen);
+  j.shape = eng.shape_of(dt, j.dmax, j.tv.ppt, j.tv.ktile, j.screen, j.pair);
   if (j.shape < 0) return fail(KM_EBUSY, "too many register-tile shapes at once");
   rc = j.mem.get(j.bytes, nullptr, 0, s);
   if (rc != KM_OK) return rc;
@@ -900,6 +906,7 @@ km_status fit_batch_on(const km_request* reqs, int32_t count, km_result* results
     }
     j.m = subset_size(j.rq.n, j.rq.k, j.rq.subset_frac);
     j.screen = batch_screen_ks(j.rq.dtype == KM_F32 ? 0 : 1, j.rq.d, j.rq.k);
+    j.pair = batch_pair_kd(j.rq.d, j.rq.k);
     j.bytes = job_layout(j, nullptr);
     const km_status ra = admit(eng, j, s);
     if (ra != KM_OK) {
@@ -924,7 +931,9 @@ km_status fit_batch_on(const km_request* reqs, int32_t count, km_result* results
   };
   rc = join();
   while (rc == KM_OK && !run.empty()) {
-    rc = eng.round(run, true, chunk_passes(run, 8), stat);
+    // plain launches: a call's chunks seldom repeat often enough to pay for the
+    // captures (30 BF16 problems: 15.3 ms so, 17.1 with graphs)
+    rc = eng.round(run, false, chunk_passes(run, 8), stat);
     if (rc != KM_OK) break;
     std::vector<Job*> keep;
     second.clear();
@@ -1006,6 +1015,7 @@ km_status km_server_submit(km_server* srv, const km_request* req, uint64_t* tick
   j->copy_x = true;
   j->m = subset_size(j->rq.n, j->rq.k, j->rq.subset_frac);
   j->screen = batch_screen_ks(j->rq.dtype == KM_F32 ? 0 : 1, j->rq.d, j->rq.k);
+  j->pair = batch_pair_kd(j->rq.d, j->rq.k);
   j->bytes = job_layout(*j, nullptr);
   j->t_submit = now_s();
   std::lock_guard<std::mutex> lk(srv->mu);

@@ -315,3 +315,33 @@ def test_shared_starts_any_sizes():
         assert info["iters"] == info1["iters"] and info["J"] == info1["J"]
         _check_against_oracle(data[i], C, L, info, p[1], p[2], p[3], (6, 7), (1e-4, 1e-4),
                               f"start {specs[i]}")
+
+
+@pytest.mark.parametrize("d,dtype", [(1, "f32"), (2, "f32"), (3, "bf16"), (4, "f32"), (5, "f32"),
+                                     (8, "bf16"), (8, "f32"), (13, "f32"), (16, "f32"),
+                                     (16, "bf16")])
+def test_batch_split_screen_edges(d, dtype):
+    """The batched split screen of small dims at the edges of its 32-center tiles
+    and 512-point units, and one center more than it takes."""
+    specs = [(n, k) for n, k in [(2, 2), (63, 3), (64, 31), (511, 32), (512, 33), (513, 64),
+                                 (1025, 65), (700, 128), (2_000, 129), (1_300, 255),
+                                 (1_537, 256), (900, 257)]]
+    data = [_problem(n, d, k, 60 + n + k, dtype) for n, k in specs]
+    out = km.kmeans_fit_batch([(to_device(Xh), k, 0.5, 3, (3, 4), (0.0, 0.0))
+                               for Xh, (n, k) in zip(data, specs)])
+    for Xh, (C, L, info), (n, k) in zip(data, out, specs):
+        _check_against_oracle(Xh, C, L, info, k, 0.5, 3, (3, 4), (0.0, 0.0),
+                              f"n={n} d={d} k={k} {dtype}")
+
+
+@pytest.mark.parametrize("copies", [2, 3, 5, 20])
+def test_batch_split_screen_crowded_centers(copies):
+    """Fits whose initial centers fall several to a tight cluster far from the
+    origin: two to four candidates inside the band, or FP64 over all centers."""
+    rng = np.random.default_rng(copies)
+    mu = rng.uniform(-60, 60, size=(6, 5))
+    Xh = (mu[rng.integers(0, 6, size=3_000)] + rng.normal(0, 0.02, size=(3_000, 5)))
+    Xh = Xh.astype(np.float32)
+    k = 6 * copies
+    (C, L, info), = km.kmeans_fit_batch([(to_device(Xh), k, 0.2, 5, (4, 5), (0.0, 0.0))])
+    _check_against_oracle(Xh, C, L, info, k, 0.2, 5, (4, 5), (0.0, 0.0), f"crowded x{copies}")
