@@ -4369,6 +4369,157 @@ __device__ void finalize_center(
   __syncthreads();  // the shared arrays may be reused by a following call
 }
 
+// As finalize_center for d < 256 dims, several centers a block: thread c of the
+// block owns column c of the block's part of the slot rows (dim or count of one
+// of its centers), or 1/sgn of its slot rows, eight in flight; 16 lanes a center
+// then add its movement, norm and rounding error.  A block adds to the pass's
+// ticket once (a returning atomic on one address takes about 30 ns, so one per
+// center was the larger part of a launch of many centers), and without an update
+// (a batched labelling pass) the first block only concludes.
+// Latency-bound like finalize_center.  Whole calls, one block per center against
+// groups: 139 -> 110 us (one pass of 10K x 17), 6.6 -> 5.6 ms (30 FP32 problems
+// of 2 to 16 dims), 15.9 -> 14.6 ms (30 BF16 problems of 32 and 128 dims).
+__device__ void finalize_group(
+    int g, long long* __restrict__ slots, long long* __restrict__ jslots, int k, int d,
+    PassState* __restrict__ st, int update, double* __restrict__ c64, float* __restrict__ cw,
+    float* __restrict__ cn, double* __restrict__ cnorm, double* __restrict__ shiftj,
+    int32_t* __restrict__ emptyj, double* __restrict__ S_out, int64_t* __restrict__ N_out,
+    uint16_t* __restrict__ cb16, float* __restrict__ cnB, int kd16,
+    const double* __restrict__ Jpart, const long long* __restrict__ upart, int64_t nb,
+    double* __restrict__ J_hist, double* __restrict__ shift_hist, bool mark_labelled,
+    bool biased, double* __restrict__ trace_c, long long* __restrict__ trace_n,
+    uint16_t* __restrict__ cb16lo, int nslots) {
+  __shared__ long long part[256], tot[256];
+  __shared__ double rs[256], rn[256], re[256], gsh[128], gnn[128], gmax[16];
+  __shared__ int last;
+  const int tid = threadIdx.x;
+  if (!update) {
+    if (g == 0) {
+      conclude_block(st, Jpart, upart, nb, jslots, shiftj, cnorm, emptyj, k, false, J_hist,
+                     shift_hist, mark_labelled);
+      __syncthreads();
+    }
+    return;
+  }
+  const int W = d + 1, sgn = finalize_split(d, nslots), nc = 256 / sgn, cpb = nc / W;
+  const int j0 = g * cpb, nj = min(cpb, k - j0);
+  const int col = tid % nc, sg = tid / nc, jl = col / W, t = col - jl * W;
+  const bool in = col < nj * W, dim = in && t < d;
+  const int j = j0 + jl;
+  const int64_t C = (int64_t)k * W;
+  const int64_t it = st->iter;
+  const int F = st->F;
+  const float B = st->B;
+  long long* base = slots + (int64_t)j0 * W + col;
+  double cold = 0.0;
+  if (dim && sg == 0) cold = c64[(int64_t)j * d + t];
+  long long sv = 0;
+  if (in)
+    for (int r0 = sg; r0 < nslots; r0 += 8 * sgn) {
+      long long v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        v[u] = r0 + u * sgn < nslots ? base[(int64_t)(r0 + u * sgn) * C] : 0;
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        sv += v[u];
+        if (r0 + u * sgn < nslots) base[(int64_t)(r0 + u * sgn) * C] = 0;
+      }
+    }
+  part[tid] = sv;
+  __syncthreads();
+  if (tid < nc) {
+    for (int s = 1; s < sgn; ++s) sv += part[tid + s * nc];
+    tot[tid] = sv;
+  }
+  __syncthreads();
+  if (tid < nc && dim) {
+    const long long Nj = tot[jl * W + d];
+    // biased sums: every point added kSumBias + q (mod 2^64)
+    if (biased) sv = (long long)((unsigned long long)sv - (unsigned long long)Nj * kSumBias);
+    const double sum = ldexp((double)sv, -F);
+    const int64_t o = (int64_t)j * d + t;
+    if (trace_c) trace_c[it * k * d + o] = cold;
+    const double cnew = Nj > 0 ? sum / (double)Nj : cold;
+    const double diff = cnew - cold;
+    double ee = 0.0;
+    c64[o] = cnew;
+    cw[o] = (float)cnew;
+    if (cb16lo) {
+      uint16_t hi, lo;
+      const double e = bf16_split(cnew, hi, lo);
+      cb16[cb16_at(j, t, kd16)] = hi;
+      cb16lo[cb16_at(j, t, kd16)] = lo;
+      ee = e * e;
+    } else if (cb16) {
+      const uint16_t b = f32_to_bf16((float)(-2.0 * cnew));
+      cb16[cb16_at(j, t, kd16)] = b;
+      const double e = bf16_err(b, cnew);
+      ee = e * e;
+    }
+    rs[tid] = diff * diff;
+    rn[tid] = cnew * cnew;
+    re[tid] = ee;
+    if (S_out) S_out[o] = sum;
+  }
+  __syncthreads();
+  const int li = tid & 15, grp = tid >> 4;
+  double em = 0.0;
+  for (int c = grp; c < nj; c += 16) {
+    double sh = 0.0, nn = 0.0, ee = 0.0;
+    for (int q = li; q < d; q += 16) {
+      sh += rs[c * W + q];
+      nn += rn[c * W + q];
+      ee += re[c * W + q];
+    }
+    for (int o = 8; o > 0; o >>= 1) {
+      sh += __shfl_xor(sh, o);
+      nn += __shfl_xor(nn, o);
+      ee += __shfl_xor(ee, o);
+    }
+    em = fmax(em, ee);
+    if (li == 0) {
+      gsh[c] = sh;
+      gnn[c] = nn;
+    }
+  }
+  if (li == 0) gmax[grp] = em;
+  __syncthreads();
+  // one wave stores what the last block reads, so that its fence covers it (a
+  // fence in all four cost 2 ms of a call over 30 BF16 problems)
+  if (tid < 64)
+    for (int c = tid; c < nj; c += 64) {
+      const double nn = gnn[c];
+      const long long Nj = tot[c * W + d];
+      shiftj[j0 + c] = sqrt(gsh[c]);
+      cn[j0 + c] = (float)nn;
+      cnorm[j0 + c] = sqrt(nn);
+      emptyj[j0 + c] = Nj == 0 ? 1 : 0;
+      if (cnB) cnB[j0 + c] = (float)(nn + (double)B);
+      if (N_out) N_out[j0 + c] = (int64_t)Nj;
+      if (trace_n) trace_n[it * k + j0 + c] = Nj;
+    }
+  if (tid == 0) {
+    if (cb16) {
+      for (int q = 1; q < 16; ++q) em = fmax(em, gmax[q]);
+      dcn_max(st, em);
+    }
+    __threadfence();
+    last = (int)atomicAdd(&st->ticket, (unsigned)nj) + nj == k ? 1 : 0;
+  }
+  __syncthreads();
+  if (last) {
+    __threadfence();
+    conclude_block(st, Jpart, upart, nb, jslots, shiftj, cnorm, emptyj, k, true, J_hist,
+                   shift_hist, mark_labelled);
+    if (tid == 0) {
+      if (cb16) dcn_publish(st);
+      st->ticket = 0u;
+    }
+  }
+  __syncthreads();  // the shared arrays may be reused by a following call
+}
+
 __global__ __launch_bounds__(256) void k_finalize(
     long long* __restrict__ slots, long long* __restrict__ jslots, int k, int d,
     PassState* __restrict__ st, const int32_t* __restrict__ gate, int update,
@@ -4381,9 +4532,14 @@ __global__ __launch_bounds__(256) void k_finalize(
     double* __restrict__ trace_c, long long* __restrict__ trace_n,
     uint16_t* __restrict__ cb16lo, int nslots) {
   if (gated(gate)) return;
-  finalize_center(blockIdx.x, slots, jslots, k, d, st, update, c64, cw, cn, cnorm, shiftj, emptyj,
-                  S_out, N_out, cb16, cnB, kd16, Jpart, upart, nb, J_hist, shift_hist, false,
-                  biased != 0, trace_c, trace_n, cb16lo, nslots);
+  if (finalize_cpb(d, nslots))
+    finalize_group(blockIdx.x, slots, jslots, k, d, st, update, c64, cw, cn, cnorm, shiftj,
+                   emptyj, S_out, N_out, cb16, cnB, kd16, Jpart, upart, nb, J_hist, shift_hist,
+                   false, biased != 0, trace_c, trace_n, cb16lo, nslots);
+  else
+    finalize_center(blockIdx.x, slots, jslots, k, d, st, update, c64, cw, cn, cnorm, shiftj,
+                    emptyj, S_out, N_out, cb16, cnB, kd16, Jpart, upart, nb, J_hist, shift_hist,
+                    false, biased != 0, trace_c, trace_n, cb16lo, nslots);
 }
 
 // ----------------------------------------------------------------------------
@@ -5409,7 +5565,7 @@ __global__ __launch_bounds__(1024, 8) void k_batch_sums(const BatchHead* __restr
   }
 }
 
-// Finalize entries of every listed instance (one per center), persistent.  The
+// Finalize entries of every listed instance (groups of its centers), persistent.  The
 // last entry of an instance concludes its pass (J, movement, stop test).
 __global__ __launch_bounds__(256) void k_batch_finalize(const BatchHead* __restrict__ hd,
                                                         const BatchInst* __restrict__ bi) {
@@ -5419,10 +5575,10 @@ __global__ __launch_bounds__(256) void k_batch_finalize(const BatchHead* __restr
     const BatchInst& b = bi[batch_find(bi, ninst, c, 1)];
     const int dn = ld_agent(&b.st->done);
     if ((b.mode == 1 && dn) || (b.mode == 2 && dn == 2)) continue;
-    finalize_center((int)(c - b.center0), b.slots, nullptr, b.k, b.d, b.st, b.mode == 1 ? 1 : 0,
-                    b.c64, b.cw, b.cn, b.cnorm, b.shiftj, b.emptyj, nullptr, nullptr, b.cb16,
-                    b.cnB, b.kd16, b.Jpart, b.upart, b.units, b.J_hist, b.shift_hist,
-                    b.mode == 2, false, nullptr, nullptr, b.cb16lo, b.nslots);
+    finalize_group((int)(c - b.center0), b.slots, nullptr, b.k, b.d, b.st, b.mode == 1 ? 1 : 0,
+                   b.c64, b.cw, b.cn, b.cnorm, b.shiftj, b.emptyj, nullptr, nullptr, b.cb16,
+                   b.cnB, b.kd16, b.Jpart, b.upart, b.units, b.J_hist, b.shift_hist, b.mode == 2,
+                   false, nullptr, nullptr, b.cb16lo, b.nslots);
   }
 }
 
@@ -6266,7 +6422,8 @@ hipError_t pass_rest(const PassBufs& b, const PassPlan& p, bool update, hipStrea
   const bool sorted = !p.fused && (update || p.bf16 || p.split);
   if (sorted) sorted_update(b, p, update, gate, s);
   if (update) {
-    hipLaunchKernelGGL(k_finalize, dim3((unsigned)b.k), dim3(256), 0, s, b.slots,
+    const int cpb = std::max(1, finalize_cpb(b.d, plan_slots(p)));
+    hipLaunchKernelGGL(k_finalize, dim3((unsigned)((b.k + cpb - 1) / cpb)), dim3(256), 0, s, b.slots,
                        sorted ? b.jslots : nullptr, b.k, b.d, b.st, gate, update ? 1 : 0, b.c64,
                        b.cw, b.cn, b.cnorm, b.shiftj, b.emptyj, b.S_out, b.N_out,
                        copy_hi(b, p), copy16(p) ? b.cnB : nullptr, p.ks * 16,

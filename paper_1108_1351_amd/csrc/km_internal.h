@@ -31,6 +31,17 @@ __host__ __device__ inline int64_t cb16_at(int64_t j, int t, int kd16) {
   return (((j >> 5) * (kd16 >> 3) + (t >> 3)) * 32 + (j & 31)) * 8 + (t & 7);
 }
 
+// The finalize of d < 256 dims: threads per column (slot rows shared between
+// them) and centers per block; 0 centers: one block per center and any d.  Few
+// slot rows (the batched passes) need no sharing; 32 of them are split so that a
+// thread loads eight, as far as the columns of a center leave threads.
+__host__ __device__ inline int finalize_split(int d, int nslots) {
+  return nslots <= 8 || d >= 128 ? 1 : d >= 64 ? 2 : 4;
+}
+__host__ __device__ inline int finalize_cpb(int d, int nslots) {
+  return d < 256 ? 256 / finalize_split(d, nslots) / (d + 1) : 0;
+}
+
 // Progress of one radix selection of the r smallest 64-bit keys.  When done,
 // a key is selected iff its top `bits` bits are <= prefix (keys are distinct).
 struct SelState {
@@ -88,7 +99,7 @@ struct BatchInst {
   int32_t ktile;     // centers per LDS tile of the assignment
   int64_t unit0, units;  // its work units in the assignment grid (tiles of tile_pts points)
   int64_t tile_pts;
-  int64_t center0;       // its first entry in the finalize grid (k entries)
+  int64_t center0;       // its first entry in the finalize grid (groups of finalize_cpb centers)
   double* c64; float* cw; float* cn; double* cnorm; double* shiftj; int32_t* emptyj;
   PassState* st;
   long long* slots;      // [kSlots][k][d+1]
@@ -113,7 +124,7 @@ struct BatchHead {
   int32_t ninst;
   int32_t pad;
   int64_t units;    // sum of the instances' units (assignment) ...
-  int64_t centers;  // ... and of their k (finalize)
+  int64_t centers;  // ... and of their finalize entries
 };
 // One problem of a shared start (sampling, initial centers, stage set-ups).
 struct StartInst {

@@ -500,7 +500,10 @@ class Engine {
         b.nslots = ns;
       }
       units[g] += b.units;
-      centers += b.k;
+      {
+        const int cpb = finalize_cpb(b.d, b.nslots);
+        centers += (b.k + cpb - 1) / cpb;
+      }
       h_insts_[(size_t)g * cap_ + cnt[g]++] = b;
       h_insts_[(size_t)kMaxShapes * cap_ + a] = b;
       mask |= 1u << g;

@@ -640,3 +640,20 @@ def test_row_pieces_any_alignment(d, dtype, offset):
     assert_step(out, Xh, C, ref, jtol=1e-9, name=f"pieces d={d} {dtype} +{offset}")
     lab2, J2, _ = km.km_assign(X, torch.from_numpy(C).cuda())
     assert_step({"labels": lab2, "J": J2}, Xh, C, ref, jtol=1e-9, name="pieces assign")
+
+
+@pytest.mark.parametrize("d", [1, 2, 31, 32, 62, 63, 64, 127, 128, 254, 255, 256])
+@pytest.mark.parametrize("extra", [-1, 0, 1])
+def test_new_centers_grouped_by_block(d, extra):
+    """A pass whose centers fill one block's group of the finalize (the columns
+    of 256 threads, shared by 4, 2 or 1 of them), one less and one more; one
+    cluster is empty and keeps its center."""
+    split = 1 if d >= 128 else 2 if d >= 64 else 4
+    k = max(2, 256 // split // (d + 1) + extra)
+    Xh = _mixture(2_003, d, 20, seed=d)
+    C = _centers_from(Xh, k, seed=d, jitter=0.4)
+    C[k // 2] = 1e4
+    out = km.km_step(to_device(Xh), torch.from_numpy(C).cuda())
+    ref = oracle.step(Xh, C)
+    assert_step(out, Xh, C, ref, jtol=1e-9, name=f"groups d={d} k={k}")
+    assert np.array_equal(out["C_new"].cpu().numpy()[k // 2], C[k // 2])
