@@ -51,6 +51,22 @@ __device__ __forceinline__ int64_t shfl_i64(int64_t v, int src) {
 
 __device__ __forceinline__ bool gated(const int32_t* gate) { return gate && *gate; }
 
+// Waits until the stores and atomics of this wave are performed.  A barrier does
+// not wait for global memory, so where several waves of a block wrote what
+// another block is to read, each of them waits before the barrier that precedes
+// the block's ticket.
+__device__ __forceinline__ void stores_done() {
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+}
+
+// Stores written through to where every block of the kernel sees them.
+__device__ __forceinline__ void st_agent(double* p, double v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void st_agent(int32_t* p, int32_t v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // Loads that bypass this CU's cache (other blocks of the kernel wrote them).
 __device__ __forceinline__ double ld_agent(const double* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -1251,6 +1267,7 @@ __global__ __launch_bounds__(256) void k_lab_total(const int32_t* __restrict__ l
   __syncthreads();
   for (int j = t; j < k; j += 256)
     if (h[j]) atomicAdd(&tot[j], (unsigned long long)h[j]);
+  stores_done();
   __syncthreads();
   if (t == 0) {
     __threadfence();
@@ -4344,21 +4361,20 @@ __device__ void finalize_center(
   const bool new_copy = update && cb16;  // the BF16 copy of this center was rewritten
   if (tid == 0) {
     if (update) {
-      shiftj[j] = sqrt(sh);
+      st_agent(&shiftj[j], sqrt(sh));
+      st_agent(&cnorm[j], sqrt(nn));
+      st_agent(&emptyj[j], Nj == 0 ? 1 : 0);
       cn[j] = (float)nn;
-      cnorm[j] = sqrt(nn);
-      emptyj[j] = Nj == 0 ? 1 : 0;
       if (cnB) cnB[j] = (float)(nn + (double)B);
     }
     if (new_copy) dcn_max(st, ee);
     if (N_out) N_out[j] = (int64_t)Nj;
     if (trace_n) trace_n[it * k + j] = Nj;
-    __threadfence();
+    stores_done();
     last = atomicAdd(&st->ticket, 1u) == (unsigned)(k - 1) ? 1 : 0;
   }
   __syncthreads();
   if (last) {
-    __threadfence();
     conclude_block(st, Jpart, upart, nb, jslots, shiftj, cnorm, emptyj, k, update != 0, J_hist,
                    shift_hist, mark_labelled);
     if (tid == 0) {
@@ -4485,16 +4501,17 @@ __device__ void finalize_group(
   }
   if (li == 0) gmax[grp] = em;
   __syncthreads();
-  // one wave stores what the last block reads, so that its fence covers it (a
-  // fence in all four cost 2 ms of a call over 30 BF16 problems)
+  // One wave stores what the last block reads -- written through, so that the
+  // wave need only wait for its own stores and not write the whole L2 back --
+  // and then takes the ticket.
   if (tid < 64)
     for (int c = tid; c < nj; c += 64) {
       const double nn = gnn[c];
       const long long Nj = tot[c * W + d];
-      shiftj[j0 + c] = sqrt(gsh[c]);
+      st_agent(&shiftj[j0 + c], sqrt(gsh[c]));
+      st_agent(&cnorm[j0 + c], sqrt(nn));
+      st_agent(&emptyj[j0 + c], Nj == 0 ? 1 : 0);
       cn[j0 + c] = (float)nn;
-      cnorm[j0 + c] = sqrt(nn);
-      emptyj[j0 + c] = Nj == 0 ? 1 : 0;
       if (cnB) cnB[j0 + c] = (float)(nn + (double)B);
       if (N_out) N_out[j0 + c] = (int64_t)Nj;
       if (trace_n) trace_n[it * k + j0 + c] = Nj;
@@ -4504,12 +4521,11 @@ __device__ void finalize_group(
       for (int q = 1; q < 16; ++q) em = fmax(em, gmax[q]);
       dcn_max(st, em);
     }
-    __threadfence();
+    stores_done();
     last = (int)atomicAdd(&st->ticket, (unsigned)nj) + nj == k ? 1 : 0;
   }
   __syncthreads();
   if (last) {
-    __threadfence();
     conclude_block(st, Jpart, upart, nb, jslots, shiftj, cnorm, emptyj, k, true, J_hist,
                    shift_hist, mark_labelled);
     if (tid == 0) {
