@@ -209,12 +209,7 @@ km_status run_stage(PassBufs b, const PassPlan& plan, int32_t max_iter, double t
   std::vector<hipEvent_t> ev;
   if (prof)
     for (int32_t i = 0; i < 3 * max_iter; ++i) ev.push_back(take_event());
-  HIP_TRY(stage_reset(b.st, s));
-  HIP_TRY(row_stats(b.X, b.dtype, rows, b.d, wants_norms(plan), b.st, s));
-  HIP_TRY(stage_begin(b.st, max_iter, tol, rows, b.cnorm, b.k, b.d, plan.fused ? 0 : plan.pg, s,
-                      reseed));
-  HIP_TRY(prep_copy(b, plan, s));
-  HIP_TRY(zero_sums(b, plan, s));
+  HIP_TRY(stage_open(b, plan, nullptr, max_iter, tol, reseed, s));
   // Passes go out in chunks (2, 4, 8, then 16), each followed by a copy of the
   // pass state.  One more chunk is queued before the host waits for a chunk's
   // state, so the device does not idle while the host reads it; passes queued
@@ -719,21 +714,14 @@ static km_status one_pass(const void* X, km_dtype dtype, int64_t n, int32_t d, c
   b.st = at<PassState>(base, o_st);
   b.S_out = S;
   b.N_out = N;
-  HIP_TRY(hipMemcpyAsync(b.c64, C, sizeof(double) * k * d, hipMemcpyDeviceToDevice, s));
-  HIP_TRY(prep_centers(b.c64, k, d, b.cw, b.cn, b.cnorm, s));
-  HIP_TRY(stage_reset(b.st, s));
-  HIP_TRY(row_stats(X, b.dtype, n, d, wants_norms(p), b.st, s));
-  HIP_TRY(stage_begin(b.st, 1, 0.0, n, b.cnorm, k, d, p.fused ? 0 : p.pg, s));
-  HIP_TRY(prep_copy(b, p, s));
-  HIP_TRY(zero_sums(b, p, s));
+  b.C_out = C_new;
+  b.label_gate = &b.st->nonfinite;
+  HIP_TRY(stage_open(b, p, C, 1, 0.0, 0, s));
+  // (rows with a NaN or Inf: the pass returns at once and writes no output)
+  HIP_TRY(lloyd_pass(b, p, update, s));
   HIP_TRY(hipMemcpyAsync(&hs, b.st, sizeof hs, hipMemcpyDeviceToHost, s));
   HIP_TRY(hipStreamSynchronize(s));
   if (hs.nonfinite) return fail(KM_EINVAL, "X contains NaN or Inf");
-  HIP_TRY(lloyd_pass(b, p, update, s));
-  if (update && C_new)
-    HIP_TRY(hipMemcpyAsync(C_new, b.c64, sizeof(double) * k * d, hipMemcpyDeviceToDevice, s));
-  HIP_TRY(hipMemcpyAsync(&hs, b.st, sizeof hs, hipMemcpyDeviceToHost, s));
-  HIP_TRY(hipStreamSynchronize(s));
   if (J) *J = hs.J;
   if (shift) *shift = hs.shift;
   if (empty) *empty = hs.empty;

@@ -556,11 +556,39 @@ __device__ __forceinline__ void row_stats_body(const T* __restrict__ X, int64_t 
   }
 }
 
+// What stage_begin takes.
+struct StageBegin {
+  int32_t on, max_iter;
+  double tol;
+  const double* cnorm;
+  int32_t k, reseed;
+  int64_t pg;
+};
+
+__device__ __forceinline__ void begin_state(PassState* __restrict__ st, int32_t max_iter,
+                                            double tol, int64_t rows,
+                                            const double* __restrict__ cnorm, int32_t k,
+                                            int32_t d_, int64_t pg, int reseed);
+
+// With bg.on the last block to finish also begins the stage, which saves a launch
+// (about 5 us of a small call) as long as the blocks' tickets, some 30 ns each,
+// take less: a grid of at most kBeginBlocks.
+constexpr unsigned kBeginBlocks = 64;
 template <typename T, int E>
 __global__ __launch_bounds__(256) void k_row_stats(const T* __restrict__ X, int64_t rows, int d,
                                                    int glog, int norms,
-                                                   PassState* __restrict__ st) {
+                                                   PassState* __restrict__ st, StageBegin bg) {
   row_stats_body<T, E>(X, rows, d, glog, norms, st, blockIdx.x, gridDim.x);
+  if (!bg.on) return;
+  __shared__ int last;
+  if (threadIdx.x == 0) {
+    stores_done();
+    last = atomicAdd(&st->ticket, 1u) == gridDim.x - 1 ? 1 : 0;
+  }
+  __syncthreads();
+  if (!last) return;
+  __threadfence();
+  begin_state(st, bg.max_iter, bg.tol, rows, bg.cnorm, bg.k, d, bg.pg, bg.reseed);
 }
 
 // Calls f with the piece size as a constant.
@@ -574,13 +602,16 @@ static void visit_vec(int dtype, int E, F&& f) {
   }
 }
 
-hipError_t row_stats(const void* X, int dtype, int64_t rows, int32_t d, bool norms,
-                     PassState* st, hipStream_t s) {
+// Statistics of the rows, and with *bg the stage's begin where the grid is small
+// enough for it; bg->on says whether it was.
+static hipError_t row_stats_begin(const void* X, int dtype, int64_t rows, int32_t d, bool norms,
+                                  PassState* st, StageBegin* bg, hipStream_t s) {
   const int E = row_vec(dtype, d, X), glog = row_glog(d, E);
   const int64_t waves = (rows + 4 * (64 >> glog) - 1) / (4 * (64 >> glog));
   const unsigned g = (unsigned)std::max<int64_t>(1, std::min<int64_t>((waves + 3) / 4, 2048));
+  bg->on = bg->cnorm && g <= kBeginBlocks ? 1 : 0;
   auto go = [&](auto kern, auto* x) {
-    hipLaunchKernelGGL(kern, dim3(g), dim3(256), 0, s, x, rows, d, glog, norms ? 1 : 0, st);
+    hipLaunchKernelGGL(kern, dim3(g), dim3(256), 0, s, x, rows, d, glog, norms ? 1 : 0, st, *bg);
   };
   visit_vec(dtype, E, [&](auto e) {
     if (dtype == 0) {
@@ -592,10 +623,16 @@ hipError_t row_stats(const void* X, int dtype, int64_t rows, int32_t d, bool nor
   return hipGetLastError();
 }
 
+hipError_t row_stats(const void* X, int dtype, int64_t rows, int32_t d, bool norms,
+                     PassState* st, hipStream_t s) {
+  StageBegin none{};
+  return row_stats_begin(X, dtype, rows, d, norms, st, &none, s);
+}
+
 // Clears up to three arrays.
-__global__ __launch_bounds__(256) void k_zero_i64(long long* __restrict__ p, int64_t count,
-                                                  long long* __restrict__ q, int64_t qcount,
-                                                  long long* __restrict__ r, int64_t rcount) {
+__device__ __forceinline__ void zero3(long long* __restrict__ p, int64_t count,
+                                      long long* __restrict__ q, int64_t qcount,
+                                      long long* __restrict__ r, int64_t rcount) {
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   const int64_t e0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   for (int64_t e = e0; e < count; e += stride) p[e] = 0;
@@ -603,10 +640,13 @@ __global__ __launch_bounds__(256) void k_zero_i64(long long* __restrict__ p, int
   for (int64_t e = e0; e < rcount; e += stride) r[e] = 0;
 }
 
-hipError_t zero_i64(long long* p, int64_t count, hipStream_t s, long long* q, int64_t qcount,
-                    long long* r, int64_t rcount) {
+__global__ __launch_bounds__(256) void k_zero_i64(long long* __restrict__ p, int64_t count) {
+  zero3(p, count, p, 0, p, 0);
+}
+
+hipError_t zero_i64(long long* p, int64_t count, hipStream_t s) {
   const unsigned g = (unsigned)std::max<int64_t>(1, std::min<int64_t>((count + 255) / 256, 4096));
-  hipLaunchKernelGGL(k_zero_i64, dim3(g), dim3(256), 0, s, p, count, q, qcount, r, rcount);
+  hipLaunchKernelGGL(k_zero_i64, dim3(g), dim3(256), 0, s, p, count);
   return hipGetLastError();
 }
 
@@ -614,7 +654,7 @@ hipError_t zero_i64(long long* p, int64_t count, hipStream_t s, long long* q, in
 __device__ __forceinline__ void prep_center(const double* __restrict__ c64, int32_t k, int32_t d,
                                             float* __restrict__ cw, float* __restrict__ cn,
                                             double* __restrict__ cnorm, int j) {
-  const int lane = threadIdx.x;
+  const int lane = threadIdx.x & 63;
   double acc = 0.0;
   for (int t = lane; t < d; t += 64) {
     const double c = c64[(int64_t)j * d + t];
@@ -726,6 +766,27 @@ __global__ __launch_bounds__(256) void k_stage_begin(PassState* __restrict__ st,
                                                      int32_t k, int32_t d_, int64_t pg,
                                                      int reseed) {
   begin_state(st, max_iter, tol, rows, cnorm, k, d_, pg, reseed);
+}
+
+// Opens a stage in one launch: the first block resets the pass state, every block
+// clears its part of the sums, and with C a wave per center takes the centers
+// over from there.  (With the copy of C, the centers, the reset, the sums and the
+// begin launched apart, and the state read back before the pass as well as after
+// it, a labelling of 1K x 2 took 114 us against 67 now, and a pass of 10K x 17
+// 110 against 79.)
+__global__ __launch_bounds__(256) void k_stage_open(
+    PassState* __restrict__ st, const double* __restrict__ C, double* __restrict__ c64, int32_t k,
+    int32_t d, float* __restrict__ cw, float* __restrict__ cn, double* __restrict__ cnorm,
+    long long* __restrict__ p, int64_t count, long long* __restrict__ q, int64_t qcount,
+    long long* __restrict__ r, int64_t rcount) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) reset_state(st);
+  if (C)
+    for (int64_t j = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); j < k;
+         j += (int64_t)gridDim.x * 4) {
+      for (int t = threadIdx.x & 63; t < d; t += 64) c64[j * d + t] = C[j * d + t];
+      prep_center(C, k, d, cw, cn, cnorm, (int)j);
+    }
+  zero3(p, count, q, qcount, r, rcount);
 }
 
 hipError_t stage_begin(PassState* st, int32_t max_iter, double tol, int64_t rows,
@@ -4230,31 +4291,24 @@ __device__ void conclude_block(PassState* __restrict__ st, const double* __restr
   }
 }
 
-// One block per center: the exact sum of its kSlots slot rows (zeroed for the
-// next pass), then (update) the new center -- the average; an empty cluster
-// keeps its center -- its movement and norm, and the BF16 copy of the screen.
-// With jslots, J is that of the sorted update.  The last block concludes the
-// pass.
-// A chain of dependent memory accesses bounds it (a few hundred kilobytes, but
-// each step waits about a microsecond for the last), so everything a center
-// needs is requested at once: a thread owns dim t0 + tid % DT and every
-// (256 / DT)-th slot row of it (DT the power of two that covers d, at most
-// 256), eight rows in flight; the slot groups are then added by shuffles and
-// through LDS.  (With eight dims a round, each waiting for the last, it took
-// 23.3 us at 64 dims and k = 256 against 15.4 us now, and the batched form 75
-// against 40 us for the 30 problems of 32 and 128 dims it was measured on; a
-// pass of a few dims stays at 7.7 us, the latency of the chain that is left.)
+// Finalize of 256 dims and more, one block per center: the exact sum of its slot
+// rows (zeroed for the next pass), then the new center -- the average; an empty
+// cluster keeps its center -- its movement and norm, and the BF16 copy of the
+// screen.  With jslots, J is that of the sorted update.  The last block concludes
+// the pass.
+// A chain of dependent memory accesses bounds it, so a thread owns dim t0 + tid
+// and requests eight of its slot rows at once (one after the other, a launch of
+// 300 dims and k = 100 took 43 us).
 __device__ void finalize_center(
     int j, long long* __restrict__ slots, long long* __restrict__ jslots, int k, int d,
-    PassState* __restrict__ st, int update, double* __restrict__ c64, float* __restrict__ cw,
+    PassState* __restrict__ st, double* __restrict__ c64, float* __restrict__ cw,
     float* __restrict__ cn, double* __restrict__ cnorm, double* __restrict__ shiftj,
     int32_t* __restrict__ emptyj, double* __restrict__ S_out, int64_t* __restrict__ N_out,
-    uint16_t* __restrict__ cb16, float* __restrict__ cnB, int kd16,
+    double* __restrict__ C_out, uint16_t* __restrict__ cb16, float* __restrict__ cnB, int kd16,
     const double* __restrict__ Jpart, const long long* __restrict__ upart, int64_t nb,
-    double* __restrict__ J_hist, double* __restrict__ shift_hist, bool mark_labelled = false,
-    bool biased = false, double* __restrict__ trace_c = nullptr,
-    long long* __restrict__ trace_n = nullptr, uint16_t* __restrict__ cb16lo = nullptr,
-    int nslots = kSlots) {
+    double* __restrict__ J_hist, double* __restrict__ shift_hist, bool biased,
+    double* __restrict__ trace_c, long long* __restrict__ trace_n,
+    uint16_t* __restrict__ cb16lo, int nslots) {
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int64_t C = (int64_t)k * (d + 1);
   // this pass's index in the stage (the last block of the pass advances it
@@ -4262,112 +4316,82 @@ __device__ void finalize_center(
   const int64_t it = st->iter;
   const int F = st->F;
   const float B = st->B;
-  if (!update) trace_c = nullptr, trace_n = nullptr;
   double* tc = trace_c ? trace_c + (it * k + j) * d : nullptr;
   long long* col = slots + (int64_t)j * (d + 1);
-  __shared__ long long part[256];
   __shared__ long long sN;
   __shared__ double wred[3][4];
   __shared__ int last;
-  int dl = 3;  // at least 8 dims a round: at most 32 slot groups
-  while ((1 << dl) < d && dl < 8) ++dl;
-  const int DT = 1 << dl, SG = 256 >> dl, c = tid & (DT - 1), sg = tid >> dl;
-  const int GW = max(DT, 64);  // stride of the slot groups' partial sums in LDS
   // the points of the cluster (counts of the slot rows)
-  long long cv = 0;
-  if (tid < nslots) cv = col[(int64_t)tid * C + d];
-  double sh = 0.0, nn = 0.0, ee = 0.0;
-  for (int t0 = 0; t0 < d; t0 += DT) {
-    const int t = t0 + c;
-    const bool in = t < d;
-    double cold = 0.0;
-    if (update && sg == 0 && in) cold = c64[(int64_t)j * d + t];
-    long long sv = 0;
-    if (in)
-      for (int r0 = sg; r0 < nslots; r0 += 8 * SG) {
-        long long v[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u)
-          v[u] = r0 + u * SG < nslots ? col[(int64_t)(r0 + u * SG) * C + t] : 0;
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-          sv += v[u];
-          if (r0 + u * SG < nslots) col[(int64_t)(r0 + u * SG) * C + t] = 0;
-        }
-      }
-    for (int o = DT; o < 64; o <<= 1) sv += __shfl_xor(sv, o);
-    if (t0 > 0) __syncthreads();  // part of the previous round was read
-    part[tid] = sv;
-    if (t0 == 0 && wv == 0) {
-      if (tid < nslots) col[(int64_t)tid * C + d] = 0;
-      cv = wave_sum(cv);
-      if (lane == 0) sN = cv;
+  if (wv == 0) {
+    long long cv = 0;
+    if (lane < nslots) {
+      cv = col[(int64_t)lane * C + d];
+      col[(int64_t)lane * C + d] = 0;
     }
-    __syncthreads();
-    if (tid < DT && in) {
-      const long long Nj = sN;
-      sv = part[c];
-      for (int g = GW; g < 256; g += GW) sv += part[g + c];
-      // biased sums: every point added kSumBias + q (mod 2^64)
-      if (biased)
-        sv = (long long)((unsigned long long)sv - (unsigned long long)Nj * kSumBias);
-      const double sum = ldexp((double)sv, -F);
-      if (update) {
-        if (tc) tc[t] = cold;
-        const double cnew = Nj > 0 ? sum / (double)Nj : cold;
-        const double diff = cnew - cold;
-        sh += diff * diff;
-        nn += cnew * cnew;
-        c64[(int64_t)j * d + t] = cnew;
-        cw[(int64_t)j * d + t] = (float)cnew;
-        if (cb16lo) {
-          uint16_t hi, lo;
-          const double e = bf16_split(cnew, hi, lo);
-          cb16[cb16_at(j, t, kd16)] = hi;
-          cb16lo[cb16_at(j, t, kd16)] = lo;
-          ee += e * e;
-        } else if (cb16) {
-          const uint16_t b = f32_to_bf16((float)(-2.0 * cnew));
-          cb16[cb16_at(j, t, kd16)] = b;
-          const double e = bf16_err(b, cnew);
-          ee += e * e;
-        }
-      }
-      if (S_out) S_out[(int64_t)j * d + t] = sum;
-    }
+    cv = wave_sum(cv);
+    if (lane == 0) sN = cv;
   }
+  __syncthreads();
   const long long Nj = sN;
-  if (update) {
-    // lanes past DT hold zeros: the butterfly covers the lanes of the dims
-    for (int o = min(DT, 64) >> 1; o > 0; o >>= 1) {
-      sh += __shfl_xor(sh, o);
-      nn += __shfl_xor(nn, o);
-      ee += __shfl_xor(ee, o);
-    }
-    if (DT > 64) {
-      if (lane == 0) {
-        wred[0][wv] = sh;
-        wred[1][wv] = nn;
-        wred[2][wv] = ee;
-      }
-      __syncthreads();
-      if (tid == 0) {
-        sh = (wred[0][0] + wred[0][1]) + (wred[0][2] + wred[0][3]);
-        nn = (wred[1][0] + wred[1][1]) + (wred[1][2] + wred[1][3]);
-        ee = (wred[2][0] + wred[2][1]) + (wred[2][2] + wred[2][3]);
+  double sh = 0.0, nn = 0.0, ee = 0.0;
+  for (int t = tid; t < d; t += 256) {
+    const double cold = c64[(int64_t)j * d + t];
+    long long sv = 0;
+    for (int r0 = 0; r0 < nslots; r0 += 8) {
+      long long v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = r0 + u < nslots ? col[(int64_t)(r0 + u) * C + t] : 0;
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        sv += v[u];
+        if (r0 + u < nslots) col[(int64_t)(r0 + u) * C + t] = 0;
       }
     }
+    // biased sums: every point added kSumBias + q (mod 2^64)
+    if (biased)
+      sv = (long long)((unsigned long long)sv - (unsigned long long)Nj * kSumBias);
+    const double sum = ldexp((double)sv, -F);
+    if (tc) tc[t] = cold;
+    const double cnew = Nj > 0 ? sum / (double)Nj : cold;
+    const double diff = cnew - cold;
+    sh += diff * diff;
+    nn += cnew * cnew;
+    c64[(int64_t)j * d + t] = cnew;
+    cw[(int64_t)j * d + t] = (float)cnew;
+    if (cb16lo) {
+      uint16_t hi, lo;
+      const double e = bf16_split(cnew, hi, lo);
+      cb16[cb16_at(j, t, kd16)] = hi;
+      cb16lo[cb16_at(j, t, kd16)] = lo;
+      ee += e * e;
+    } else if (cb16) {
+      const uint16_t b = f32_to_bf16((float)(-2.0 * cnew));
+      cb16[cb16_at(j, t, kd16)] = b;
+      const double e = bf16_err(b, cnew);
+      ee += e * e;
+    }
+    if (S_out) S_out[(int64_t)j * d + t] = sum;
+    if (C_out) C_out[(int64_t)j * d + t] = cnew;
   }
-  const bool new_copy = update && cb16;  // the BF16 copy of this center was rewritten
+  sh = wave_sum(sh);
+  nn = wave_sum(nn);
+  ee = wave_sum(ee);
+  if (lane == 0) {
+    wred[0][wv] = sh;
+    wred[1][wv] = nn;
+    wred[2][wv] = ee;
+  }
+  __syncthreads();
   if (tid == 0) {
-    if (update) {
-      st_agent(&shiftj[j], sqrt(sh));
-      st_agent(&cnorm[j], sqrt(nn));
-      st_agent(&emptyj[j], Nj == 0 ? 1 : 0);
-      cn[j] = (float)nn;
-      if (cnB) cnB[j] = (float)(nn + (double)B);
-    }
-    if (new_copy) dcn_max(st, ee);
+    sh = (wred[0][0] + wred[0][1]) + (wred[0][2] + wred[0][3]);
+    nn = (wred[1][0] + wred[1][1]) + (wred[1][2] + wred[1][3]);
+    ee = (wred[2][0] + wred[2][1]) + (wred[2][2] + wred[2][3]);
+    st_agent(&shiftj[j], sqrt(sh));
+    st_agent(&cnorm[j], sqrt(nn));
+    st_agent(&emptyj[j], Nj == 0 ? 1 : 0);
+    cn[j] = (float)nn;
+    if (cnB) cnB[j] = (float)(nn + (double)B);
+    if (cb16) dcn_max(st, ee);
     if (N_out) N_out[j] = (int64_t)Nj;
     if (trace_n) trace_n[it * k + j] = Nj;
     stores_done();
@@ -4375,17 +4399,16 @@ __device__ void finalize_center(
   }
   __syncthreads();
   if (last) {
-    conclude_block(st, Jpart, upart, nb, jslots, shiftj, cnorm, emptyj, k, update != 0, J_hist,
-                   shift_hist, mark_labelled);
+    conclude_block(st, Jpart, upart, nb, jslots, shiftj, cnorm, emptyj, k, true, J_hist,
+                   shift_hist);
     if (tid == 0) {
-      if (new_copy) dcn_publish(st);
+      if (cb16) dcn_publish(st);
       st->ticket = 0u;
     }
   }
-  __syncthreads();  // the shared arrays may be reused by a following call
 }
 
-// As finalize_center for d < 256 dims, several centers a block: thread c of the
+// As finalize_center below 256 dims, several centers a block: thread c of the
 // block owns column c of the block's part of the slot rows (dim or count of one
 // of its centers), or 1/sgn of its slot rows, eight in flight; 16 lanes a center
 // then add its movement, norm and rounding error.  A block adds to the pass's
@@ -4400,7 +4423,7 @@ __device__ void finalize_group(
     PassState* __restrict__ st, int update, double* __restrict__ c64, float* __restrict__ cw,
     float* __restrict__ cn, double* __restrict__ cnorm, double* __restrict__ shiftj,
     int32_t* __restrict__ emptyj, double* __restrict__ S_out, int64_t* __restrict__ N_out,
-    uint16_t* __restrict__ cb16, float* __restrict__ cnB, int kd16,
+    double* __restrict__ C_out, uint16_t* __restrict__ cb16, float* __restrict__ cnB, int kd16,
     const double* __restrict__ Jpart, const long long* __restrict__ upart, int64_t nb,
     double* __restrict__ J_hist, double* __restrict__ shift_hist, bool mark_labelled,
     bool biased, double* __restrict__ trace_c, long long* __restrict__ trace_n,
@@ -4477,6 +4500,7 @@ __device__ void finalize_group(
     rn[tid] = cnew * cnew;
     re[tid] = ee;
     if (S_out) S_out[o] = sum;
+    if (C_out) C_out[o] = cnew;
   }
   __syncthreads();
   const int li = tid & 15, grp = tid >> 4;
@@ -4538,24 +4562,24 @@ __device__ void finalize_group(
 
 __global__ __launch_bounds__(256) void k_finalize(
     long long* __restrict__ slots, long long* __restrict__ jslots, int k, int d,
-    PassState* __restrict__ st, const int32_t* __restrict__ gate, int update,
+    PassState* __restrict__ st, const int32_t* __restrict__ gate,
     double* __restrict__ c64, float* __restrict__ cw, float* __restrict__ cn,
     double* __restrict__ cnorm, double* __restrict__ shiftj, int32_t* __restrict__ emptyj,
     double* __restrict__ S_out, int64_t* __restrict__ N_out,
-    uint16_t* __restrict__ cb16, float* __restrict__ cnB, int kd16,
+    double* __restrict__ C_out, uint16_t* __restrict__ cb16, float* __restrict__ cnB, int kd16,
     const double* __restrict__ Jpart, const long long* __restrict__ upart, int64_t nb,
     double* __restrict__ J_hist, double* __restrict__ shift_hist, int biased,
     double* __restrict__ trace_c, long long* __restrict__ trace_n,
     uint16_t* __restrict__ cb16lo, int nslots) {
   if (gated(gate)) return;
   if (finalize_cpb(d, nslots))
-    finalize_group(blockIdx.x, slots, jslots, k, d, st, update, c64, cw, cn, cnorm, shiftj,
-                   emptyj, S_out, N_out, cb16, cnB, kd16, Jpart, upart, nb, J_hist, shift_hist,
-                   false, biased != 0, trace_c, trace_n, cb16lo, nslots);
+    finalize_group(blockIdx.x, slots, jslots, k, d, st, 1, c64, cw, cn, cnorm, shiftj,
+                   emptyj, S_out, N_out, C_out, cb16, cnB, kd16, Jpart, upart, nb, J_hist,
+                   shift_hist, false, biased != 0, trace_c, trace_n, cb16lo, nslots);
   else
-    finalize_center(blockIdx.x, slots, jslots, k, d, st, update, c64, cw, cn, cnorm, shiftj,
-                    emptyj, S_out, N_out, cb16, cnB, kd16, Jpart, upart, nb, J_hist, shift_hist,
-                    false, biased != 0, trace_c, trace_n, cb16lo, nslots);
+    finalize_center(blockIdx.x, slots, jslots, k, d, st, c64, cw, cn, cnorm, shiftj, emptyj,
+                    S_out, N_out, C_out, cb16, cnB, kd16, Jpart, upart, nb, J_hist, shift_hist,
+                    biased != 0, trace_c, trace_n, cb16lo, nslots);
 }
 
 // ----------------------------------------------------------------------------
@@ -5592,7 +5616,7 @@ __global__ __launch_bounds__(256) void k_batch_finalize(const BatchHead* __restr
     const int dn = ld_agent(&b.st->done);
     if ((b.mode == 1 && dn) || (b.mode == 2 && dn == 2)) continue;
     finalize_group((int)(c - b.center0), b.slots, nullptr, b.k, b.d, b.st, b.mode == 1 ? 1 : 0,
-                   b.c64, b.cw, b.cn, b.cnorm, b.shiftj, b.emptyj, nullptr, nullptr, b.cb16,
+                   b.c64, b.cw, b.cn, b.cnorm, b.shiftj, b.emptyj, nullptr, nullptr, nullptr, b.cb16,
                    b.cnB, b.kd16, b.Jpart, b.upart, b.units, b.J_hist, b.shift_hist, b.mode == 2,
                    false, nullptr, nullptr, b.cb16lo, b.nslots);
   }
@@ -6399,7 +6423,7 @@ static void dispatch_resolve(const PassBufs& b, const PassPlan& p, const int32_t
 }
 
 hipError_t pass_assign(const PassBufs& b, const PassPlan& p, bool update, hipStream_t s) {
-  const int32_t* gate = update ? &b.st->done : nullptr;
+  const int32_t* gate = update ? &b.st->done : b.label_gate;
   if (p.split) {
     if (b.dtype == 0) dispatch_split<float, false>(b, p, gate, s);
     else dispatch_split<uint16_t, false>(b, p, gate, s);
@@ -6418,7 +6442,7 @@ hipError_t pass_assign(const PassBufs& b, const PassPlan& p, bool update, hipStr
 }
 
 hipError_t pass_rest(const PassBufs& b, const PassPlan& p, bool update, hipStream_t s) {
-  const int32_t* gate = update ? &b.st->done : nullptr;
+  const int32_t* gate = update ? &b.st->done : b.label_gate;
   const int64_t nb = p.bf16 ? 2 * p.blocks : p.blocks;
   if (p.split) {
     if (b.dtype == 0) dispatch_resolve<float>(b, p, gate, s);
@@ -6440,8 +6464,8 @@ hipError_t pass_rest(const PassBufs& b, const PassPlan& p, bool update, hipStrea
   if (update) {
     const int cpb = std::max(1, finalize_cpb(b.d, plan_slots(p)));
     hipLaunchKernelGGL(k_finalize, dim3((unsigned)((b.k + cpb - 1) / cpb)), dim3(256), 0, s, b.slots,
-                       sorted ? b.jslots : nullptr, b.k, b.d, b.st, gate, update ? 1 : 0, b.c64,
-                       b.cw, b.cn, b.cnorm, b.shiftj, b.emptyj, b.S_out, b.N_out,
+                       sorted ? b.jslots : nullptr, b.k, b.d, b.st, gate, b.c64,
+                       b.cw, b.cn, b.cnorm, b.shiftj, b.emptyj, b.S_out, b.N_out, b.C_out,
                        copy_hi(b, p), copy16(p) ? b.cnB : nullptr, p.ks * 16,
                        (const double*)b.Jpart, (const long long*)b.upart, nb, b.J_hist,
                        b.shift_hist, (p.fscreen && p.fsplit) ? 1 : 0, b.trace_c, b.trace_n,
@@ -6573,15 +6597,28 @@ hipError_t fill_uniform(void* p, int kind, int64_t count, uint64_t seed, hipStre
   return hipGetLastError();
 }
 
-hipError_t zero_sums(const PassBufs& b, const PassPlan& p, hipStream_t s) {
-  return zero_i64(b.slots, (int64_t)plan_slots(p) * b.k * (b.d + 1), s, b.jslots, kSlots * 2,
-                  b.scnt, sort_claims(p, b.k) ? b.k : 0);
-}
-
 hipError_t prep_copy(const PassBufs& b, const PassPlan& p, hipStream_t s) {
   if (!copy16(p)) return hipSuccess;
   return prep_bf16(b.c64, b.k, b.d, p.ks * 16, b.st, copy_hi(b, p), b.cnB, s, copy_lo(b, p),
                    p.split ? split_rows(b.k) : 0);
+}
+
+hipError_t stage_open(const PassBufs& b, const PassPlan& p, const double* C, int32_t max_iter,
+                      double tol, int reseed, hipStream_t s) {
+  const int64_t count = (int64_t)plan_slots(p) * b.k * (b.d + 1);
+  const int64_t need = std::max<int64_t>((count + 255) / 256, C ? (b.k + 3) / 4 : 1);
+  hipLaunchKernelGGL(k_stage_open, dim3((unsigned)std::min<int64_t>(need, 4096)), dim3(256), 0, s,
+                     b.st, C, b.c64, b.k, b.d, b.cw, b.cn, b.cnorm, b.slots, count, b.jslots,
+                     (int64_t)kSlots * 2, b.scnt, (int64_t)(sort_claims(p, b.k) ? b.k : 0));
+  const int64_t pg = p.fused ? 0 : p.pg;
+  StageBegin bg{0, max_iter, tol, b.cnorm, b.k, reseed, pg};
+  hipError_t e = row_stats_begin(b.X, b.dtype, b.n, b.d, wants_norms(p), b.st, &bg, s);
+  if (e != hipSuccess) return e;
+  if (!bg.on) {
+    e = stage_begin(b.st, max_iter, tol, b.n, b.cnorm, b.k, b.d, pg, s, reseed);
+    if (e != hipSuccess) return e;
+  }
+  return prep_copy(b, p, s);
 }
 
 hipError_t lloyd_pass(const PassBufs& b, const PassPlan& p, bool update, hipStream_t s) {

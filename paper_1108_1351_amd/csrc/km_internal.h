@@ -165,8 +165,7 @@ hipError_t centers_from_rows(const void* X, int64_t nrows, int dtype, int32_t d,
 hipError_t stage_reset(PassState* st, hipStream_t s);
 hipError_t row_stats(const void* X, int dtype, int64_t rows, int32_t d, bool norms,
                      PassState* st, hipStream_t s);
-hipError_t zero_i64(long long* p, int64_t count, hipStream_t s, long long* q = nullptr,
-                    int64_t qcount = 0, long long* r = nullptr, int64_t rcount = 0);
+hipError_t zero_i64(long long* p, int64_t count, hipStream_t s);
 // cb16lo: when given, -2c is kept as hi + lo (the rest rounded to BF16 again);
 // rows: padded rows of the copy (0: bf16_rows(k))
 hipError_t prep_bf16(const double* c64, int32_t k, int32_t d, int kd16, PassState* st,
@@ -200,6 +199,8 @@ struct PassBufs {
   PassState* st;
   double* J_hist; double* shift_hist;
   double* S_out; int64_t* N_out;   // optional exact sums / counts of the pass
+  double* C_out;                   // optional second copy of the new centers
+  const int32_t* label_gate;       // optional: nonzero, a labelling pass returns at once
   // optional per-pass trace, indexed by the stage's pass: the centers a pass
   // starts from ([pass][k][d]) and its cluster sizes ([pass][k])
   double* trace_c; long long* trace_n;
@@ -282,7 +283,10 @@ PassPlan plan_pass(int64_t rows, int32_t d, int32_t k, int dtype, int precision,
                    size_t lds_limit, int cus);
 // Clears the sums the plan's passes add into (slot rows, J limbs, label totals),
 // and writes its BF16 center copy.
-hipError_t zero_sums(const PassBufs& b, const PassPlan& p, hipStream_t s);
+// A stage's set-up: pass state, sums, row statistics, scale, the screens' center
+// copy; with C the centers are taken from there first.
+hipError_t stage_open(const PassBufs& b, const PassPlan& p, const double* C, int32_t max_iter,
+                      double tol, int reseed, hipStream_t s);
 hipError_t prep_copy(const PassBufs& b, const PassPlan& p, hipStream_t s);
 hipError_t lloyd_pass(const PassBufs& b, const PassPlan& p, bool update, hipStream_t s);
 // the assignment kernel of a pass (for the BF16 path, its screen of all points), and

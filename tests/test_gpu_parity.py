@@ -657,3 +657,43 @@ def test_new_centers_grouped_by_block(d, extra):
     ref = oracle.step(Xh, C)
     assert_step(out, Xh, C, ref, jtol=1e-9, name=f"groups d={d} k={k}")
     assert np.array_equal(out["C_new"].cpu().numpy()[k // 2], C[k // 2])
+
+
+@pytest.mark.parametrize("n", [1, 65_536, 65_537, 70_001])
+@pytest.mark.parametrize("d,k", [(2, 3), (2, 90)])
+def test_stage_begun_by_last_statistics_block(n, d, k):
+    """Passes whose row statistics just fit the grid that begins the stage itself,
+    and one row more."""
+    Xh = _mixture(n, d, 5, seed=n)
+    Xh[-1] *= 3.0  # (the largest element in the last block)
+    C = _centers_from(Xh, k, seed=k, jitter=0.4)
+    out = km.km_step(to_device(Xh), torch.from_numpy(C).cuda())
+    assert_step(out, Xh, C, oracle.step(Xh, C), jtol=1e-9, name=f"begin n={n} d={d} k={k}")
+
+
+@pytest.mark.parametrize("d,k,dtype", [(2, 3, "f32"), (16, 64, "f32"), (64, 200, "f32"),
+                                       (300, 5, "f32"), (100, 300, "bf16"), (16, 1024, "bf16")])
+@pytest.mark.parametrize("n", [700, 70_001])
+def test_refused_rows_leave_outputs_alone(d, k, dtype, n):
+    """A NaN in the last row: km_step and km_assign return KM_EINVAL and write none
+    of their device outputs."""
+    import ctypes
+    X = to_device(_mixture(n, d, 5, seed=d, dtype=dtype))
+    X[-1, -1] = float("nan")
+    C = torch.randn(k, d, dtype=torch.float64, device="cuda")
+    code, lib = 0 if dtype == "f32" else 1, km.load()
+    lab = torch.full((n,), -7, dtype=torch.int32, device="cuda")
+    S, Cn = (torch.full((k, d), -7.0, dtype=torch.float64, device="cuda") for _ in range(2))
+    N = torch.full((k,), -7, dtype=torch.int64, device="cuda")
+    J, sh, em, un = ctypes.c_double(), ctypes.c_double(), ctypes.c_int32(), ctypes.c_int64()
+    stream = torch.cuda.current_stream().cuda_stream
+    torch.cuda.synchronize()
+    rc = lib.km_step(X.data_ptr(), code, n, d, C.data_ptr(), k, 0, lab.data_ptr(), S.data_ptr(),
+                     N.data_ptr(), Cn.data_ptr(), ctypes.byref(J), ctypes.byref(sh),
+                     ctypes.byref(em), ctypes.byref(un), stream)
+    assert rc == km.KM_EINVAL
+    rc = lib.km_assign(X.data_ptr(), code, n, d, C.data_ptr(), k, 0, lab.data_ptr(),
+                       ctypes.byref(J), ctypes.byref(un), stream)
+    assert rc == km.KM_EINVAL
+    for t in (lab, S, Cn, N):
+        assert bool((t == -7).all())
