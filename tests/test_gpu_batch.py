@@ -345,3 +345,16 @@ def test_batch_split_screen_crowded_centers(copies):
     k = 6 * copies
     (C, L, info), = km.kmeans_fit_batch([(to_device(Xh), k, 0.2, 5, (4, 5), (0.0, 0.0))])
     _check_against_oracle(Xh, C, L, info, k, 0.2, 5, (4, 5), (0.0, 0.0), f"crowded x{copies}")
+
+
+@pytest.mark.parametrize("d", [17, 31, 32, 33, 63, 64, 65, 100, 127, 128])
+def test_batch_bf16_screen_row_lengths(d):
+    """J, labels and centers of the batched BF16 screen for rows that fill their
+    lanes and rows that do not, at ragged last units."""
+    specs = [(5, 2), (255, 4), (257, 33), (1_030, 256)]
+    data = [_problem(n, d, k, 80 + n + k, "bf16") for n, k in specs]
+    out = km.kmeans_fit_batch([(to_device(Xh), k, 1.0, 3, (3, 4), (0.0, 0.0))
+                               for Xh, (n, k) in zip(data, specs)])
+    for Xh, (C, L, info), (n, k) in zip(data, out, specs):
+        _check_against_oracle(Xh, C, L, info, k, 1.0, 3, (3, 4), (0.0, 0.0),
+                              f"n={n} d={d} k={k} bf16")
