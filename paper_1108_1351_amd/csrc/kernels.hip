@@ -5334,10 +5334,14 @@ __global__ __launch_bounds__(256, 3) void k_batch_screen(const BatchHead* __rest
     }
     // Candidates of pair points join the lists (a full point's list was filled
     // by the second sweep).  The listed points (one to kBatchCands candidates)
-    // are then decided in FP64 by groups of 16 lanes, one point per group at a
-    // time: lane l of a group holds dims 8l .. 8l+7 of the point and of each
-    // candidate row, so both are read as whole rows; the 16 partial sums are
-    // added in a fixed tree.  Lowest index on equal distances.
+    // are then decided in FP64 by groups of C8 lanes, one point per group at a
+    // time: lane l of a group holds dims 8l .. 8l+7 of the point and of a
+    // candidate row (two at once up to 64 dims), so all are read as whole rows;
+    // the partial sums are added in a fixed tree.  Lowest index on equal
+    // distances.  (16 lanes a point whatever its length took 51 us a launch
+    // over the problems of 32 dims against 41 now; four rows at once 44 us, and
+    // at 128 dims more than one costs: 78 us with one, 83 with two, 89 with
+    // four.)
     __shared__ uint8_t lpts[4][64];
     __shared__ uint8_t blab[4][64];
     __shared__ int lcnt[4];
@@ -5367,9 +5371,10 @@ __global__ __launch_bounds__(256, 3) void k_batch_screen(const BatchHead* __rest
       __builtin_amdgcn_wave_barrier();
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
       const int nl = lcnt[wave];
-      const int grp = lane >> 4, sub = lane & 15, t0 = 8 * sub;
+      constexpr int R = KS < 8 ? 2 : 1, PS = 64 / C8;
+      const int grp = lane / C8, sub = lane & (C8 - 1), t0 = 8 * sub;
       const int64_t p0w = tile * 256 + (int64_t)wave * 64;
-      for (int l0 = 0; l0 < nl; l0 += 4) {
+      for (int l0 = 0; l0 < nl; l0 += PS) {
         const int li = l0 + grp;
         const bool act = li < nl;
         const int slot = act ? lpts[wave][li] : 0;
@@ -5383,27 +5388,31 @@ __global__ __launch_bounds__(256, 3) void k_batch_screen(const BatchHead* __rest
         for (int o = 32; o > 0; o >>= 1) qn = max(qn, __shfl_xor(qn, o));
         double bd = INFINITY;
         int bj = INT_MAX;
-        for (int q = 0; q < qn; ++q) {
-          const bool use = act && q < cnt;
-          const int j = use ? (int)cand[wave][pp][ps][q] : 0;
-          const double* cj = b.c64 + (int64_t)j * d;
-          double cv[8];
+        for (int q0 = 0; q0 < qn; q0 += R) {
+          int j[R];
+          double cv[R][8];
 #pragma unroll
-          for (int e = 0; e < 8; ++e) cv[e] = cj[t0 + e < d ? t0 + e : 0];
-          double part = 0.0;
+          for (int r = 0; r < R; ++r) {
+            j[r] = act && q0 + r < cnt ? (int)cand[wave][pp][ps][q0 + r] : 0;
+            const double* cj = b.c64 + (int64_t)j[r] * d;
 #pragma unroll
-          for (int e = 0; e < 8; ++e) {
-            const float xv = (e & 1) ? bf16_hi(w4[e >> 1]) : bf16_lo(w4[e >> 1]);
-            const double df = t0 + e < d ? (double)xv - cv[e] : 0.0;
-            part = __builtin_fma(df, df, part);
+            for (int e = 0; e < 8; ++e) cv[r][e] = cj[t0 + e < d ? t0 + e : 0];
           }
-          part += __shfl_xor(part, 8);
-          part += __shfl_xor(part, 4);
-          part += __shfl_xor(part, 2);
-          part += __shfl_xor(part, 1);
-          if (use && (part < bd || (part == bd && j < bj))) {
-            bd = part;
-            bj = j;
+#pragma unroll
+          for (int r = 0; r < R; ++r) {
+            double part = 0.0;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+              const float xv = (e & 1) ? bf16_hi(w4[e >> 1]) : bf16_lo(w4[e >> 1]);
+              const double df = t0 + e < d ? (double)xv - cv[r][e] : 0.0;
+              part = __builtin_fma(df, df, part);
+            }
+#pragma unroll
+            for (int o = C8 / 2; o > 0; o >>= 1) part += __shfl_xor(part, o);
+            if (act && q0 + r < cnt && (part < bd || (part == bd && j[r] < bj))) {
+              bd = part;
+              bj = j[r];
+            }
           }
         }
         if (act && sub == 0) blab[wave][slot] = (uint8_t)(bj < k ? bj : 0);
