@@ -242,12 +242,12 @@ km_status km_probe_mfma_bf16(int32_t iters, double* tflops, void* stream);
  * Many independent problems at once.  Each request is the two-stage method of
  * kmeans_fit on its own data; the passes of all requests advance together,
  * one launch per kernel for all of them (a batched pass), so that many small
- * problems share the GPU instead of each paying its own launches.  FP32 data,
- * and BF16 data with d <= 16, are scored in FP32 with the same certified error
- * bound and FP64 check as kmeans_fit's FP32 kernels; BF16 data with
- * 16 < d <= 128 and k <= 256 on BF16 matrix cores against -2c kept as two BF16
- * parts, with a certified band and FP64 decisions among the candidates inside
- * it.  Labels equal the FP64 argmin except at FP64 ties.  Cluster sums are
+ * problems share the GPU instead of each paying its own launches.  Data with
+ * d <= 16 and k <= 256 (FP32 and BF16), and BF16 data with 16 < d <= 128 and
+ * k <= 256, are scored on BF16 matrix cores against -2c kept as two BF16 parts,
+ * with a certified band and FP64 decisions among the candidates inside it; other
+ * shapes in FP32 with the same certified error bound and FP64 check as
+ * kmeans_fit's FP32 kernels.  Labels equal the FP64 argmin except at FP64 ties.  Cluster sums are
  * exact 64-bit integers; d <= 128.  The FP32 kernel's register tile (points
  * per thread, centers per LDS tile) comes from a built-in autotuner, measured
  * once per (dtype, d bucket, k bucket) and cached for the process.

@@ -4298,7 +4298,7 @@ __device__ void conclude_block(PassState* __restrict__ st, const double* __restr
 // the pass.
 // A chain of dependent memory accesses bounds it, so a thread owns dim t0 + tid
 // and requests eight of its slot rows at once (one after the other, a launch of
-// 300 dims and k = 100 took 43 us).
+// 300 dims and k = 40 took 43 us).
 __device__ void finalize_center(
     int j, long long* __restrict__ slots, long long* __restrict__ jslots, int k, int d,
     PassState* __restrict__ st, double* __restrict__ c64, float* __restrict__ cw,
@@ -5505,7 +5505,7 @@ __global__ __launch_bounds__(256, 3) void k_batch_screen(const BatchHead* __rest
 // 16 waves a block, two blocks a CU, and units of as few as 1024 points (one
 // label group per wave) when the problems are small.  (Four waves a block and
 // 8192 points a unit took 331 us per pass on 30 problems of 1e3 to 1e5 points
-// in 32 and 128 dims, 47 % of a 43.9 ms batch; the batch takes 23.5 ms now.)  The table keeps dim
+// in 32 and 128 dims against 34 now.)  The table keeps dim
 // 8 s + e of a lane's piece s at column e * pieces + s, so the lanes of a point
 // add to consecutive words.
 __global__ __launch_bounds__(1024, 8) void k_batch_sums(const BatchHead* __restrict__ hd,
