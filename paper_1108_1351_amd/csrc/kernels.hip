@@ -3963,7 +3963,11 @@ __global__ __launch_bounds__(256, 2) void k_screen_split(
 #pragma unroll
         for (int t = 0; t < CT; ++t) {
           uint16_t a, b, c;
-          bf16_parts(fminf(cb[t] - B, 1e30f), a, b, c);  // padding rows: 1e30
+          // Padding rows score 1e38 above the point's offset.  Wherever the band is
+          // finite that lies above every center's score: ||c||^2 + ||x||^2 is below
+          // 3.9e37 then (the band holds 8.8 times it), so scores are below 8e37.
+          const bool real = (g * CT + t) * 32 + pc < k;
+          bf16_parts(real ? cb[t] - B : 1e38f, a, b, c);
           u16x8 v = {0, 0, 0, 0, 0, 0, 0, 0};
           if (h) v = (u16x8){a, b, c, 0x3f80, 0x3f80, 0x3f80, 0, 0};
           const v8bf ca = __builtin_bit_cast(v8bf, v);
@@ -4082,8 +4086,11 @@ __global__ __launch_bounds__(256, 2) void k_screen_split(
       if (full) {
         lq[pos] = (uint32_t)i;
         // a center whose exact distance is at most the best's scores at most E2
-        // above the smallest score, whose key is within delta of it
-        label = __float_as_int((v1 + E2 + delta * (2.f * fabsf(v1) + E2)) * 1.0001f) & INT_MAX;
+        // above the smallest score, whose key is within delta of it; without a
+        // finite band scores may be NaN, so no score is below the threshold (a
+        // NaN) and all centers are looked at
+        const float thr = (v1 + E2 + delta * (2.f * fabsf(v1) + E2)) * 1.0001f;
+        label = E2 < INFINITY ? __float_as_int(thr) & INT_MAX : 0x7fc00000;
       }
     }
     // at most 3 x 256 points join between two looks at the count

@@ -697,3 +697,40 @@ def test_refused_rows_leave_outputs_alone(d, k, dtype, n):
     assert rc == km.KM_EINVAL
     for t in (lab, S, Cn, N):
         assert bool((t == -7).all())
+
+
+@pytest.mark.parametrize("e", [40, 44, 46, 47, 48, 50, 53, 56, 58, 59, 60, 61, 62])
+@pytest.mark.parametrize("d,k,dtype", [(20, 900, "f32"), (64, 256, "f32"), (300, 70, "f32"),
+                                       (300, 12, "f32"), (300, 65, "bf16")])
+def test_split_screen_any_d_large_norms(d, k, dtype, e):
+    """Overlapping rows and centers scaled by 2^e: squared norms from 1e25 to
+    beyond FP32.  Labels are the FP64 nearest centers throughout."""
+    n = 3_001
+    rng = np.random.default_rng(d + k)
+    Xh = rng.normal(0, 1.0, size=(n, d)).astype(np.float32)
+    if dtype == "bf16":
+        Xh = (Xh.view(np.uint32) & 0xffff0000).view(np.float32)
+    Xh = Xh * np.float32(2.0 ** e)
+    if dtype == "bf16":
+        Xh = (Xh.view(np.uint32) >> 16).astype(np.uint16)
+    C = rng.normal(0, 0.7, size=(k, d)) * 2.0 ** e
+    lab, J, _ = km.km_assign(to_device(Xh), torch.from_numpy(C).cuda())
+    rlab, D1, _ = oracle.assign(Xh, C)
+    assert np.array_equal(lab.cpu().numpy(), rlab), (e, int((lab.cpu().numpy() != rlab).sum()))
+    assert abs(J - D1.sum()) <= 1e-9 * D1.sum()
+    out = km.km_step(to_device(Xh), torch.from_numpy(C).cuda())
+    assert np.array_equal(out["labels"].cpu().numpy(), rlab), e
+
+
+@pytest.mark.parametrize("e", [44, 50, 56])
+@pytest.mark.parametrize("d,k", [(64, 256), (300, 40)])
+def test_split_screen_any_d_large_norms_fit(d, k, e):
+    """A fit of a mixture scaled by 2^e has the centers, labels and J of the
+    unscaled one, scaled (every value is a multiple of the same power of two)."""
+    Xh = _mixture(4_003, d, k, seed=d + k, spread=3.0)
+    X = to_device(Xh)
+    C, L, info = km.kmeans_fit(X, k, 0.3, 5, 6, 0.0)
+    Cs, Ls, infos = km.kmeans_fit(X * 2.0 ** e, k, 0.3, 5, 6, 0.0)
+    assert torch.equal(Ls, L) and torch.equal(Cs, C * 2.0 ** e)
+    assert info["iters"] == infos["iters"]
+    assert abs(infos["J"] / 4.0 ** e - info["J"]) <= 1e-9 * info["J"]
