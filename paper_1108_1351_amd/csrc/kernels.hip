@@ -77,6 +77,10 @@ __device__ __forceinline__ long long ld_agent(const long long* p) {
 __device__ __forceinline__ int32_t ld_agent(const int32_t* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+// Points in a screen's queue: up to 2^32 - 1 of them.
+__device__ __forceinline__ int64_t queue_length(const PassState* st) {
+  return (int64_t)__hip_atomic_load(&st->qcount, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
 
 // Round to the nearest BF16 (ties to even); inputs are finite.
 __device__ __forceinline__ uint16_t f32_to_bf16(float f) {
@@ -3417,7 +3421,7 @@ __global__ __launch_bounds__(512) void k_rescreen_bf16(
   const int lane = threadIdx.x & 63, h = lane >> 5, pc = lane & 31, wave = threadIdx.x >> 6;
   const int nct = (k + 31) / 32;
   const float cmax = st->cmax;
-  const int64_t count = (int64_t)ld_agent(reinterpret_cast<const int32_t*>(&st->qcount));
+  const int64_t count = queue_length(st);
   const int64_t per_block = 8 * PT * 32;
   const bool vec = (d & 7) == 0 && (reinterpret_cast<uintptr_t>(X) & 15u) == 0;
   int64_t nfull = 0, ncand = 0;
@@ -3745,7 +3749,7 @@ __global__ __launch_bounds__(256, 2) void k_screen_split(
   if (gated(gate)) return;
   // LIST: the points the first sweep queued
   if constexpr (LIST)
-    n = (int64_t)ld_agent(reinterpret_cast<const int32_t*>(&st->qcount));
+    n = queue_length(st);
   constexpr int CMAX = 16;                   // candidates kept per queued point
   __shared__ int cand_n[LIST ? 256 : 1];
   __shared__ uint16_t cand_j[LIST ? 256 * CMAX : 1];

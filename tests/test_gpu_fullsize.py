@@ -132,3 +132,17 @@ def test_full_size_128d_n1e8_bf16():
     # labels at the returned centers agree on the sample as well
     lab3, J3, _ = km.km_assign(Xd, info["centers64"])
     assert_step({"labels": lab3, "J": J3}, sample, C64, ref, jtol=1e-9, name="1e6-row assign")
+
+
+def test_split_screen_queue_beyond_2_31():
+    """More than 2^31 points that all need the split screen's second sweep (five
+    equal nearest centers): every one of them is decided, lowest index first."""
+    n, d, k = (1 << 31) + 70_001, 17, 1200
+    print(f"[full] split screen queue: n={n} d={d} k={k} bf16", flush=True)
+    X = torch.full((n, d), 1.5, dtype=torch.bfloat16, device="cuda")
+    C = 100.0 + 50.0 * torch.rand((k, d), dtype=torch.float64, device="cuda")
+    C[7:12] = 2.0
+    lab, J, unc = km.km_assign(X, C)
+    assert unc >= n
+    assert int(lab.min()) == 7 and int(lab.max()) == 7
+    assert abs(J - n * d * 0.25) <= 1e-9 * n * d * 0.25
