@@ -3743,7 +3743,7 @@ template <typename T, int KC, bool LIST>
 __global__ __launch_bounds__(256, 2) void k_screen_split(
     const T* __restrict__ X, int64_t n, int d, int k, int nq, int bg,
     const uint16_t* __restrict__ cb16, const uint16_t* __restrict__ cb16lo,
-    const float* __restrict__ cnB, const float* __restrict__ cw, const double* __restrict__ c64,
+    const float* __restrict__ cn, const float* __restrict__ cw, const double* __restrict__ c64,
     PassState* __restrict__ st, const int32_t* __restrict__ gate, int32_t* __restrict__ labels,
     uint32_t* __restrict__ queue, double* __restrict__ Jpart, long long* __restrict__ upart) {
   if (gated(gate)) return;
@@ -3874,10 +3874,13 @@ __global__ __launch_bounds__(256, 2) void k_screen_split(
     // rounding of the FP32 sums (any rounding of every addition: nadd at the
     // products' magnitude, and the six parts of the norms joining in the last
     // MFMA, whose other products are zeros), and that
-    // of ||c||^2 from cnB = ||c||^2 + B.  An error of the offset is common to
-    // all scores of the point.
+    // of ||c||^2 to FP32.  An error of the offset is common to all scores of the
+    // point.  (Nothing here grows with the norms of other rows: with ||c||^2
+    // taken from ||c||^2 + B, B above every row's squared norm, one row a
+    // thousand times as long as the rest left every point to the exact
+    // decisions, 4.8 ms for 2e5 x 64, k = 256 against 0.25.)
     auto point_norms = [&]() {
-      const float B = st->B, cmax = st->cmax, dcn = st->dcn * 1.01f;
+      const float cmax = st->cmax, dcn = st->dcn * 1.01f;
 #pragma unroll
       for (int p = 0; p < 2; ++p) {
         const float xn2 = sum_halves(s2[p], h);
@@ -3887,7 +3890,7 @@ __global__ __launch_bounds__(256, 2) void k_screen_split(
         const float xc = xn * cmax, nn = 1.1f * (cmax * cmax + xn2);
         const float e1 = 0x1.03p-23f * (nadd * 2.05f * xc + 8.f * (nn + 2.05f * xc)) +
                          xn * dcn + 2.1f * 0x1p-8f * xr * cmax +
-                         3.f * 0x1p-23f * (B + cmax * cmax) + 1e-30f;
+                         0x1p-23f * cmax * cmax + 1e-30f;
         const float off = xn2 + 1.02f * e1 + (float)(16 * ksl + 16) * 0x1.03p-23f * xn2;
         E2v[p] = 2.01f * e1;
         uint16_t a, b, c;
@@ -3936,7 +3939,7 @@ __global__ __launch_bounds__(256, 2) void k_screen_split(
     for (int g = 0; g < ng; ++g) {
       float cb[CT];
 #pragma unroll
-      for (int t = 0; t < CT; ++t) cb[t] = cnB[(g * CT + t) * 32 + pc];
+      for (int t = 0; t < CT; ++t) cb[t] = cn[min((g * CT + t) * 32 + pc, k - 1)];
 #pragma unroll
       for (int p = 0; p < 2; ++p)
 #pragma unroll
@@ -3962,23 +3965,20 @@ __global__ __launch_bounds__(256, 2) void k_screen_split(
       }
       if (g == 0) point_norms();
       // the norms' MFMA, then the keys of the group's scores
-      {
-        const float B = st->B;
 #pragma unroll
-        for (int t = 0; t < CT; ++t) {
-          uint16_t a, b, c;
-          // Padding rows score 1e38 above the point's offset.  Wherever the band is
-          // finite that lies above every center's score: ||c||^2 + ||x||^2 is below
-          // 3.9e37 then (the band holds 8.8 times it), so scores are below 8e37.
-          const bool real = (g * CT + t) * 32 + pc < k;
-          bf16_parts(real ? cb[t] - B : 1e38f, a, b, c);
-          u16x8 v = {0, 0, 0, 0, 0, 0, 0, 0};
-          if (h) v = (u16x8){a, b, c, 0x3f80, 0x3f80, 0x3f80, 0, 0};
-          const v8bf ca = __builtin_bit_cast(v8bf, v);
+      for (int t = 0; t < CT; ++t) {
+        uint16_t a, b, c;
+        // Padding rows score 1e38 above the point's offset.  Wherever the band is
+        // finite that lies above every center's score: ||c||^2 + ||x||^2 is below
+        // 3.9e37 then (the band holds 8.8 times it), so scores are below 8e37.
+        const bool real = (g * CT + t) * 32 + pc < k;
+        bf16_parts(real ? cb[t] : 1e38f, a, b, c);
+        u16x8 v = {0, 0, 0, 0, 0, 0, 0, 0};
+        if (h) v = (u16x8){a, b, c, 0x3f80, 0x3f80, 0x3f80, 0, 0};
+        const v8bf ca = __builtin_bit_cast(v8bf, v);
 #pragma unroll
-          for (int p = 0; p < 2; ++p)
-            acc[p][t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ca, xa[p], acc[p][t], 0, 0, 0);
-        }
+        for (int p = 0; p < 2; ++p)
+          acc[p][t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ca, xa[p], acc[p][t], 0, 0, 0);
       }
 #pragma unroll
       for (int t = 0; t < CT; ++t)
@@ -6432,7 +6432,7 @@ static void dispatch_split(const PassBufs& b, const PassPlan& p, const int32_t* 
   visit_split<T, LIST>(p.kd, [&](auto kern) {
     hipLaunchKernelGGL(kern, dim3((unsigned)p.blocks), dim3(256), 0, s, (const T*)b.X, b.n, b.d,
                        b.k, p.nt, split_bits(b.k), (const uint16_t*)copy_hi(b, p),
-                       (const uint16_t*)copy_lo(b, p), (const float*)b.cnB, (const float*)b.cw,
+                       (const uint16_t*)copy_lo(b, p), (const float*)b.cn, (const float*)b.cw,
                        (const double*)b.c64, b.st, gate, b.labels, b.perm, b.Jpart, b.upart);
   });
 }

@@ -734,3 +734,23 @@ def test_split_screen_any_d_large_norms_fit(d, k, e):
     assert torch.equal(Ls, L) and torch.equal(Cs, C * 2.0 ** e)
     assert info["iters"] == infos["iters"]
     assert abs(infos["J"] / 4.0 ** e - info["J"]) <= 1e-9 * info["J"]
+
+
+@pytest.mark.parametrize("f", [1e2, 1e3, 1e4, 1e6])
+@pytest.mark.parametrize("d,k,dtype", [(64, 256, "f32"), (300, 40, "f32"), (300, 64, "bf16")])
+def test_split_screen_any_d_one_far_row(d, k, dtype, f):
+    """One row f times as long as the others: labels as the oracle's, and the
+    others' bands stay their own (no more of them are left undecided than
+    without that row, the row itself apart)."""
+    Xh = _mixture(20_011, d, k, seed=d + k, dtype=dtype, spread=50.0)
+    C = _centers_from(Xh, k, seed=k, jitter=0.3)
+    Cd = torch.from_numpy(C).cuda()
+    _, _, calm = km.km_assign(to_device(Xh), Cd)
+    far = widen(Xh)[777] * f
+    far = far.astype(np.float32)
+    Xh[777] = far if dtype == "f32" else (far.view(np.uint32) >> 16).astype(np.uint16)
+    lab, J, unc = km.km_assign(to_device(Xh), Cd)
+    rlab, D1, _ = oracle.assign(Xh, C)
+    assert np.array_equal(lab.cpu().numpy(), rlab)
+    assert abs(J - D1.sum()) <= 1e-9 * D1.sum()
+    assert unc <= calm + 1, (calm, unc)
