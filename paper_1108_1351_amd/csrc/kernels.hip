@@ -3526,6 +3526,9 @@ __device__ __forceinline__ void bf16_parts(float v, uint16_t& a, uint16_t& b, ui
 // Labels of points a screen leaves open are negative: the sign bit and up to four
 // candidate centers of bg bits each (the first one repeated in unused fields).
 __device__ __forceinline__ int open_fields(int bg) { return min(4, 31 / bg); }
+// ... which never reach bit 30 (30 bits at most): it marks points to be decided
+// among all centers.
+constexpr int32_t kAllCenters = (int32_t)0xc0000000u;
 
 // Dims [t0, t0 + 8) of a row, zero from d on.  whole: all eight lie below d
 // (wave-uniform).  FP32 rows load as dwords; BF16 rows as 16-byte pieces when
@@ -3561,23 +3564,56 @@ __device__ __forceinline__ void load8_split(const T* __restrict__ row, int t0, i
   for (int e = 0; e < 8; ++e) v[e] = t0 + e < d ? widen<T>(row[t0 + e]) : 0.f;
 }
 
-// Exact decisions of open points by groups of 16 lanes (8 dims a lane of each
-// 128): direct form in FP32 with its error bound, FP64 when the best two are
+// Dims [t0, t0 + 4) of a row likewise (whole, vec: as above), ...
+template <typename T>
+__device__ __forceinline__ void load4_split(const T* __restrict__ row, int t0, int d, bool whole,
+                                            bool vec, float (&v)[4]) {
+  if constexpr (sizeof(T) == 4) {
+    if (whole) {
+      const f32x4a4 a = *reinterpret_cast<const f32x4a4*>(row + t0);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = a[e];
+      return;
+    }
+  } else if (whole && vec) {
+    const uint2 w = *reinterpret_cast<const uint2*>(row + t0);
+    v[0] = bf16_lo(w.x); v[1] = bf16_hi(w.x); v[2] = bf16_lo(w.y); v[3] = bf16_hi(w.y);
+    return;
+  }
+#pragma unroll
+  for (int e = 0; e < 4; ++e) v[e] = t0 + e < d ? widen<T>(row[t0 + e]) : 0.f;
+}
+// ... and of an FP64 row.
+typedef double f64x2a8 __attribute__((ext_vector_type(2), aligned(8)));
+__device__ __forceinline__ void load4_f64(const double* __restrict__ row, int t0, int d, bool whole,
+                                          double (&v)[4]) {
+  if (whole) {
+    const f64x2a8 a = *reinterpret_cast<const f64x2a8*>(row + t0);
+    const f64x2a8 b = *reinterpret_cast<const f64x2a8*>(row + t0 + 2);
+    v[0] = a.x; v[1] = a.y; v[2] = b.x; v[3] = b.y;
+    return;
+  }
+#pragma unroll
+  for (int e = 0; e < 4; ++e) v[e] = t0 + e < d ? row[t0 + e] : 0.0;
+}
+
+// Exact decisions of open points by groups of 16 lanes (4 dims a lane of each
+// 64): direct form in FP32 with its error bound, FP64 when the best two are
 // closer than that; lowest index among equal distances.
 template <typename T>
 struct Resolver {
   const T* X;
   int d, k;
-  bool vec, cvec;
+  bool vec;
   const float* cw;
   const double* c64;
   float rel, u2c;
-  // FP32 direct form over a lane's 8 ceil(d / 128) terms and four pairwise adds,
+  // FP32 direct form over a lane's 4 ceil(d / 64) terms and four pairwise adds,
   // plus 2 sqrt(D) ||c - cw|| for the rounded center
   __device__ __forceinline__ Resolver(const T* X_, int d_, int k_, bool vec_, const float* cw_,
                                       const double* c64_, float cmax)
-      : X(X_), d(d_), k(k_), vec(vec_), cvec((d_ & 3) == 0), cw(cw_), c64(c64_),
-        rel((float)(8 * ((d_ + 127) / 128) + 6) * 0x1p-24f * 1.01f),
+      : X(X_), d(d_), k(k_), vec(vec_), cw(cw_), c64(c64_),
+        rel((float)(4 * ((d_ + 63) / 64) + 6) * 0x1p-24f * 1.01f),
         u2c(2.f * 0x1p-24f * 1.01f * cmax) {}
   __device__ __forceinline__ float err(float D) const { return rel * D + sqrtf(D) * u2c + 1e-30f; }
   __device__ __forceinline__ bool close(float b, float s) const {
@@ -3588,32 +3624,32 @@ struct Resolver {
                                         int& bj) const {
     const T* xr = X + i * d;
     float part[4] = {0.f, 0.f, 0.f, 0.f};
-    for (int t0 = 8 * (threadIdx.x & 15); t0 < d; t0 += 128) {
-      const bool in8 = t0 + 8 <= d;
-      float xv[8];
-      load8_split<T>(xr, t0, d, in8, vec, xv);
-      float cv[4][8];
+    // pieces of 64 dims, two in flight
+    auto pieces = [&](int b, auto np) {
+      constexpr int P = np();
+      float xv[P][4], cv[P][4][4];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const float* cr = cw + (int64_t)(cj[u] >= 0 ? cj[u] : 0) * d + t0;
-        if (cvec && in8) {
-          const float4 a = *reinterpret_cast<const float4*>(cr);
-          const float4 b = *reinterpret_cast<const float4*>(cr + 4);
-          cv[u][0] = a.x; cv[u][1] = a.y; cv[u][2] = a.z; cv[u][3] = a.w;
-          cv[u][4] = b.x; cv[u][5] = b.y; cv[u][6] = b.z; cv[u][7] = b.w;
-        } else {
+      for (int p = 0; p < P; ++p) {
+        const int t0 = b + 64 * p + 4 * (threadIdx.x & 15);
+        const bool in4 = t0 + 4 <= d;
+        load4_split<T>(xr, t0, d, in4, vec, xv[p]);
 #pragma unroll
-          for (int e = 0; e < 8; ++e) cv[u][e] = t0 + e < d ? cr[e] : 0.f;
-        }
+        for (int u = 0; u < 4; ++u)
+          load4_split<float>(cw + (int64_t)max(cj[u], 0) * d, t0, d, in4, true, cv[p][u]);
       }
 #pragma unroll
-      for (int u = 0; u < 4; ++u)
+      for (int p = 0; p < P; ++p)
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const float diff = xv[e] - cv[u][e];
-          part[u] = __builtin_fmaf(diff, diff, part[u]);
-        }
-    }
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const float diff = xv[p][e] - cv[p][u][e];
+            part[u] = __builtin_fmaf(diff, diff, part[u]);
+          }
+    };
+    int b = 0;
+    for (; b + 64 < d; b += 128) pieces(b, std::integral_constant<int, 2>());
+    if (b < d) pieces(b, std::integral_constant<int, 1>());
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       float v = part[u];
@@ -3636,13 +3672,15 @@ struct Resolver {
   __device__ __forceinline__ void rank64(int64_t i, int j, double& bD, int& b64) const {
     const T* xr = X + i * d;
     double p = 0.0;
-    for (int t0 = 8 * (threadIdx.x & 15); t0 < d; t0 += 128) {
-      float xv[8];
-      load8_split<T>(xr, t0, d, t0 + 8 <= d, vec, xv);
+    for (int t0 = 4 * (threadIdx.x & 15); t0 < d; t0 += 64) {
+      const bool in4 = t0 + 4 <= d;
+      float xv[4];
+      double cv[4];
+      load4_split<T>(xr, t0, d, in4, vec, xv);
+      load4_f64(c64 + (int64_t)j * d, t0, d, in4, cv);
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const double cv = c64[(int64_t)j * d + (t0 + e < d ? t0 + e : 0)];
-        const double diff = t0 + e < d ? (double)xv[e] - cv : 0.0;
+      for (int e = 0; e < 4; ++e) {
+        const double diff = (double)xv[e] - cv[e];
         p = __builtin_fma(diff, diff, p);
       }
     }
@@ -3655,63 +3693,87 @@ struct Resolver {
       b64 = j;
     }
   }
-  // The nearest of all centers, by the block's 16 groups (every thread calls
-  // it; one group alone would walk k / 4 dependent loads).
-  __device__ int all_centers(int64_t i) const {
-    __shared__ float gbest[16], gsec[16];
-    __shared__ double gD[16];
-    __shared__ int gj[16];
-    const int li = threadIdx.x & 15, grp = threadIdx.x >> 4;
-    float best = INFINITY, sec = INFINITY;
-    int bj = INT_MAX;
-    for (int u0 = 4 * grp; u0 < k; u0 += 64) {
-      int cj[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) cj[u] = u0 + u < k ? u0 + u : -1;
-      rank4(i, cj, best, sec, bj);
-    }
-    __syncthreads();  // an earlier call's results were read
-    if (li == 0) {
-      gbest[grp] = best;
-      gsec[grp] = sec;
-      gj[grp] = bj;
-    }
-    __syncthreads();
-    best = sec = INFINITY;
-    bj = INT_MAX;
-#pragma unroll
-    for (int g = 0; g < 16; ++g) {
-      const float v = gbest[g];
-      if (v < best || (v == best && gj[g] < bj)) {
-        sec = fminf(best, gsec[g]);
-        best = v;
-        bj = gj[g];
-      } else {
-        sec = fminf(sec, v);
-      }
-    }
-    if (bj == INT_MAX || close(best, sec)) {  // the same in every thread
-      double bD = INFINITY;
-      int b64 = INT_MAX;
-      for (int u = grp; u < k; u += 16) rank64(i, u, bD, b64);
-      __syncthreads();
-      if (li == 0) {
-        gD[grp] = bD;
-        gj[grp] = b64;
-      }
-      __syncthreads();
-      bD = INFINITY;
-      bj = INT_MAX;
-#pragma unroll
-      for (int g = 0; g < 16; ++g)
-        if (gD[g] < bD || (gD[g] == bD && gj[g] < bj)) {
-          bD = gD[g];
-          bj = gj[g];
-        }
-    }
-    return bj;
-  }
 };
+
+// Labels of m <= 16 points pt(0), pt(1), ... from the FP64 distances to all
+// centers (lowest index on equal ones), by a block of four waves: tiles of 64
+// centers and 32 dims pass through LDS, a lane takes a center and a wave four of
+// the points.
+template <typename T, typename F>
+__device__ __forceinline__ void decide_all(const T* __restrict__ X, int d, int k,
+                                           const double* __restrict__ c64, int m, F&& pt,
+                                           int32_t* __restrict__ labels) {
+  constexpr int TC = 64, TD = 32, ST = TD + 2;
+  __shared__ __align__(16) double cs[TC * ST];
+  __shared__ __align__(16) float xs[16 * TD];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int row = threadIdx.x >> 4, col = 2 * (threadIdx.x & 15);
+  const T* xr = X + pt(min(row, m - 1)) * d;
+  double bD[4];
+  int bj[4];
+#pragma unroll
+  for (int p = 0; p < 4; ++p) {
+    bD[p] = INFINITY;
+    bj[p] = INT_MAX;
+  }
+  for (int j0 = 0; j0 < k; j0 += TC) {
+    double part[4] = {0.0, 0.0, 0.0, 0.0};
+    for (int t0 = 0; t0 < d; t0 += TD) {
+      const int td = min(TD, d - t0);
+      double cv[4][2];
+      float xv[2];
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        const bool in = col + e < td;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int j = j0 + 16 * r + row;
+          cv[r][e] = in && j < k ? c64[(int64_t)j * d + t0 + col + e] : 0.0;
+        }
+        xv[e] = in ? widen<T>(xr[t0 + col + e]) : 0.f;
+      }
+      __syncthreads();  // the tile before was read
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) cs[(16 * r + row) * ST + col + e] = cv[r][e];
+        xs[row * TD + col + e] = xv[e];
+      }
+      __syncthreads();
+#pragma unroll 4
+      for (int t = 0; t < td; t += 2) {  // (zeros past td)
+        const double2 c = *reinterpret_cast<const double2*>(&cs[lane * ST + t]);
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+          const float2 x = *reinterpret_cast<const float2*>(&xs[(4 * wave + p) * TD + t]);
+          const double a = (double)x.x - c.x, b = (double)x.y - c.y;
+          part[p] = __builtin_fma(a, a, part[p]);
+          part[p] = __builtin_fma(b, b, part[p]);
+        }
+      }
+    }
+    const int j = j0 + lane;
+#pragma unroll
+    for (int p = 0; p < 4; ++p)
+      if (j < k && part[p] < bD[p]) {
+        bD[p] = part[p];
+        bj[p] = j;
+      }
+  }
+#pragma unroll
+  for (int p = 0; p < 4; ++p) {
+    for (int o = 32; o > 0; o >>= 1) {
+      const double oD = __shfl_xor(bD[p], o);
+      const int oj = __shfl_xor(bj[p], o);
+      if (oD < bD[p] || (oD == bD[p] && oj < bj[p])) {
+        bD[p] = oD;
+        bj[p] = oj;
+      }
+    }
+    const int q = 4 * wave + p;
+    if (lane == 0 && q < m) labels[pt(q)] = bj[p] < k ? bj[p] : 0;
+  }
+}
 
 // The split screen of all points: scores from 32x32x16 BF16 MFMAs over three
 // products per dim, c'lo x^ + c'hi xlo + c'hi x^ (c' = -2c = c'hi + c'lo + e,
@@ -3735,7 +3797,8 @@ struct Resolver {
 // the candidates; the label then holds them (open_fields) and k_resolve decides.
 // Else the point is queued, its label the threshold of its candidates' scores,
 // and the LIST variant sweeps the queued points again: every center at or below
-// the threshold becomes a candidate (up to 16), decided in the same kernel.
+// the threshold becomes a candidate, decided in the same kernel if there are at
+// most 16, and otherwise left to k_resolve.
 // Why 256 points x 32 CT centers: 2 x CT accumulator tiles per wave reuse every
 // center operand for two point tiles, and two such blocks fit a CU (64 KB of
 // LDS, 256 VGPRs a wave), one wave's key updates beside another's MFMAs.
@@ -4005,18 +4068,21 @@ __global__ __launch_bounds__(256, 2) void k_screen_split(
     }
     if constexpr (LIST) {
       // decide among the collected centers: a group of 16 lanes per point, four
-      // center rows in flight; more centers than the list holds, or none: all
-      // of them, by the whole block
+      // center rows in flight; points of more centers than the list holds, or of
+      // none, are left to k_resolve
       __syncthreads();
       const int grp = threadIdx.x >> 4;
       const int here = (int)min<int64_t>(ppb, n - base);
       const Resolver<T> rs(X, d, k, vec, cw, c64, st->cmax);
       for (int q = grp; q < here; q += 16) {
         const int c = cand_n[q];
-        if (c < 1 || c > CMAX) continue;
         const int64_t i = queue[base + q];
         float best = INFINITY, sec = INFINITY;
         int bj = INT_MAX;
+        if (c < 1 || c > CMAX) {
+          if ((threadIdx.x & 15) == 0) labels[i] = kAllCenters;
+          continue;
+        }
         for (int u0 = 0; u0 < c; u0 += 4) {
           int cj[4];
 #pragma unroll
@@ -4029,13 +4095,6 @@ __global__ __launch_bounds__(256, 2) void k_screen_split(
           for (int u = 0; u < c; ++u) rs.rank64(i, cand_j[q * CMAX + u], bD, bj);
         }
         if ((threadIdx.x & 15) == 0) labels[i] = bj < k ? bj : 0;
-      }
-      for (int q = 0; q < here; ++q) {
-        const int c = cand_n[q];
-        if (c >= 1 && c <= CMAX) continue;
-        const int64_t i = queue[base + q];
-        const int bj = rs.all_centers(i);
-        if (threadIdx.x == 0) labels[i] = bj < k ? bj : 0;
       }
       __syncthreads();  // the lists are rebuilt for the next points
       continue;
@@ -4119,8 +4178,13 @@ __global__ __launch_bounds__(256, 2) void k_screen_split(
 }
 
 // Decides the points whose label holds candidates (k_screen_split).  A block
-// takes ranges of rb points and lists the open ones in LDS; groups of 16 lanes
-// take one point each.
+// takes rb points at a time, in pieces of 64 that are dealt out over the blocks
+// (open points often lie together), and lists the open ones in LDS; groups of 16
+// lanes take one point each.  Points of all centers are listed from the other end
+// and go 16 at a time (decide_all).  (Decided one by one by the blocks of the second
+// sweep, a pass of 2e5 x 64, k = 256 that no point could be screened in took 4.8 ms
+// against 0.93, and a fit of rows equal to ten of them 123 ms against 6.0; with the
+// FP32 kernels 4.5 and 31.)
 template <typename T>
 __global__ __launch_bounds__(256) void k_resolve(
     const T* __restrict__ X, int64_t n, int d, int k, int bg, int rb,
@@ -4129,31 +4193,34 @@ __global__ __launch_bounds__(256) void k_resolve(
     int32_t* __restrict__ labels) {
   if (gated(gate)) return;
   __shared__ uint16_t list[4096];
-  __shared__ int cnt;
+  __shared__ int cnt, call;
   const int li = threadIdx.x & 15, grp = threadIdx.x >> 4;
   const bool vec = (d & 7) == 0 && (reinterpret_cast<uintptr_t>(X) & 15u) == 0;
   const int GM = (1 << bg) - 1, nf = open_fields(bg);
   const Resolver<T> rs(X, d, k, vec, cw, c64, st->cmax);
-  for (int64_t r0 = (int64_t)blockIdx.x * rb; r0 < n; r0 += (int64_t)gridDim.x * rb) {
-    if (threadIdx.x == 0) cnt = 0;
+  for (int64_t r0 = 64 * (int64_t)blockIdx.x; r0 < n; r0 += (int64_t)gridDim.x * rb) {
+    auto at = [&](int o) { return r0 + 64 * (int64_t)gridDim.x * (o >> 6) + (o & 63); };
+    if (threadIdx.x == 0) cnt = call = 0;
     __syncthreads();
-    const int rn = (int)min<int64_t>(rb, n - r0);
 #pragma unroll 1
-    for (int u0 = 0; u0 < rn; u0 += 1024) {
+    for (int u0 = 0; u0 < rb; u0 += 1024) {
       int lv[4];
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
         const int o = u0 + u * 256 + (int)threadIdx.x;
-        lv[u] = o < rn ? labels[r0 + o] : 0;
+        lv[u] = o < rb && at(o) < n ? labels[at(o)] : 0;
       }
 #pragma unroll
       for (int u = 0; u < 4; ++u)
-        if (lv[u] < 0) list[atomicAdd(&cnt, 1)] = (uint16_t)(u0 + u * 256 + threadIdx.x);
+        if (lv[u] < 0) {
+          const int e = lv[u] == kAllCenters ? 4095 - atomicAdd(&call, 1) : atomicAdd(&cnt, 1);
+          list[e] = (uint16_t)(u0 + u * 256 + threadIdx.x);
+        }
     }
     __syncthreads();
-    const int m = cnt;
+    const int m = cnt, ma = call;
     for (int q = grp; q < m; q += 16) {
-      const int64_t pt = r0 + list[q];
+      const int64_t pt = at(list[q]);
       const int code = labels[pt];
       int cj[4];
 #pragma unroll
@@ -4173,6 +4240,9 @@ __global__ __launch_bounds__(256) void k_resolve(
       }
       if (li == 0) labels[pt] = bj < k ? bj : 0;
     }
+    for (int q0 = 0; q0 < ma; q0 += 16)
+      decide_all<T>(X, d, k, c64, min(16, ma - q0),
+                    [&](int q) { return at(list[4095 - q0 - q]); }, labels);
     __syncthreads();  // the list is rebuilt for the next range
   }
 }
@@ -6442,9 +6512,9 @@ template <typename T>
 static void dispatch_resolve(const PassBufs& b, const PassPlan& p, const int32_t* gate,
                              hipStream_t s) {
   dispatch_split<T, true>(b, p, gate, s);
-  // ranges of 256 to 4096 points, one per resident block while there are enough
+  // 64 to 4096 points at a time, so many that the resident blocks take all at once
   const int64_t cap = std::max<int64_t>(1, p.rr_blocks);
-  const int64_t rb = std::min<int64_t>(4096, std::max<int64_t>(256, (b.n / cap + 255) / 256 * 256));
+  const int64_t rb = std::min<int64_t>(4096, std::max<int64_t>(64, (b.n / cap + 63) / 64 * 64));
   const unsigned g = (unsigned)std::max<int64_t>(1, std::min<int64_t>((b.n + rb - 1) / rb, cap));
   hipLaunchKernelGGL(k_resolve<T>, dim3(g), dim3(256), 0, s, (const T*)b.X, b.n, b.d, b.k,
                      split_bits(b.k), (int)rb, (const float*)b.cw, (const double*)b.c64,

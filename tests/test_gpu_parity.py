@@ -754,3 +754,65 @@ def test_split_screen_any_d_one_far_row(d, k, dtype, f):
     assert np.array_equal(lab.cpu().numpy(), rlab)
     assert abs(J - D1.sum()) <= 1e-9 * D1.sum()
     assert unc <= calm + 1, (calm, unc)
+
+
+@pytest.mark.parametrize("n", [1, 7, 8, 9, 16, 17, 24, 25, 63, 65, 257, 2_000])
+@pytest.mark.parametrize("d,k", [(20, 900), (64, 256), (300, 70)])
+def test_split_screen_points_of_all_centers(n, d, k):
+    """Points with more candidates than the second sweep keeps (40 centers held
+    twice or closer than their rounding), by groups of lanes and by whole blocks:
+    the lowest index of the nearest."""
+    rng = np.random.default_rng(n + d)
+    C = rng.normal(0, 20.0, size=(k, d))
+    C[20:60] = C[20] + rng.normal(0, 1e-9, size=(40, d)) * (rng.random((40, 1)) < 0.5)
+    Xh = (C[20] + rng.normal(0, 1.0, size=(n, d))).astype(np.float32)
+    lab, J, unc = km.km_assign(to_device(Xh), torch.from_numpy(C).cuda())
+    rlab, D1, _ = oracle.assign(Xh, C)
+    assert unc == n
+    # (the oracle adds a row's terms in another order: equal up to that rounding)
+    got = lab.cpu().numpy()
+    Dg = ((Xh.astype(np.float64) - C[got]) ** 2).sum(1)
+    assert np.all(Dg <= D1 * (1 + d * 2.0 ** -52))
+    same = np.array_equal(C[got], C[rlab])
+    assert not same or np.array_equal(got, rlab)
+    assert abs(J - D1.sum()) <= 1e-9 * D1.sum()
+
+
+def _best_ms(fn, reps=6):
+    ts = []
+    for _ in range(reps):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        fn()
+        b.record()
+        torch.cuda.synchronize()
+        ts.append(a.elapsed_time(b))
+    return min(ts[1:])
+
+
+@pytest.mark.parametrize("what", ["equal centers", "equal rows", "half zero rows", "far origin"])
+def test_split_screen_undecided_points_keep_pace(what):
+    """Where the screen can decide next to nothing, auto precision stays within
+    1.25 of the FP32 kernels' time (they leave the same points to FP64)."""
+    n, d, k = 200_000, 64, 256
+    g = torch.Generator(device="cuda").manual_seed(3)
+    mu = (torch.rand((k, d), generator=g, device="cuda") * 2 - 1) * 50
+    X = mu[torch.randint(0, k, (n,), generator=g, device="cuda")]
+    X = X + 1.5 * torch.randn((n, d), generator=g, device="cuda")
+    C = mu.double() + 0.3
+    if what == "equal centers":
+        C[100:] = C[0]
+    elif what == "equal rows":
+        X = X[torch.arange(n, device="cuda") % 10].contiguous()
+    elif what == "half zero rows":
+        X[: n // 2] = 0
+    else:
+        X, C = X + 1e5, C + 1e5
+
+    def call(precision):
+        if what in ("equal centers", "far origin"):
+            return km.km_step(X, C, precision=precision)
+        return km.kmeans_fit_ex(X, k, 0.05, 3, (5, 5), 0.0, precision=precision)
+    auto, fp32 = _best_ms(lambda: call("auto")), _best_ms(lambda: call("fp32"))
+    print(f"[pace] {what}: auto {auto:.3f} ms, fp32 {fp32:.3f} ms", flush=True)
+    assert auto <= 1.25 * fp32
