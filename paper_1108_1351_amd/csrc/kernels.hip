@@ -4959,12 +4959,12 @@ __global__ __launch_bounds__(256, 2) void k_batch_pair(const BatchHead* __restri
     const int d = b.d, k = b.k, nt = (k + 31) >> 5;
     const bool lds = b.mode == 1 && b.lds_sums;
     const T* X = reinterpret_cast<const T*>(b.X);
-    const float B = st->B, cmax = st->cmax, scale = st->scale;
+    const float cmax = st->cmax, scale = st->scale;
     for (int e = threadIdx.x; e < k * KD; e += 256) {
       const int j = e / KD, t = e - j * KD;
       cs[j * CSS + t] = t < d ? b.c64[(int64_t)j * d + t] : 0.0;
     }
-    for (int e = threadIdx.x; e < 32 * nt; e += 256) cbias[e] = e < k ? b.cn[e] + B : 1e30f;
+    for (int e = threadIdx.x; e < 32 * nt; e += 256) cbias[e] = e < k ? b.cn[e] : 1e38f;
     if (lds)
       for (int e = threadIdx.x; e < k * (d + 1); e += 256) S[e] = 0ull;
     __syncthreads();
@@ -4993,15 +4993,15 @@ __global__ __launch_bounds__(256, 2) void k_batch_pair(const BatchHead* __restri
     }
     __syncthreads();
     // the band of two scores as in k_fused_pair, with ||c' - c'hi|| <= 2^-8 ||c||
-    // for its exact maximum and two more roundings of the C input
+    // and two more roundings of the C input, as factors of ||c||^2 + the offset,
+    // ||c|| ||x|| and ||c|| ||x - x^||
     const int bg = nt == 1 ? 5 : nt == 2 ? 6 : nt <= 4 ? 7 : 8;
     const int GM = (1 << bg) - 1, keep = opaque_vgpr(~GM);
-    const float dcn = cmax * 0x1.03p-8f;
-    const float ea = (float)(16 * NM + 12) * 0x1p-23f * 1.01f;
-    const float cc = 2.f * cmax + 2.004f * dcn;
-    const float c0 = (2.f * ea * (cmax * cmax + B) + 1e-30f) * 1.0001f;
-    const float c1 = (2.f * dcn * 0x1p-8f * 1.001f + 2.f * ea * cc) * 1.0001f;
-    const float c2 = (2.f * dcn * 1.004f + 0x1p-6f * cmax + 2.f * ea * 1.004f * cc) * 1.0001f;
+    constexpr float dc = 0x1.03p-8f, ea = (float)(16 * NM + 12) * 0x1p-23f * 1.01f;
+    constexpr float cc = 2.f + 2.004f * dc;
+    constexpr float e0 = 2.f * ea * 1.0001f;
+    constexpr float e1 = (2.f * dc * 0x1p-8f * 1.001f + 2.f * ea * cc) * 1.0001f;
+    constexpr float e2 = (2.f * dc * 1.004f + 0x1p-6f + 2.f * ea * 1.004f * cc) * 1.0001f;
     const float delta = (float)(1 << bg) * 0x1p-23f * 1.01f;
     const bool whole = d == KD && (reinterpret_cast<uintptr_t>(X) & 15u) == 0;
     double Jacc = 0.0;
@@ -5047,6 +5047,15 @@ __global__ __launch_bounds__(256, 2) void k_batch_pair(const BatchHead* __restri
           wB[2 * HW + q] = l[1];
         }
       }
+      // Each point's scores get an offset of its own that keeps them positive: at
+      // least ||x||^2, so that a score is ||x - c||^2 and more.  (One offset for
+      // all rows, above the largest squared norm, let a single row 100 times as
+      // long as the others leave most points of its problem to the FP64 check.)
+      const float xn = __builtin_amdgcn_sqrtf(s2) * 1.01f;
+      const float off = 1.05f * xn * xn + 1e-30f;
+      const auto offs = __builtin_amdgcn_permlane32_swap(__float_as_int(off), __float_as_int(off),
+                                                         false, false);
+      const float offA = __int_as_float((int)offs[0]), offB = __int_as_float((int)offs[1]);
       v8bf oA[NM], oB[NM];
 #pragma unroll
       for (int m = 0; m < NM; ++m) {
@@ -5063,7 +5072,12 @@ __global__ __launch_bounds__(256, 2) void k_batch_pair(const BatchHead* __restri
           const float4 v = *reinterpret_cast<const float4*>(&cbias[32 * t + 16 * h + 4 * g]);
           bias[4 * g] = v.x; bias[4 * g + 1] = v.y; bias[4 * g + 2] = v.z; bias[4 * g + 3] = v.w;
         }
-        v16f accA = bias, accB = bias;
+        v16f accA, accB;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          accA[r] = bias[r] + offA;
+          accB[r] = bias[r] + offB;
+        }
 #pragma unroll
         for (int m = 0; m < NM; ++m) {
           const v8bf at = aop[(t * NM + m) * 64 + lane];
@@ -5091,16 +5105,23 @@ __global__ __launch_bounds__(256, 2) void k_batch_pair(const BatchHead* __restri
         k0[q] = (int)w[0];
         k1[q] = (int)w[1];
       }
-      const float xn = __builtin_amdgcn_sqrtf(s2) * 1.01f;
-      const float xr = sizeof(T) == 4 ? __builtin_amdgcn_sqrtf(r2) * 1.01f : 0.f;
-      const float E2 = __builtin_fmaf(c2, xr, __builtin_fmaf(c1, xn, c0));
       const int best = min(k0[0], k1[0]);
       const float v1 = __int_as_float(best & ~GM);
+      int l = best & GM;
+      // Centers longer than 2 ||x|| + ||c_l|| are farther than c_l: the others'
+      // norms bound the band, and one far center does not widen it.  (Scores could
+      // overflow where these squares do not, beyond 1e37.)
+      const float xr = sizeof(T) == 4 ? __builtin_amdgcn_sqrtf(r2) * 1.01f : 0.f;
+      float cm = cmax;
+      if (l < k) cm = fminf(cmax, (2.f * xn + __builtin_amdgcn_sqrtf(cbias[l])) * 1.001f);
+      const float cm2 = __builtin_fmaf(cm, cm, off);
+      const float E2 = cm2 < 1e37f ? __builtin_fmaf(e0, cm2, 1e-30f) +
+                                         cm * __builtin_fmaf(e2, xr, e1 * xn)
+                                   : INFINITY;
       auto apart = [&](int key) {
         const float v = __int_as_float(key & ~GM);
         return (v - v1) > E2 + delta * (fabsf(v) + fabsf(v1));
       };
-      int l = best & GM;
       const int others[3] = {max(k0[0], k1[0]), k0[1], k1[1]};
       const bool certain = k == 1 || (l < k && apart(min(others[0], min(k0[1], k1[1]))));
       const bool closed = l < k && apart(k0[2]) && apart(k1[2]);

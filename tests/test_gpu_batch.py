@@ -358,3 +358,44 @@ def test_batch_bf16_screen_row_lengths(d):
     for Xh, (C, L, info), (n, k) in zip(data, out, specs):
         _check_against_oracle(Xh, C, L, info, k, 1.0, 3, (3, 4), (0.0, 0.0),
                               f"n={n} d={d} k={k} bf16")
+
+
+@pytest.mark.parametrize("f", [1e2, 1e3, 1e4])
+@pytest.mark.parametrize("d,k,dtype", [(2, 8, "f32"), (8, 64, "f32"), (16, 256, "f32"),
+                                       (16, 30, "bf16")])
+def test_batch_split_screen_one_far_row(d, k, dtype, f):
+    """One row f times as long as the others does not leave the others undecided,
+    whether it is far from every center or has drawn one to itself."""
+    Xh = _problem(20_011, d, k, 70 + k, dtype)
+    args = (k, 0.3, 3, (3, 3), (0.0, 0.0))
+    (_, _, calm), = km.kmeans_fit_batch([(to_device(Xh), *args)])
+    Xw = Xh.astype(np.float32) if dtype == "f32" else \
+        (Xh.astype(np.uint32) << 16).view(np.float32)
+    far = (Xw[777] * np.float32(f)).astype(np.float32)
+    Xh[777] = far if dtype == "f32" else (far.view(np.uint32) >> 16).astype(np.uint16)
+    (C, L, info), = km.kmeans_fit_batch([(to_device(Xh), *args)])
+    # (the sums' quantum grows with the far row: labels may differ from the
+    # oracle's where the two nearest centers are as near as that)
+    ref = oracle.fit(Xh, *args)
+    assert info["iters"] == ref.info["iters"]
+    assert_centers(C.cpu().numpy().astype(np.float64), ref.centers, Xh, tol=1e-5)
+    assert abs(info["J"] - ref.info["J"]) <= JTOL * ref.info["J"] + j_atol(Xh)
+    _, D1, D2 = oracle.assign(Xh, ref.centers)
+    assert np.all((L.cpu().numpy() == ref.labels) | (D2 - D1 < 1e-3 * D2))
+    passes = info["m"] * 3 + len(Xh) * 4
+    assert info["uncertain"] <= calm["uncertain"] + 0.05 * passes
+
+
+@pytest.mark.parametrize("e", [30, 44, 50, 56, 58, 60, 61, 62])
+@pytest.mark.parametrize("d,k,dtype", [(2, 5, "f32"), (8, 33, "f32"), (16, 256, "f32"),
+                                       (16, 30, "bf16"), (40, 60, "bf16"), (40, 60, "f32")])
+def test_batch_large_norms(d, k, dtype, e):
+    """Overlapping rows scaled by 2^e: the fit of the unscaled rows, scaled."""
+    rng = np.random.default_rng(d + k)
+    X = torch.from_numpy(rng.normal(0, 1.0, size=(3_001, d)).astype(np.float32)).cuda()
+    X = X if dtype == "f32" else X.bfloat16()
+    args = (k, 0.5, 3, (3, 3), (0.0, 0.0))
+    (C, L, info), = km.kmeans_fit_batch([(X, *args)])
+    (Cs, Ls, infos), = km.kmeans_fit_batch([(X * 2.0 ** e, *args)])
+    assert torch.equal(Ls, L) and torch.equal(Cs, C * 2.0 ** e)
+    assert infos["iters"] == info["iters"] and infos["J"] == info["J"] * 4.0 ** e
