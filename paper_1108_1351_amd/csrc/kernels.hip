@@ -4940,12 +4940,7 @@ __global__ __launch_bounds__(256, 2) void k_batch_pair(const BatchHead* __restri
   constexpr int NS = sizeof(T) == 4 ? 3 : 2;
   constexpr int NM = (NS * H + 7) / 8, NE = NM * 8;
   constexpr int CSS = KD + 2;
-  constexpr int KM = kPairCenters;
   extern __shared__ __align__(16) unsigned char smem[];
-  double* cs = reinterpret_cast<double*>(smem);                          // [KM][CSS]
-  v8bf* aop = reinterpret_cast<v8bf*>(cs + KM * CSS);                    // [KM / 32][NM][64]
-  float* cbias = reinterpret_cast<float*>(aop + KM / 32 * NM * 64);      // [KM]
-  unsigned long long* S = reinterpret_cast<unsigned long long*>(cbias + KM);  // [k][d + 1]
   const int lane = threadIdx.x & 63, h = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int ninst = hd->ninst;
@@ -4957,6 +4952,10 @@ __global__ __launch_bounds__(256, 2) void k_batch_pair(const BatchHead* __restri
     if ((b.mode == 1 && dn) || (b.mode == 2 && dn == 2)) continue;
     const int64_t tile = u - b.unit0, n = b.n;
     const int d = b.d, k = b.k, nt = (k + 31) >> 5;
+    double* cs = reinterpret_cast<double*>(smem);                          // [32 nt][CSS]
+    v8bf* aop = reinterpret_cast<v8bf*>(cs + 32 * nt * CSS);               // [nt][NM][64]
+    float* cbias = reinterpret_cast<float*>(aop + nt * NM * 64);           // [32 nt]
+    unsigned long long* S = reinterpret_cast<unsigned long long*>(cbias + 32 * nt);  // [k][d + 1]
     const bool lds = b.mode == 1 && b.lds_sums;
     const T* X = reinterpret_cast<const T*>(b.X);
     const float cmax = st->cmax, scale = st->scale;
@@ -5007,8 +5006,8 @@ __global__ __launch_bounds__(256, 2) void k_batch_pair(const BatchHead* __restri
     double Jacc = 0.0;
     int64_t ucnt = 0;
 #pragma unroll 1
-    for (int it = 0; it < kPairPoints / 256; ++it) {
-      const int64_t p0 = tile * kPairPoints + it * 256 + wave * 64;
+    for (int64_t o = 0; o < b.tile_pts; o += 256) {
+      const int64_t p0 = tile * b.tile_pts + o + wave * 64;
       if (p0 >= n) break;
       const int64_t i = p0 + lane;
       const bool valid = i < n;
@@ -6640,10 +6639,10 @@ int batch_pair_kd(int32_t d, int32_t k) {
   return d <= 4 ? 4 : d <= 8 ? 8 : 16;
 }
 
-size_t batch_pair_lds(int dtype, int kd, size_t sums) {
+size_t batch_pair_lds(int dtype, int kd, int kmax, size_t sums) {
   const int nm = ((dtype == 0 ? 3 : 2) * (kd / 2) + 7) / 8;
-  return (size_t)kPairCenters * (kd + 2) * 8 + (size_t)kPairCenters / 32 * nm * 64 * 16 +
-         kPairCenters * 4 + sums;
+  return (size_t)kmax * (kd + 2) * 8 + (size_t)kmax / 32 * nm * 64 * 16 + kmax * 4 +
+         std::min<size_t>(sums, (size_t)kmax * (kd + 1) * 8);
 }
 
 template <typename T, typename F>

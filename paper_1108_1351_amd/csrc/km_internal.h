@@ -250,11 +250,12 @@ struct BatchShape {
 // returns its K steps (2, 4 or 8), or 0.
 int batch_screen_ks(int dtype, int32_t d, int32_t k);
 // The batched split screen takes d <= 16 and k <= kPairCenters, in units of
-// kPairPoints points; returns its padded dims (4, 8 or 16), or 0.  Its LDS, with
+// kPairPoints points or more; returns its padded dims (4, 8 or 16), or 0.  Its LDS
+// for problems of at most kmax centers (a multiple of 32), with at most
 // `sums` bytes of cluster sums.
 constexpr int kPairCenters = 256, kPairPoints = 512;
 int batch_pair_kd(int32_t d, int32_t k);
-size_t batch_pair_lds(int dtype, int kd, size_t sums);
+size_t batch_pair_lds(int dtype, int kd, int kmax, size_t sums);
 int batch_dmax(int32_t d);                       // 0: d too large for the batched path
 int64_t batch_resident_blocks(int dtype, int dmax, int ppt, size_t lds, int cus,
                               int screen = 0, int pair = 0);

@@ -347,6 +347,11 @@ class Engine {
     int blocks;
     int screen;  // K steps of the batched BF16 screen, 0 for the other kernels
     int pair;    // padded dims of the batched split screen, 0 for the other kernels
+    // split screen: LDS and blocks for problems of up to 64, 128 and 256 centers
+    // (a launch has those of the largest among its problems), 0: not asked
+    size_t lds_lv[3];
+    int blocks_lv[3];
+    int top;  // the highest level of a captured graph
   };
 
   // cap: problems advanced together, at most kTableCap (the tables' size)
@@ -417,12 +422,37 @@ class Engine {
     if ((int)shapes_.size() >= kMaxShapes) return -1;
     // the screen's LDS is static (center tiles, candidate lists)
     Shape sh{dtype, dmax, ppt, ktile,
-             screen ? 0 : pair ? batch_pair_lds(dtype, pair, kSumsLds) : batch_lds(dmax, ktile),
-             0, screen, pair};
-    sh.blocks = (int)std::max<int64_t>(
-        1, batch_resident_blocks(dtype, dmax, ppt, sh.lds, device_cus(), screen, pair));
+             screen || pair ? 0 : batch_lds(dmax, ktile), 0, screen, pair, {}, {}, 0};
+    if (!pair)
+      sh.blocks = (int)std::max<int64_t>(
+          1, batch_resident_blocks(dtype, dmax, ppt, sh.lds, device_cus(), screen, 0));
     shapes_.push_back(sh);
     return (int)shapes_.size() - 1;
+  }
+
+  // Split screen: the LDS level of a problem, which sets the blocks that stay
+  // resident (64 centers of 16 dims take 24 KB, 256 of them 95) ...
+  int pair_level(Shape& sh, int k) {
+    int lv = 0;
+    while ((64 << lv) < k) ++lv;
+    if (!sh.blocks_lv[lv]) {
+      sh.lds_lv[lv] = batch_pair_lds(sh.dtype, sh.pair, 64 << lv, kSumsLds);
+      sh.blocks_lv[lv] = (int)std::max<int64_t>(
+          1, batch_resident_blocks(sh.dtype, sh.dmax, sh.ppt, sh.lds_lv[lv], device_cus(), 0,
+                                   sh.pair));
+    }
+    return lv;
+  }
+  // ... and its points per unit, so many that the resident blocks take its units in
+  // two rounds or more: every unit lays out the centers and flushes its sums anew
+  // (512 points a unit whatever the rows, LDS for 256 centers whatever k: 132 us a
+  // pass of 5e6 x 2, k = 4 against 86, 165 of 2e6 x 16, k = 16 against 90).  The
+  // order of a problem's J follows from it, so it is a matter of the problem alone.
+  int64_t pair_tile(Shape& sh, int k, int64_t rows) {
+    const int64_t blocks = sh.blocks_lv[pair_level(sh, k)];
+    int64_t tile = kPairPoints;
+    while ((rows + tile - 1) / tile > 4 * blocks) tile *= 2;
+    return tile;
   }
 
   // `passes` batched passes for the given problems (each in phase 1, 2 or 3),
@@ -435,6 +465,7 @@ class Engine {
     if (na > cap_) return fail(KM_EINVAL, "more than %d active problems", cap_);
     const int ns = (int)shapes_.size();
     std::vector<int> cnt(ns, 0);
+    std::vector<int> level(ns, 0);
     std::vector<int64_t> units(ns, 0);
     int64_t centers = 0, sunits = 0;
     unsigned mask = 0;
@@ -468,6 +499,10 @@ class Engine {
       b.kd16 = 16 * j.screen;
       b.ktile = j.tv.ktile;
       b.tile_pts = 256LL * shapes_[g].ppt;
+      if (j.pair) {
+        level[g] = std::max(level[g], pair_level(shapes_[g], b.k));
+        b.tile_pts = pair_tile(shapes_[g], b.k, b.n);
+      }
       b.unit0 = units[g];
       b.units = (b.n + b.tile_pts - 1) / b.tile_pts;
       b.center0 = centers;
@@ -493,7 +528,8 @@ class Engine {
       {
         // one slot row per writer (tile flushes or point ranges), at most 8: more
         // rows cost the finalize more than they save the writers (55 against
-        // 39 us a pass on 30 problems of 32 and 128 dims, the sums unchanged)
+        // 39 us a pass on 30 problems of 32 and 128 dims, the sums unchanged; 5.62
+        // against 5.65 ms for 66 passes of one problem of 5e6 x 2, k = 4)
         const int64_t writers = b.sunits ? (b.n + spts - 1) / spts : b.units;
         int ns = 1;
         while (ns < 8 && ns < writers) ns <<= 1;
@@ -508,7 +544,18 @@ class Engine {
       h_insts_[(size_t)kMaxShapes * cap_ + a] = b;
       mask |= 1u << g;
     }
-    for (int g = 0; g < ns; ++g) h_heads_[g] = BatchHead{cnt[g], 0, units[g], 0};
+    uint64_t levels = 0;
+    for (int g = 0; g < ns; ++g) {
+      h_heads_[g] = BatchHead{cnt[g], 0, units[g], 0};
+      Shape& sh = shapes_[g];
+      if (!sh.pair || !cnt[g]) continue;
+      // (a graph once captured serves smaller problems too: problems that leave do
+      // not make the rest capture theirs anew)
+      if (graphs) level[g] = sh.top = std::max(sh.top, level[g]);
+      sh.lds = sh.lds_lv[level[g]];
+      sh.blocks = sh.blocks_lv[level[g]];
+      levels |= (uint64_t)level[g] << (2 * g);
+    }
     h_heads_[kMaxShapes] = BatchHead{na, 0, 0, centers};
     h_heads_[kMaxShapes + 1] = BatchHead{na, 0, sunits, 0};
     // descriptors: only the used prefix of each table travels
@@ -523,7 +570,7 @@ class Engine {
                            hipMemcpyHostToDevice, s_));
     if (graphs) {
       hipGraphExec_t ex = nullptr;
-      rc = graph_for(mask, passes, &ex);
+      rc = graph_for(mask, levels, passes, &ex);
       if (rc != KM_OK) goto done;
       HIP_TRY(hipGraphLaunch(ex, s_));
     } else {
@@ -562,10 +609,11 @@ class Engine {
     return rc;
   }
 
-  // The launches of `passes` rounds for a set of shapes, captured once and replayed.
-  km_status graph_for(unsigned mask, int passes, hipGraphExec_t* out) {
+  // The launches of `passes` rounds for a set of shapes (and their LDS levels),
+  // captured once and replayed.
+  km_status graph_for(unsigned mask, uint64_t levels, int passes, hipGraphExec_t* out) {
     km_status rc = KM_OK;
-    const uint64_t key = (uint64_t)mask << 8 | (uint64_t)passes;
+    const uint64_t key = levels << 24 | (uint64_t)mask << 8 | (uint64_t)passes;
     auto it = graphs_.find(key);
     if (it != graphs_.end()) {
       *out = it->second;
