@@ -3564,10 +3564,15 @@ __device__ __forceinline__ void load8_split(const T* __restrict__ row, int t0, i
   for (int e = 0; e < 8; ++e) v[e] = t0 + e < d ? widen<T>(row[t0 + e]) : 0.f;
 }
 
-// Dims [t0, t0 + 4) of a row likewise (whole, vec: as above), ...
+// Dims [t0, t0 + 4) of a row likewise; BF16 rows load as dwords when dw says they
+// start on one, ...
+template <typename T>
+__device__ __forceinline__ bool on_dwords(const T* X, int d) {
+  return sizeof(T) == 4 || ((d & 1) == 0 && (reinterpret_cast<uintptr_t>(X) & 3u) == 0);
+}
 template <typename T>
 __device__ __forceinline__ void load4_split(const T* __restrict__ row, int t0, int d, bool whole,
-                                            bool vec, float (&v)[4]) {
+                                            bool dw, float (&v)[4]) {
   if constexpr (sizeof(T) == 4) {
     if (whole) {
       const f32x4a4 a = *reinterpret_cast<const f32x4a4*>(row + t0);
@@ -3575,8 +3580,8 @@ __device__ __forceinline__ void load4_split(const T* __restrict__ row, int t0, i
       for (int e = 0; e < 4; ++e) v[e] = a[e];
       return;
     }
-  } else if (whole && vec) {
-    const uint2 w = *reinterpret_cast<const uint2*>(row + t0);
+  } else if (whole && dw) {
+    const u32x2a4 w = *reinterpret_cast<const u32x2a4*>(row + t0);
     v[0] = bf16_lo(w.x); v[1] = bf16_hi(w.x); v[2] = bf16_lo(w.y); v[3] = bf16_hi(w.y);
     return;
   }
@@ -3604,15 +3609,15 @@ template <typename T>
 struct Resolver {
   const T* X;
   int d, k;
-  bool vec;
+  bool dw;
   const float* cw;
   const double* c64;
   float rel, u2c;
   // FP32 direct form over a lane's 4 ceil(d / 64) terms and four pairwise adds,
   // plus 2 sqrt(D) ||c - cw|| for the rounded center
-  __device__ __forceinline__ Resolver(const T* X_, int d_, int k_, bool vec_, const float* cw_,
+  __device__ __forceinline__ Resolver(const T* X_, int d_, int k_, const float* cw_,
                                       const double* c64_, float cmax)
-      : X(X_), d(d_), k(k_), vec(vec_), cw(cw_), c64(c64_),
+      : X(X_), d(d_), k(k_), dw(on_dwords(X_, d_)), cw(cw_), c64(c64_),
         rel((float)(4 * ((d_ + 63) / 64) + 6) * 0x1p-24f * 1.01f),
         u2c(2.f * 0x1p-24f * 1.01f * cmax) {}
   __device__ __forceinline__ float err(float D) const { return rel * D + sqrtf(D) * u2c + 1e-30f; }
@@ -3632,7 +3637,7 @@ struct Resolver {
       for (int p = 0; p < P; ++p) {
         const int t0 = b + 64 * p + 4 * (threadIdx.x & 15);
         const bool in4 = t0 + 4 <= d;
-        load4_split<T>(xr, t0, d, in4, vec, xv[p]);
+        load4_split<T>(xr, t0, d, in4, dw, xv[p]);
 #pragma unroll
         for (int u = 0; u < 4; ++u)
           load4_split<float>(cw + (int64_t)max(cj[u], 0) * d, t0, d, in4, true, cv[p][u]);
@@ -3676,7 +3681,7 @@ struct Resolver {
       const bool in4 = t0 + 4 <= d;
       float xv[4];
       double cv[4];
-      load4_split<T>(xr, t0, d, in4, vec, xv);
+      load4_split<T>(xr, t0, d, in4, dw, xv);
       load4_f64(c64 + (int64_t)j * d, t0, d, in4, cv);
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
@@ -4073,7 +4078,7 @@ __global__ __launch_bounds__(256, 2) void k_screen_split(
       __syncthreads();
       const int grp = threadIdx.x >> 4;
       const int here = (int)min<int64_t>(ppb, n - base);
-      const Resolver<T> rs(X, d, k, vec, cw, c64, st->cmax);
+      const Resolver<T> rs(X, d, k, cw, c64, st->cmax);
       for (int q = grp; q < here; q += 16) {
         const int c = cand_n[q];
         const int64_t i = queue[base + q];
@@ -4195,9 +4200,8 @@ __global__ __launch_bounds__(256) void k_resolve(
   __shared__ uint16_t list[4096];
   __shared__ int cnt, call;
   const int li = threadIdx.x & 15, grp = threadIdx.x >> 4;
-  const bool vec = (d & 7) == 0 && (reinterpret_cast<uintptr_t>(X) & 15u) == 0;
   const int GM = (1 << bg) - 1, nf = open_fields(bg);
-  const Resolver<T> rs(X, d, k, vec, cw, c64, st->cmax);
+  const Resolver<T> rs(X, d, k, cw, c64, st->cmax);
   for (int64_t r0 = 64 * (int64_t)blockIdx.x; r0 < n; r0 += (int64_t)gridDim.x * rb) {
     auto at = [&](int o) { return r0 + 64 * (int64_t)gridDim.x * (o >> 6) + (o & 63); };
     if (threadIdx.x == 0) cnt = call = 0;
@@ -4247,6 +4251,59 @@ __global__ __launch_bounds__(256) void k_resolve(
   }
 }
 
+constexpr int kLabelRows = 4;
+// J of a labelling pass of the split screen: the squared distance of every row to
+// the center of its label, in FP64 throughout (the sorted update's fixed units
+// follow the largest norms: beside a center 1e8 times as far out as the rows they
+// left J nine digits).  2^glog lanes, 16 to the whole block by d, take four rows at a
+// time, 4 dims a lane; a lane's sum, and the block's over its lanes, run in a fixed
+// order.
+template <typename T>
+__global__ __launch_bounds__(256) void k_label_J(const T* __restrict__ X, int64_t n, int d,
+                                                 const double* __restrict__ c64,
+                                                 const int32_t* __restrict__ labels,
+                                                 const int32_t* __restrict__ gate, int glog,
+                                                 double* __restrict__ Jpart) {
+  if (gated(gate)) return;
+  constexpr int R = kLabelRows;
+  const bool dw = on_dwords(X, d);
+  const int per = 256 >> glog;  // groups of a block
+  const int64_t step = (int64_t)R * per * gridDim.x;
+  double J = 0.0;
+  for (int64_t r0 = R * (per * (int64_t)blockIdx.x + (threadIdx.x >> glog)); r0 < n; r0 += step) {
+    const T* xr[R];
+    const double* cr[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const int64_t i = min(r0 + r, n - 1);
+      xr[r] = X + i * d;
+      cr[r] = c64 + (int64_t)labels[i] * d;
+    }
+    for (int t0 = 4 * (threadIdx.x & ((1 << glog) - 1)); t0 < d; t0 += 4 << glog) {
+      const bool in4 = t0 + 4 <= d;
+      float xv[R][4];
+      double cv[R][4];
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        load4_split<T>(xr[r], t0, d, in4, dw, xv[r]);
+        load4_f64(cr[r], t0, d, in4, cv[r]);
+      }
+#pragma unroll
+      for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const double diff = r0 + r < n ? (double)xv[r][e] - cv[r][e] : 0.0;
+          J = __builtin_fma(diff, diff, J);
+        }
+    }
+  }
+  for (int o = 32; o > 0; o >>= 1) J += __shfl_xor(J, o);
+  __shared__ double wJ[4];
+  if ((threadIdx.x & 63) == 0) wJ[threadIdx.x >> 6] = J;
+  __syncthreads();
+  if (threadIdx.x == 0) Jpart[blockIdx.x] = (wJ[0] + wJ[1]) + (wJ[2] + wJ[3]);
+}
+
 // ============================================================================
 // New centers from the slot sums, stage bookkeeping
 // ============================================================================
@@ -4275,7 +4332,8 @@ __device__ void conclude_block(PassState* __restrict__ st, const double* __restr
                                const double* __restrict__ cnorm,
                                const int32_t* __restrict__ emptyj, int k, bool update,
                                double* __restrict__ J_hist, double* __restrict__ shift_hist,
-                               bool mark_labelled = false) {
+                               bool mark_labelled = false, int64_t nbJ = -1) {
+  if (nbJ < 0) nbJ = nb;  // partials of J
   __shared__ double wJ[4], wS[4], wN[4];
   __shared__ long long wU[4], wE[4], wP[4];
   __shared__ int wM[4];
@@ -4292,14 +4350,14 @@ __device__ void conclude_block(PassState* __restrict__ st, const double* __restr
     a1 = ld_agent(&jslots[2 * lane + 1]);
   }
   // partials of four blocks in flight per thread, added in block order
-  for (int64_t b0 = tid; b0 < nb; b0 += 1024) {
+  for (int64_t b0 = tid; b0 < max(nb, nbJ); b0 += 1024) {
     double jv[4];
     long long uv[4], pv[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       const int64_t b = b0 + 256 * u;
       const bool in = b < nb;
-      jv[u] = in && !jslots ? ld_agent(&Jpart[b]) : 0.0;
+      jv[u] = b < nbJ && !jslots ? ld_agent(&Jpart[b]) : 0.0;
       uv[u] = in ? ld_agent(&upart[2 * b]) : 0;
       pv[u] = in ? ld_agent(&upart[2 * b + 1]) : 0;
     }
@@ -4833,9 +4891,9 @@ __global__ __launch_bounds__(256) void k_reseed(const T* __restrict__ X, int d, 
 __global__ __launch_bounds__(256) void k_sum_J(PassState* __restrict__ st,
                                                const double* __restrict__ Jpart,
                                                const long long* __restrict__ upart, int64_t nb,
-                                               long long* __restrict__ jslots) {
+                                               long long* __restrict__ jslots, int64_t nbJ) {
   conclude_block(st, Jpart, upart, nb, jslots, nullptr, nullptr, nullptr, 0, false, nullptr,
-                 nullptr);
+                 nullptr, false, nbJ);
 }
 
 // ============================================================================
@@ -6346,9 +6404,12 @@ PassPlan plan_pass(int64_t rows, int32_t d, int32_t k, int dtype, int precision,
   // a persistent grid: no more blocks than stay resident at once
   const int64_t res = dtype == 0 ? plan_blocks<float>(p, cus) : plan_blocks<uint16_t>(p, cus);
   p.blocks = std::max<int64_t>(1, std::min<int64_t>({work, res, (int64_t)kMaxBlocks}));
-  if (p.split)
+  if (p.split) {
     p.rr_blocks = dtype == 0 ? resident_blocks(k_resolve<float>, 0, cus)
                              : resident_blocks(k_resolve<uint16_t>, 0, cus);
+    p.lj_blocks = dtype == 0 ? resident_blocks(k_label_J<float>, 0, cus)
+                             : resident_blocks(k_label_J<uint16_t>, 0, cus);
+  }
   if (p.bf16) {
     // the re-rank's blocks walk ranges of the points in a grid-stride loop:
     // all of them resident, so none waits for a second round of blocks
@@ -6541,6 +6602,25 @@ static void dispatch_resolve(const PassBufs& b, const PassPlan& p, const int32_t
                      (const PassState*)b.st, gate, b.labels);
 }
 
+// J of a labelling pass; returns its partials, and their number in nb.  They take
+// the label order's buffer where that holds more of them than Jpart.
+template <typename T>
+static double* dispatch_label_J(const PassBufs& b, const PassPlan& p, const int32_t* gate,
+                                int64_t* nb, hipStream_t s) {
+  // a long row's chain of pieces is shared by more lanes where the rows are too few
+  // to fill the GPU without (which leaves lanes idle in its last piece: 1e6 x 300
+  // BF16 with 64 lanes a row 2.05 ms in all, 1.97 with 16)
+  const bool few = b.n < p.lj_blocks * kLabelRows * 16;
+  const int glog = !few || b.d <= 256 ? 4 : b.d <= 1024 ? 6 : 8;
+  const int64_t rows = kLabelRows * (256 >> glog);
+  const int64_t most = std::max(p.blocks, std::min<int64_t>(b.n / 2, p.lj_blocks));
+  *nb = std::min<int64_t>((b.n + rows - 1) / rows, most);
+  double* part = *nb > p.blocks ? reinterpret_cast<double*>(b.perm) : b.Jpart;
+  hipLaunchKernelGGL(k_label_J<T>, dim3((unsigned)*nb), dim3(256), 0, s, (const T*)b.X, b.n, b.d,
+                     (const double*)b.c64, (const int32_t*)b.labels, gate, glog, part);
+  return part;
+}
+
 hipError_t pass_assign(const PassBufs& b, const PassPlan& p, bool update, hipStream_t s) {
   const int32_t* gate = update ? &b.st->done : b.label_gate;
   if (p.split) {
@@ -6576,9 +6656,14 @@ hipError_t pass_rest(const PassBufs& b, const PassPlan& p, bool update, hipStrea
     }
   }
   // The sorted update makes the sums of an update pass and, with the BF16
-  // and split screens, J of every pass; the FP32 kernels add J themselves in a
-  // labelling pass.
-  const bool sorted = !p.fused && (update || p.bf16 || p.split);
+  // screen, J of every pass; the FP32 kernels add J themselves in a labelling
+  // pass, and the split screen has a kernel for it.
+  const bool sorted = !p.fused && (update || p.bf16);
+  const double* Jpart = b.Jpart;
+  int64_t nbJ = nb;
+  if (p.split && !update)
+    Jpart = b.dtype == 0 ? dispatch_label_J<float>(b, p, gate, &nbJ, s)
+                         : dispatch_label_J<uint16_t>(b, p, gate, &nbJ, s);
   if (sorted) sorted_update(b, p, update, gate, s);
   if (update) {
     const int cpb = std::max(1, finalize_cpb(b.d, plan_slots(p)));
@@ -6606,8 +6691,8 @@ hipError_t pass_rest(const PassBufs& b, const PassPlan& p, bool update, hipStrea
       else far((const uint16_t*)b.X);
     }
   } else {
-    hipLaunchKernelGGL(k_sum_J, dim3(1), dim3(256), 0, s, b.st, (const double*)b.Jpart,
-                       (const long long*)b.upart, nb, sorted ? b.jslots : nullptr);
+    hipLaunchKernelGGL(k_sum_J, dim3(1), dim3(256), 0, s, b.st, Jpart, (const long long*)b.upart,
+                       nb, sorted ? b.jslots : nullptr, nbJ);
   }
   return hipGetLastError();
 }

@@ -816,3 +816,22 @@ def test_split_screen_undecided_points_keep_pace(what):
     auto, fp32 = _best_ms(lambda: call("auto")), _best_ms(lambda: call("fp32"))
     print(f"[pace] {what}: auto {auto:.3f} ms, fp32 {fp32:.3f} ms", flush=True)
     assert auto <= 1.25 * fp32
+
+
+@pytest.mark.parametrize("f", [1.0, 1e5, 1e8, 1e11, 1e15])
+@pytest.mark.parametrize("d,k,dtype", [(17, 1200, "f32"), (64, 256, "f32"), (65, 200, "f32"),
+                                       (300, 40, "f32"), (300, 64, "bf16"), (20, 1000, "bf16")])
+def test_assign_J_beside_a_far_center(d, k, dtype, f):
+    """J of a labelling is the FP64 sum of the rows' squared distances, also where
+    one row, at a center of its own, lies f times as far out as the others."""
+    Xh = _mixture(10_007, d, min(k, 50), seed=d + k, dtype=dtype)
+    C = _centers_from(Xh, k, seed=k, jitter=0.3)
+    far = (widen(Xh)[777] * f).astype(np.float32)
+    if dtype == "bf16":
+        far = (far.view(np.uint32) & 0xffff0000).view(np.float32)
+    Xh[777] = far if dtype == "f32" else (far.view(np.uint32) >> 16).astype(np.uint16)
+    C[5] = far
+    lab, J, _ = km.km_assign(to_device(Xh), torch.from_numpy(C).cuda())
+    rlab, D1, _ = oracle.assign(Xh, C)
+    assert np.array_equal(lab.cpu().numpy(), rlab)
+    assert abs(J - D1.sum()) <= 1e-12 * D1.sum(), (J, D1.sum())
