@@ -153,3 +153,23 @@ def test_check_finite_rejects_before_any_pass():
     with pytest.raises(km.KMeansError) as e:
         km.kmeans_fit_ex(to_device(Xh), 5, 0.01, 3, 10, 1e-4, check_finite=True)
     assert e.value.status == km.KM_EINVAL
+
+
+# the split screen for rows of any dims, whose center copy lies inside the slot rows
+SPLIT_ANY_D = [(64, 256, "f32"), (300, 24, "f32"), (129, 130, "f32"), (300, 30, "bf16"),
+               (20, 900, "bf16")]
+
+
+@pytest.mark.parametrize("d,k,dtype", SPLIT_ANY_D)
+def test_trace_on_split_screen_any_d(d, k, dtype):
+    test_trace_matches_oracle("split any d", 20_011, d, k, dtype, "auto")
+
+
+@pytest.mark.parametrize("d,k,dtype", [(300, 12, "f32"), (64, 200, "f32"), (300, 12, "bf16")])
+def test_reseed_on_split_screen_any_d(d, k, dtype):
+    test_reseed_matches_oracle("split any d", 20_000, d, k, dtype, "auto")
+
+
+@pytest.mark.parametrize("d,k,dtype", SPLIT_ANY_D)
+def test_caller_workspace_on_split_screen_any_d(d, k, dtype):
+    test_caller_workspace(d, k, dtype)

@@ -835,3 +835,12 @@ def test_assign_J_beside_a_far_center(d, k, dtype, f):
     rlab, D1, _ = oracle.assign(Xh, C)
     assert np.array_equal(lab.cpu().numpy(), rlab)
     assert abs(J - D1.sum()) <= 1e-12 * D1.sum(), (J, D1.sum())
+
+
+@pytest.mark.parametrize("d,k", [(129, 2), (143, 2), (144, 2), (145, 2), (300, 2), (320, 2),
+                                 (129, 1), (300, 1)])
+@pytest.mark.parametrize("n", [1, 257, 3_001])
+def test_split_screen_any_d_one_and_two_centers(d, k, n):
+    """Two centers on both sides of where their padded copy fits beside the sums
+    (143, 144 and 320 dims), and one, which never takes the screen."""
+    test_split_screen_any_d(d, k, "f32", n)

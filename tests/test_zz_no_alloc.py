@@ -65,3 +65,12 @@ def test_static_fit_rejects_problems_beyond_its_array():
             ctypes.byref(info))
     assert rc == km.KM_ENOMEM
     assert "scratch" in km.kmeans_last_error()
+
+
+@pytest.mark.parametrize("n,d,k,dtype", [(20_011, 64, 256, "f32"), (5_003, 300, 40, "f32"),
+                                         (5_003, 300, 30, "bf16")])
+def test_static_fit_on_split_screen_any_d(n, d, k, dtype):
+    spec = synth.MixtureSpec(d, 40, "uniform", -20.0, 20.0, sigma_lo=0.5, sigma_hi=2.0,
+                             weights="dirichlet1")
+    X = torch.from_numpy(synth.generate(spec, d + k, n, "f32")).cuda()
+    _compare(X if dtype == "f32" else X.bfloat16(), k, 0.1, 3, 8, 0.0)
