@@ -5187,13 +5187,15 @@ __global__ __launch_bounds__(256, 2) void k_batch_pair(const BatchHead* __restri
       double x64[KD];
 #pragma unroll
       for (int q = 0; q < KD; ++q) x64[q] = (double)x[q];
-      auto dist64 = [&](int j) {  // FP64 direct form over the whole row (zero past d)
+      // FP64 direct form over the whole row (zero past d), rounded as the FP64 check
+      // rounds it, so that it breaks ties as the check would
+      auto dist64 = [&](int j) {
         const double* cj = cs + j * CSS;
         double p = 0.0;
 #pragma unroll
         for (int q = 0; q < KD; ++q) {
           const double e = x64[q] - cj[q];
-          p = __builtin_fma(e, e, p);
+          p = p + e * e;
         }
         return p;
       };

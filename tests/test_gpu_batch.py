@@ -448,3 +448,34 @@ def test_batch_large_problem_of_few_centers_keeps_pace(n, d, k):
     fp32 = {2: 5.7, 8: 9.1, 16: 9.3}[d] * 5450.0 / gbs
     print(f"[pace] n={n} d={d} k={k}: {best:.2f} ms, FP32 kernel {fp32:.2f} ms", flush=True)
     assert best <= 1.1 * fp32
+
+
+@pytest.mark.parametrize("e", [-30, -50, -62, -70])
+@pytest.mark.parametrize("d,k,dtype", [(2, 5, "f32"), (8, 33, "f32"), (16, 256, "f32"),
+                                       (16, 30, "bf16"), (40, 60, "bf16")])
+def test_batch_small_norms(d, k, dtype, e):
+    """Rows scaled by 2^e to where FP32 squares vanish: the fit of the unscaled
+    rows, scaled."""
+    test_batch_large_norms(d, k, dtype, e)
+
+
+@pytest.mark.parametrize("d,dtype", [(3, "f32"), (7, "f32"), (15, "f32"), (16, "f32"), (11, "bf16")])
+def test_batch_ties_of_whole_number_rows(d, dtype):
+    """Rows of small whole numbers, whose points often lie as far from one center
+    as from another: labels, passes and centers exactly the oracle's (the sums
+    are exact, and FP64 distances are rounded in its order)."""
+    rng = np.random.default_rng(d)
+    probs, data = [], []
+    for i in range(30):
+        n, k = int(rng.integers(200, 900)), int(rng.integers(20, 100))
+        Xh = np.round(rng.normal(0, 1.2, size=(n, d)) + rng.integers(-3, 4, size=(n, 1)))
+        Xh = Xh.astype(np.float32)
+        if dtype == "bf16":
+            Xh = (Xh.view(np.uint32) >> 16).astype(np.uint16)
+        data.append(Xh)
+        probs.append((to_device(Xh), k, 0.5, i, (4, 4), (0.0, 0.0)))
+    for Xh, p, (C, L, info) in zip(data, probs, km.kmeans_fit_batch(probs)):
+        ref = oracle.fit(Xh, *p[1:])
+        assert np.array_equal(L.cpu().numpy(), ref.labels)
+        assert np.array_equal(C.cpu().numpy(), ref.centers.astype(np.float32))
+        assert info["iters"] == ref.info["iters"]
