@@ -3604,7 +3604,9 @@ __device__ __forceinline__ void load4_f64(const double* __restrict__ row, int t0
 
 // Exact decisions of open points by groups of 16 lanes (4 dims a lane of each
 // 64): direct form in FP32 with its error bound, FP64 when the best two are
-// closer than that; lowest index among equal distances.
+// closer than that, and FP64 summed in index order (dist64_row, as the FP32
+// kernels' check has it) when the rounding of the lanes' sums could decide;
+// lowest index among equal distances.
 template <typename T>
 struct Resolver {
   const T* X;
@@ -3613,13 +3615,14 @@ struct Resolver {
   const float* cw;
   const double* c64;
   float rel, u2c;
+  double tie;
   // FP32 direct form over a lane's 4 ceil(d / 64) terms and four pairwise adds,
   // plus 2 sqrt(D) ||c - cw|| for the rounded center
   __device__ __forceinline__ Resolver(const T* X_, int d_, int k_, const float* cw_,
                                       const double* c64_, float cmax)
       : X(X_), d(d_), k(k_), dw(on_dwords(X_, d_)), cw(cw_), c64(c64_),
         rel((float)(4 * ((d_ + 63) / 64) + 6) * 0x1p-24f * 1.01f),
-        u2c(2.f * 0x1p-24f * 1.01f * cmax) {}
+        u2c(2.f * 0x1p-24f * 1.01f * cmax), tie((d_ + 16) * 0x1p-51) {}
   __device__ __forceinline__ float err(float D) const { return rel * D + sqrtf(D) * u2c + 1e-30f; }
   __device__ __forceinline__ bool close(float b, float s) const {
     return !((s - b) > err(b) + err(s));
@@ -3673,8 +3676,9 @@ struct Resolver {
       }
     }
   }
-  // FP64 distance of center j into the running best
-  __device__ __forceinline__ void rank64(int64_t i, int j, double& bD, int& b64) const {
+  // FP64 distance of center j into the running best two
+  __device__ __forceinline__ void rank64(int64_t i, int j, double& bD, double& sD,
+                                         int& b64) const {
     const T* xr = X + i * d;
     double p = 0.0;
     for (int t0 = 4 * (threadIdx.x & 15); t0 < d; t0 += 64) {
@@ -3693,10 +3697,31 @@ struct Resolver {
     p += __shfl_xor(p, 4);
     p += __shfl_xor(p, 2);
     p += __shfl_xor(p, 1);
-    if (p < bD || (p == bD && j < b64)) {
+    if (p < bD) {
+      sD = bD;
       bD = p;
       b64 = j;
+    } else {
+      sD = fmin(sD, p);
     }
+  }
+  // Whether rounding (of d + 5 additions here, d there) could order the two otherwise
+  __device__ __forceinline__ bool tied(double bD, double sD) const {
+    return sD < INFINITY && !(sD - bD > tie * sD);
+  }
+  // The nearest of the group's candidates, one per lane (none: j < 0), in index order.
+  __device__ __forceinline__ int ordered(int64_t i, int j) const {
+    double D = j >= 0 ? dist64_row<T>(X + i * d, c64 + (int64_t)j * d, d) : INFINITY;
+    if (j < 0) j = INT_MAX;
+    for (int o = 8; o > 0; o >>= 1) {
+      const double oD = __shfl_xor(D, o);
+      const int oj = __shfl_xor(j, o);
+      if (oD < D || (oD == D && oj < j)) {
+        D = oD;
+        j = oj;
+      }
+    }
+    return j;
   }
 };
 
@@ -3752,8 +3777,8 @@ __device__ __forceinline__ void decide_all(const T* __restrict__ X, int d, int k
         for (int p = 0; p < 4; ++p) {
           const float2 x = *reinterpret_cast<const float2*>(&xs[(4 * wave + p) * TD + t]);
           const double a = (double)x.x - c.x, b = (double)x.y - c.y;
-          part[p] = __builtin_fma(a, a, part[p]);
-          part[p] = __builtin_fma(b, b, part[p]);
+          part[p] = part[p] + a * a;  // (as dist64_row)
+          part[p] = part[p] + b * b;
         }
       }
     }
@@ -4095,9 +4120,11 @@ __global__ __launch_bounds__(256, 2) void k_screen_split(
           rs.rank4(i, cj, best, sec, bj);
         }
         if (rs.close(best, sec)) {
-          double bD = INFINITY;
+          double bD = INFINITY, sD = INFINITY;
           bj = INT_MAX;
-          for (int u = 0; u < c; ++u) rs.rank64(i, cand_j[q * CMAX + u], bD, bj);
+          for (int u = 0; u < c; ++u) rs.rank64(i, cand_j[q * CMAX + u], bD, sD, bj);
+          const int li = threadIdx.x & 15;
+          if (rs.tied(bD, sD)) bj = rs.ordered(i, li < c ? cand_j[q * CMAX + li] : -1);
         }
         if ((threadIdx.x & 15) == 0) labels[i] = bj < k ? bj : 0;
       }
@@ -4188,7 +4215,7 @@ __global__ __launch_bounds__(256, 2) void k_screen_split(
 // lanes take one point each.  Points of all centers are listed from the other end
 // and go 16 at a time (decide_all).  (Decided one by one by the blocks of the second
 // sweep, a pass of 2e5 x 64, k = 256 that no point could be screened in took 4.8 ms
-// against 0.93, and a fit of rows equal to ten of them 123 ms against 6.0; with the
+// against 1.1, and a fit of rows equal to ten of them 123 ms against 6.9; with the
 // FP32 kernels 4.5 and 31.)
 template <typename T>
 __global__ __launch_bounds__(256) void k_resolve(
@@ -4236,11 +4263,15 @@ __global__ __launch_bounds__(256) void k_resolve(
       int bj = INT_MAX;
       rs.rank4(pt, cj, best, sec, bj);
       if (rs.close(best, sec)) {
-        double bD = INFINITY;
+        double bD = INFINITY, sD = INFINITY;
         bj = INT_MAX;
 #pragma unroll
         for (int u = 0; u < 4; ++u)
-          if (cj[u] >= 0 && cj[u] != bj) rs.rank64(pt, cj[u], bD, bj);
+          if (cj[u] >= 0 && (u == 0 || cj[u] != cj[0])) rs.rank64(pt, cj[u], bD, sD, bj);
+        if (rs.tied(bD, sD)) {
+          const int j = li < nf ? (code >> (bg * li)) & GM : k;
+          bj = rs.ordered(pt, j < k ? j : -1);
+        }
       }
       if (li == 0) labels[pt] = bj < k ? bj : 0;
     }

@@ -844,3 +844,27 @@ def test_split_screen_any_d_one_and_two_centers(d, k, n):
     """Two centers on both sides of where their padded copy fits beside the sums
     (143, 144 and 320 dims), and one, which never takes the screen."""
     test_split_screen_any_d(d, k, "f32", n)
+
+
+@pytest.mark.parametrize("d,k,dtype", [(17, 1200, "f32"), (20, 900, "bf16"), (64, 200, "f32"),
+                                       (129, 60, "f32"), (300, 40, "f32"), (300, 40, "bf16")])
+def test_split_screen_any_d_ties_of_whole_number_rows(d, k, dtype):
+    """Rows of small whole numbers at centers that are averages of a few of them,
+    so that points often lie as far from one center as from another: exactly the
+    oracle's labels, as FP64 distances are rounded in its order."""
+    for seed in range(6):
+        rng = np.random.default_rng(seed)
+        base = rng.integers(-2, 3, size=(12, d)).astype(np.float64)
+        Xw = base[rng.integers(0, 12, size=4_001)].copy()
+        flip = rng.random(Xw.shape) < 3.0 / d
+        Xw[flip] += rng.integers(-1, 2, size=int(flip.sum()))
+        Xh = Xw.astype(np.float32)
+        if dtype == "bf16":
+            Xh = (Xh.view(np.uint32) >> 16).astype(np.uint16)
+        C = np.stack([Xw[rng.choice(4_001, size=m, replace=False)].mean(0) if m > 1 else
+                      base[rng.integers(0, 12)] + rng.permutation(np.eye(d)[0]) / 3
+                      for m in rng.choice([1, 1, 1, 3], size=k)])
+        lab, _, _ = km.km_assign(to_device(Xh), torch.from_numpy(C).cuda())
+        rlab, _, _ = oracle.assign(Xh, C)
+        bad = np.where(lab.cpu().numpy() != rlab)[0]
+        assert len(bad) == 0, (seed, len(bad), bad[:5])
