@@ -62,9 +62,11 @@ typedef enum {
   KM_PREC_AUTO = 0,        /* d <= 16 and k <= 128: split BF16 MFMA screen (-2c and FP32 points as
                               BF16 high + low parts, FP32 accumulation); BF16 data with 32 <= d
                               <= 256: BF16 MFMA + re-rank; other data with d > 16 whose cluster
-                              sums do not fit in LDS: split BF16 MFMA screen; otherwise FP32.
-                              Every screen is certified: points its error band cannot decide get
-                              exact (FP32 with its error bound, then FP64) decisions */
+                              sums do not fit in LDS, 2 <= k <= 16384: split BF16 MFMA screen
+                              (where its padded center copy fits in half of the slot rows: k = 2
+                              only at some d); otherwise FP32.  Every screen is certified: points
+                              its error band cannot decide get exact (FP32 with its error bound,
+                              then FP64) decisions */
   KM_PREC_FP32 = 1,        /* FP32 distances, FP64 check of uncertain points */
   KM_PREC_BF16_RERANK = 2  /* BF16 MFMA x.c^T, FP32 re-rank of the top 4, FP64 check */
 } km_precision;
@@ -79,9 +81,10 @@ typedef struct {
   int64_t dist_evals;    /* k*(m*iters[0] + n*iters[1]) + k*n: point-center distances the method needs */
   double shift[2];       /* last largest center movement of each stage */
   int64_t uncertain;     /* labels the screen could not settle among its best candidates, summed
-                            over passes: the check over all centers (FP32 and split screen
-                            paths); on the BF16 screen path the points queued for the
-                            re-screen, plus those it sends to the FP64 check */
+                            over passes: the FP64 check over all centers (FP32 and small-d
+                            paths); points swept again (split screen beyond); on the BF16
+                            screen path the points queued for the re-screen, plus those it
+                            sends to the FP64 check */
   double seconds[3];     /* wall time of sampling, fast stage, slow stage + final labels */
   int64_t fp64_pairs;    /* labels decided among a short candidate list, summed over passes:
                             FP64 distances to the best two (FP32 and small-d paths), the two

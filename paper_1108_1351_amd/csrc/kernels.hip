@@ -3830,8 +3830,9 @@ __device__ __forceinline__ void decide_all(const T* __restrict__ X, int d, int k
 // the threshold becomes a candidate, decided in the same kernel if there are at
 // most 16, and otherwise left to k_resolve.
 // Why 256 points x 32 CT centers: 2 x CT accumulator tiles per wave reuse every
-// center operand for two point tiles, and two such blocks fit a CU (64 KB of
-// LDS, 256 VGPRs a wave), one wave's key updates beside another's MFMAs.
+// center operand for two point tiles, and two such blocks fit a CU (at four steps a
+// chunk 37 KB of LDS each, 42 KB in the second sweep, and 256 VGPRs a wave), one
+// wave's key updates beside another's MFMAs.
 template <typename T, int KC, bool LIST>
 __global__ __launch_bounds__(256, 2) void k_screen_split(
     const T* __restrict__ X, int64_t n, int d, int k, int nq, int bg,
@@ -5011,7 +5012,7 @@ __global__ __launch_bounds__(256) void k_batch_assign(const BatchHead* __restric
 
 // The batched pass of small dims (d <= 16, k <= 256) on the split BF16 screen of
 // k_fused_pair: one launch per padded row length KD for all its instances.  A
-// work unit is 512 points of one instance; the block first lays the instance's
+// work unit is 512 points or more of one instance; the block first lays the instance's
 // FP64 centers, split A operands and C input out in LDS (about 4 us), then each
 // wave takes 64 points at a time as two 32-point tiles.  A lane ranks 16 scores of
 // both tiles per 32 centers with four VALU operations each, where the FP32 form
@@ -6834,7 +6835,8 @@ hipError_t fill_uniform(void* p, int kind, int64_t count, uint64_t seed, hipStre
   return hipGetLastError();
 }
 
-hipError_t prep_copy(const PassBufs& b, const PassPlan& p, hipStream_t s) {
+// Writes the plan's BF16 center copy.
+static hipError_t prep_copy(const PassBufs& b, const PassPlan& p, hipStream_t s) {
   if (!copy16(p)) return hipSuccess;
   return prep_bf16(b.c64, b.k, b.d, p.ks * 16, b.st, copy_hi(b, p), b.cnB, s, copy_lo(b, p),
                    p.split ? split_rows(b.k) : 0);

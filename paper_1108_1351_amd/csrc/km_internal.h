@@ -183,7 +183,8 @@ struct PassBufs {
   double* shiftj; int32_t* emptyj;
   long long* slots;    // [kSlots][k][d+1] exact cluster sums (counts last); zero between passes
   long long* jslots;   // [kSlots][2] J of the sorted update as limbs of 2^-FJ, 2^(40-FJ); zeroed
-  uint32_t* perm;      // [n] point indices in label order (sorted update)
+  uint32_t* perm;      // [n] point indices in label order (sorted update); before that the
+                       //   split screen's queue, in its labelling pass the partials of J
   long long* scnt;     // [k * sort_chunks] label counts per chunk, then their offsets; for
                        //   k <= 4096 the first k: label totals, then positions, 0 between passes
   long long* stot;     // [scan tiles + 1] tile totals of the offset scan
@@ -284,13 +285,10 @@ hipError_t fill_uniform(void* p, int kind, int64_t count, uint64_t seed, hipStre
 
 PassPlan plan_pass(int64_t rows, int32_t d, int32_t k, int dtype, int precision,
                    size_t lds_limit, int cus);
-// Clears the sums the plan's passes add into (slot rows, J limbs, label totals),
-// and writes its BF16 center copy.
 // A stage's set-up: pass state, sums, row statistics, scale, the screens' center
 // copy; with C the centers are taken from there first.
 hipError_t stage_open(const PassBufs& b, const PassPlan& p, const double* C, int32_t max_iter,
                       double tol, int reseed, hipStream_t s);
-hipError_t prep_copy(const PassBufs& b, const PassPlan& p, hipStream_t s);
 hipError_t lloyd_pass(const PassBufs& b, const PassPlan& p, bool update, hipStream_t s);
 // the assignment kernel of a pass (for the BF16 path, its screen of all points), and
 // everything after it (re-screen, update, reduction, stop test)
